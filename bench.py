@@ -49,18 +49,19 @@ sys.path.insert(0, ROOT)
 
 METRIC = "solvent particle-steps/s + % HBM peak; batched FP32 vs FP64; p50/p99 job latency"
 HBM_PEAK_GBS = 8000.0
-REC_BYTES = {8: 64, 4: 32}          # staging record of the scatter, per particle
+REC_BYTES = {8: 64, 4: 32}          # a particle's record
 
 
 def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
                       flow: bool = False) -> float:
     """Bytes a kernel must move per launch given its inputs and outputs (not
-    counting re-reads), tb = bytes of the storage type, R = staging record:
-    stream_bin  per free particle: read x, v (6 tb) + list flag (1), write x
+    counting re-reads), tb = bytes of the storage type, R = record:
+    stream      per free particle: read x, v (6 tb) + state (1), write x
                 (3 tb) + key/rank (8); cell counters 8 B per cell.  With a
-                flow every particle also writes v (12 tb + 9).
-    scatter     per particle: read key/rank (8), cell start (4), x, v (6 tb),
-                id (4), state (1); write the record (R).
+                flow every particle also writes v (12 tb + 9).  (In small
+                systems it is a part of the chain's launch.)
+    perm        per particle: read key/rank (8), cell start (4); write the
+                array position (4).
     collide     per particle: read the record (R); write x, v (6 tb), id (4),
                 state (1), list flag (1); per cell: read the start (4), zero
                 the counter (4).
@@ -69,10 +70,10 @@ def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
     analysis    per particle: read x (3 tb) and state (1)."""
     nf = max(n - n_cand, 0)
     R = REC_BYTES[tb]
-    if kernel == "stream_bin":
+    if kernel in ("stream", "stream_bin"):
         return nf * ((12 if flow else 9) * tb + 9) + 8 * ncell
-    if kernel == "scatter":
-        return n * (6 * tb + 17 + R)
+    if kernel == "perm":
+        return n * 16
     if kernel == "collide":
         return n * (R + 6 * tb + 6) + 8 * ncell
     if kernel == "scan_final":
@@ -243,7 +244,7 @@ def run_single(name, precision, steps, warmup, profile_steps, tun, keep=False):
     _log(f"{name} fp{precision} kernels {json.dumps(kernels)}")
     # the dominant bandwidth-bound kernel: the largest event time among the
     # particle kernels (the MD chain is latency-bound, reported apart)
-    hbm_kernels = [k for k in ("collide", "stream_bin", "scatter") if k in kern]
+    hbm_kernels = [k for k in ("collide", "stream", "perm") if k in kern]
     traffic = traffic_table(name, precision)
     dom = max(hbm_kernels, key=lambda k: kern[k][0] * kern[k][1])
     avg_ms = kern[dom][0]
@@ -656,7 +657,7 @@ def main():
         _log("janus32 fp64")
         r = run_single("janus32", 64, 10, 2, 3, tun)
         extras["janus32_fp64"] = dict(value=r["value"], chain=r["chain"],
-                                      kernels={k: r["kernels"][k] for k in ("chain", "collide", "stream_bin")
+                                      kernels={k: r["kernels"][k] for k in ("chain", "collide", "stream")
                                                if k in r["kernels"]}, flags=r["flags"])
         for prec in (64, 32):
             _log(f"poiseuille fp{prec}")

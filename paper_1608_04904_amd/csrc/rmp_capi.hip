@@ -5,9 +5,9 @@
 // block (descriptors and work-list prefixes) in device memory.  One tick
 // launches, for all occupied replicas at once:
 //
-//   [ k_chain  ||  k_stream_bin ]  (fork/join on a side stream)
-//   k_scan_blocks, k_scan_final, k_scatter, k_collide, k_chunk_scan,
-//   k_cand_write
+//   [ k_chain  ||  k_stream ]  (in large launches on a side stream, in small
+//   ones in one launch), k_scan_blocks, k_scan_final, k_perm, k_collide,
+//   k_chunk_scan, k_cand_write
 //
 // optionally replayed from a captured hipGraph.
 #include "rmp_kernels.hip"
@@ -147,7 +147,7 @@ Sizes sizes_of(const rmp_params* p)
 
 // offsets of every array inside a replica workspace
 struct Layout {
-    size_t cp, rs, x[2], v[2], id[2], st[2], keyrank, stage, cflag, count, start, scanblk,
+    size_t cp, rs, rec[2], keyrank, perm, xchg, lbits, count, start, scanblk, axes, bulk, tilemask,
         chunk_cnt, chunk_off, cand_idx, order, partials, epart, tpart, bigmask, ptable, obs_part, mean, total;
 };
 
@@ -160,17 +160,16 @@ Layout layout_of(const rmp_params* p)
     auto take = [&](size_t bytes) { size_t r = o; o = aup(o + (bytes ? bytes : 1)); return r; };
     L.cp = take(sizeof(ColloidParams));
     L.rs = take(sizeof(RepState));
-    for (int b = 0; b < 2; ++b) {
-        L.x[b] = take(3 * s.n * tb);
-        L.v[b] = take(3 * s.n * tb);
-        L.id[b] = take(4 * s.n);
-        L.st[b] = take(s.n);
-    }
+    for (int b = 0; b < 2; ++b) L.rec[b] = take((tb == 8 ? sizeof(Rec<double>) : sizeof(Rec<float>)) * s.n);
     L.keyrank = take(8 * s.n);
-    L.stage = take((tb == 8 ? sizeof(Rec<double>) : sizeof(Rec<float>)) * s.n);
-    L.cflag = take(s.n);
+    L.perm = take(4 * s.n);
+    L.xchg = take(8 * s.n);
+    L.lbits = take(8 * (size_t)(CHUNK / 64) * s.n_chunks);
     L.count = take(4 * s.ncell);
     L.start = take(4 * (s.ncell + 1));
+    L.axes = take(3 * 8 * (size_t)s.ncell);
+    L.bulk = take(2 * 8 * (size_t)s.ncell);
+    L.tilemask = take(4 * (size_t)s.n_tiles_max);
     L.scanblk = take(4 * (size_t)s.n_scanblk);
     L.chunk_cnt = take(4 * (size_t)s.n_chunks);
     L.chunk_off = take(4 * (size_t)s.n_chunks);
@@ -192,10 +191,10 @@ size_t ctl_bytes_for(int32_t nslots)
     return aup(sizeof(RepDesc) * (size_t)nslots) + 6 * aup(4 * (size_t)(nslots + 1)) + aup(16);
 }
 
-const char* KNAMES[] = {"stream_bin", "chain", "scan_blocks", "scan_final", "scatter",
-                        "collide", "chunk_scan", "cand_write", "list", "analysis"};
-enum { KN_STREAM, KN_CHAIN, KN_SCANB, KN_SCANF, KN_SCATTER, KN_COLLIDE, KN_CHUNKSCAN,
-       KN_CANDW, KN_LIST, KN_ANALYSIS, KN_COUNT };
+const char* KNAMES[] = {"stream", "chain", "scan_blocks", "scan_final", "perm", "collide",
+                        "chunk_scan", "cand_write", "list", "analysis"};
+enum { KN_STREAM, KN_CHAIN, KN_SCANB, KN_SCANF, KN_PERM, KN_COLLIDE, KN_CHUNKSCAN, KN_CANDW, KN_LIST, KN_ANALYSIS,
+       KN_COUNT };
 
 struct Replica {
     bool used = false;
@@ -237,10 +236,12 @@ struct rmp_batch {
     std::vector<int32_t> hprefix[6];
     int32_t totals[6] = {};
     bool dirty = true;
-    bool have_rule[2] = {false, false};
+    bool have_rule[2][3] = {};      // [rule][wave form, dense, flow] among the occupied slots
     bool multi_scan = false;
     int32_t max_scanblk = 0;        // most scan blocks of any occupied slot
     bool any_analysis = false;
+    bool any_colloid = false;                 // some occupied slot has colloids
+    bool any_free = false, any_flow = false;  // occupied slots without and with a flow
     bool any_iterative = false;     // some occupied slot uses the iterative RATTLE
     int64_t n_total = 0;            // solvent particles over the occupied slots
     int32_t device = 0;             // device current at creation (its stream's device)
@@ -329,6 +330,10 @@ rmp_status last_launch(const char* what)
 }
 
 constexpr int64_t CHAIN_PRIO_MAX_PARTICLES = (int64_t)1 << 22;
+// particles from which the streaming is a launch of its own next to the MD
+// chain: its kernel then has more than four waves per SIMD to hold, while in
+// the chain's launch it gets the chain's registers, two waves per SIMD
+constexpr int64_t CHAIN_SIDE_N = (int64_t)1 << 20;
 
 // Shape of the MD-chain workgroups: NT threads with K list entries each.
 // Shapes 0, 1, 2: 256 threads with K = 1, 2, 4; shape 3: 512 threads, K = 1.
@@ -410,23 +415,44 @@ ChainShape chain_shape_of(const rmp_batch* b)
     return ChainShape{256, k, k == 1 ? 0 : (k == 2 ? 1 : 2)};
 }
 
-// Threads and particles per thread of the collision workgroup (a group of
-// cells holds at most their product of particles)
-int collide_nt(const rmp_batch* b) { return b->tun.collide_block == 512 ? 512 : 256; }
+// Threads and slots per lane of the collision's wave form (a wave's run of
+// cells holds at most 64 times the latter).  With many tiles a workgroup is
+// one wave, which takes the runs of its tile one after the other and so has
+// the next run's index loads and the last run's ranks in flight; with few,
+// four waves share a tile.
+constexpr int64_t COLLIDE_ONE_WAVE_N = (int64_t)1 << 21;
+
+int collide_nt(const rmp_batch* b)
+{
+    if (b->tun.collide_block == 256 || b->tun.collide_block == 512) return b->tun.collide_block;
+    int64_t n = 0;
+    for (const auto& R : b->reps)
+        if (R.used) n += R.p.n_solvent;
+    return n >= COLLIDE_ONE_WAVE_N ? 64 : 256;
+}
 int collide_ppt(const rmp_batch* b) { return b->tun.collide_ppt == 1 ? 1 : 2; }
 
-// Cells per collision tile: the slot's override, else the batch tuning,
-// else sized so that the mean tile holds about 0.94 of a group's capacity
-// (measured at 128^3, rho 10: 48 cells 1.16 ms, 39 cells 1.29 ms, 32 cells
-// 1.49 ms per collision; a tile beyond the capacity takes a second group),
-// between MIN_TILE_CELLS and COLL_TCMAX
+// Particles per cell beyond which the collision takes the workgroup form: at
+// 32 a run of 128 slots holds three whole cells or four, so a wave has a
+// quarter of its lanes idle, and a cell beyond 128 particles would take the
+// one-by-one path
+constexpr double DENSE_RHO = 32.0;
+
+bool dense_of(int64_t ncell, int64_t n) { return ncell > 0 && (double)n > DENSE_RHO * (double)ncell; }
+
+// Cells per collision tile: the slot's override, else the batch tuning, else
+// sized so that the mean tile fills TILE_FILL of the workgroup's slots (runs
+// end at whole cells; a tile beyond one run per wave takes another round), in
+// the workgroup form 0.94; between MIN_TILE_CELLS and COLL_TCMAX
+constexpr double TILE_FILL = 0.86;
+
 int tile_cells_of(const rmp_batch* b, int override_cells, int64_t ncell, int64_t n)
 {
     int tc = override_cells > 0 ? override_cells : b->tun.collide_cells;
     if (tc <= 0) {
         const double rho = ncell > 0 ? (double)n / (double)ncell : 1.0;
-        const double cap = (double)(collide_nt(b) * collide_ppt(b));
-        tc = rho > 0.0 ? (int)(0.94 * cap / rho) : COLL_TCMAX;
+        const double cap = dense_of(ncell, n) ? 0.94 * 512.0 : TILE_FILL * (double)(std::max(collide_nt(b), 256) * collide_ppt(b));
+        tc = rho > 0.0 ? (int)std::min(cap / rho, (double)COLL_TCMAX) : COLL_TCMAX;
     }
     if (tc < MIN_TILE_CELLS) tc = MIN_TILE_CELLS;
     if (tc > COLL_TCMAX) tc = COLL_TCMAX;
@@ -460,6 +486,8 @@ void fill_desc(rmp_batch* b, Replica& r)
     D.tile_cells = tile_cells_of(b, r.tile_cells, s.ncell, s.n);
     D.n_tiles = (int32_t)((s.ncell + D.tile_cells - 1) / D.tile_cells);
     D.n_scanblk = s.n_scanblk;
+    D.nc = p->n_colloids;
+    D.dense = dense_of(s.ncell, s.n) ? 1 : 0;
     D.cand_cap = s.cand_cap;
     const ChainShape cs = chain_shape_of(b);
     const int K = cs.k;
@@ -493,20 +521,23 @@ void fill_desc(rmp_batch* b, Replica& r)
     // colloid, so the margin sets speed only, never results
     D.cull_me = 5.0 * std::sqrt(p->kT / p->mass) * (r.n_md * p->dt) + 0.5;
     D.cull_margin = D.cull_me + 0.5 * p->skin;
+    // the tile masks' speed cap: six thermal speeds (one particle in 10^7 is
+    // faster), and room for two cells however cold the system; a wave with a
+    // faster particle tests every colloid
+    D.vcap = std::max(6.0 * D.vscale, 2.0 / (3.0 * D.tau));
     D.bulk_on = p->bulk_rate > 0.0 ? 1 : 0;
     D.seed = r.seed;
-    for (int q = 0; q < 2; ++q) {
-        D.x[q] = w + L.x[q];
-        D.v[q] = w + L.v[q];
-        D.id[q] = (uint32_t*)(w + L.id[q]);
-        D.st[q] = (uint8_t*)(w + L.st[q]);
-    }
-    D.keyrank = (uint64_t*)(w + L.keyrank);
-    D.stage = (void*)(w + L.stage);
-    D.cflag = (uint8_t*)(w + L.cflag);
+    for (int q = 0; q < 2; ++q) D.rec[q] = w + L.rec[q];
     D.count = (uint32_t*)(w + L.count);
+    D.keyrank = (uint64_t*)(w + L.keyrank);
+    D.perm = (uint32_t*)(w + L.perm);
+    D.xchg = (double*)(w + L.xchg);
+    D.lbits = (uint64_t*)(w + L.lbits);
     D.start = (uint32_t*)(w + L.start);
     D.scanblk = (uint32_t*)(w + L.scanblk);
+    D.axes = (double*)(w + L.axes);
+    D.bulk = (double*)(w + L.bulk);
+    D.tilemask = (uint32_t*)(w + L.tilemask);
     D.chunk_cnt = (uint32_t*)(w + L.chunk_cnt);
     D.chunk_off = (uint32_t*)(w + L.chunk_off);
     D.cand_idx = (uint32_t*)(w + L.cand_idx);
@@ -661,10 +692,11 @@ rmp_status sync_ctl(rmp_batch* b)
     if (!b->dirty) return RMP_OK;
     const int S = b->nslots;
     for (int k = 0; k < 6; ++k) b->hprefix[k].assign(S + 1, 0);
-    b->have_rule[0] = b->have_rule[1] = false;
+    std::memset(b->have_rule, 0, sizeof(b->have_rule));
     b->multi_scan = false;
     b->max_scanblk = 0;
     b->any_analysis = false;
+    b->any_free = b->any_flow = b->any_colloid = false;
     b->any_iterative = false;
     b->n_total = 0;
     for (int r = 0; r < S; ++r) {
@@ -676,10 +708,12 @@ rmp_status sync_ctl(rmp_batch* b)
             items[PF_TILE] = R.desc.n_tiles;
             items[PF_SCAN] = R.desc.n_scanblk;
             items[PF_CHAIN] = R.desc.G;
-            b->have_rule[R.p.rule] = true;
+            b->have_rule[R.p.rule][R.desc.dense ? 1 : R.desc.flow ? 2 : 0] = true;
             if (R.desc.n_scanblk > 1) b->multi_scan = true;
             b->max_scanblk = std::max(b->max_scanblk, R.desc.n_scanblk);
             if (R.an) b->any_analysis = true;
+            (R.desc.flow ? b->any_flow : b->any_free) = true;
+            if (R.desc.nc > 0) b->any_colloid = true;
             if (iterative_rattle(&R.p)) b->any_iterative = true;
             b->n_total += R.p.n_solvent;
             b->hdesc[r] = R.desc;
@@ -722,6 +756,8 @@ Work work(const rmp_batch* b, int kind)
     w.nrep = b->nslots;
     w.flags = 0;
     w.budget = barrier_budget(b);
+    w.n_chain = b->totals[PF_CHAIN];
+    w.chunks = b->d_prefix[PF_CHUNK];
     return w;
 }
 
@@ -783,15 +819,29 @@ void launch_chain_shape(rmp_batch* b, hipStream_t s, dim3 g, bool ticket, int nc
     else hipLaunchKernelGGL((k_chain<T, K, false, 0, NT>), g, blk, 0, s, w);
 }
 
+// more chain workgroups than the device holds at once: ticketed work list
+bool chain_ticket(const rmp_batch* b, const ChainShape& cs)
+{
+    return b->totals[PF_CHAIN] > b->chain_resident[chain_nc(b) ? 1 : 0][cs.q];
+}
+
+// Small launches with one or two colloids per system stream in the chain's
+// launch: the fork to a side stream and the join (about 17 us) would cost
+// more than they hide, the streaming before or after the chain about 22 us.
+bool stream_in_chain(const rmp_batch* b)
+{
+    return b->tun.chain_serial == 0 && b->n_total < CHAIN_SIDE_N && chain_nc(b) != 0 && b->any_free &&
+           !b->any_flow && !chain_ticket(b, chain_shape_of(b));
+}
+
 template <class T>
-rmp_status launch_chain(rmp_batch* b, hipStream_t s)
+rmp_status launch_chain(rmp_batch* b, hipStream_t s, bool with_stream)
 {
     Timer tm(b, KN_CHAIN, s);
     const ChainShape cs = chain_shape_of(b);
-    const dim3 g(b->totals[PF_CHAIN]);
     const int nc = chain_nc(b);
-    // more workgroups than the device holds at once: ticketed work list
-    const bool ticket = b->totals[PF_CHAIN] > b->chain_resident[nc ? 1 : 0][cs.q];
+    const bool ticket = chain_ticket(b, cs);
+    const dim3 g(b->totals[PF_CHAIN] + (with_stream ? b->totals[PF_CHUNK] * (CHUNK / cs.nt) : 0));
     Work w = work(b, PF_CHAIN);
     // small launches: the chain's dependent steps are the whole critical
     // path, so its waves take issue priority over the streaming kernel that
@@ -823,22 +873,24 @@ rmp_status launch_list(rmp_batch* b)
     }
     {
         Timer tm(b, KN_CANDW, s);
-        hipLaunchKernelGGL(k_cand_write, dim3(b->totals[PF_CHUNK]), dim3(256), 0, s, work(b, PF_CHUNK));
+        hipLaunchKernelGGL((k_cand_write<T>), dim3(b->totals[PF_CHUNK]), dim3(256), 0, s, work(b, PF_CHUNK));
     }
     return last_launch("list build");
 }
 
-template <class T, int RULE>
+template <class T, int RULE, bool FLOW>
 void launch_collide_rule(rmp_batch* b, hipStream_t s)
 {
     const dim3 g(b->totals[PF_TILE]);
     const Work w = work(b, PF_TILE);
     const int xcd = b->tun.collide_xcd;
     const int nt = collide_nt(b), ppt = collide_ppt(b);
-    if (nt == 512 && ppt == 2) hipLaunchKernelGGL((k_collide<T, RULE, 512, 2>), g, dim3(512), 0, s, w, xcd);
-    else if (nt == 512) hipLaunchKernelGGL((k_collide<T, RULE, 512, 1>), g, dim3(512), 0, s, w, xcd);
-    else if (ppt == 2) hipLaunchKernelGGL((k_collide<T, RULE, 256, 2>), g, dim3(256), 0, s, w, xcd);
-    else hipLaunchKernelGGL((k_collide<T, RULE, 256, 1>), g, dim3(256), 0, s, w, xcd);
+#define RMP_COLLIDE(NT, PPT)                                                                  \
+    if (nt == NT && ppt == PPT)                                                               \
+        hipLaunchKernelGGL((k_collide<T, RULE, NT, PPT, FLOW>), g, dim3(NT), 0, s, w, xcd);
+    RMP_COLLIDE(64, 1) RMP_COLLIDE(64, 2) RMP_COLLIDE(256, 1) RMP_COLLIDE(256, 2)
+    RMP_COLLIDE(512, 1) RMP_COLLIDE(512, 2)
+#undef RMP_COLLIDE
 }
 
 // every collision launch is followed by the pass over the cells beyond a
@@ -849,10 +901,18 @@ void launch_collide(rmp_batch* b, hipStream_t s, int rule)
     const int items = b->totals[PF_TILE];
     const dim3 gb((unsigned)((items + 63) / 64));
     if (rule == 0) {
-        launch_collide_rule<T, 0>(b, s);
+        if (b->have_rule[0][0]) launch_collide_rule<T, 0, false>(b, s);
+        if (b->have_rule[0][2]) launch_collide_rule<T, 0, true>(b, s);
+        if (b->have_rule[0][1])
+            hipLaunchKernelGGL((k_collide_dense<T, 0, 256, 2>), dim3(items), dim3(256), 0, s, work(b, PF_TILE),
+                               b->tun.collide_xcd);
         hipLaunchKernelGGL((k_collide_big<T, 0>), gb, dim3(256), 0, s, work(b, PF_TILE), items);
     } else {
-        launch_collide_rule<T, 1>(b, s);
+        if (b->have_rule[1][0]) launch_collide_rule<T, 1, false>(b, s);
+        if (b->have_rule[1][2]) launch_collide_rule<T, 1, true>(b, s);
+        if (b->have_rule[1][1])
+            hipLaunchKernelGGL((k_collide_dense<T, 1, 256, 2>), dim3(items), dim3(256), 0, s, work(b, PF_TILE),
+                               b->tun.collide_xcd);
         hipLaunchKernelGGL((k_collide_big<T, 1>), gb, dim3(256), 0, s, work(b, PF_TILE), items);
     }
 }
@@ -863,26 +923,30 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
 {
     const int nch = b->totals[PF_CHUNK];
     if (nch == 0) return RMP_OK;
-    // fork: the MD chain runs on the side stream next to the streaming
-    // kernel (chain_serial: before it, on the same stream)
-    const bool serial = b->tun.chain_serial != 0;
+    // in large launches the MD chain runs on the side stream next to the
+    // streaming kernel, in small ones in one launch with it (stream_in_chain);
+    // without colloids the chain only closes counters
+    const bool serial = b->tun.chain_serial != 0 || b->n_total < CHAIN_SIDE_N || !b->any_colloid;
+    const bool fused = stream_in_chain(b);
     if (!serial) {
         HIPCHK(hipEventRecord(b->fork, s));
         HIPCHK(hipStreamWaitEvent(b->side, b->fork, 0));
     }
-    rmp_status st = launch_chain<T>(b, serial ? s : b->side);
+    rmp_status st = launch_chain<T>(b, serial ? s : b->side, fused);
     if (st != RMP_OK) return st;
-    {
+    // stream_block threads holding stream_ppt particles each (1, 2 or 4)
+    int bs = b->tun.stream_block;
+    if (bs != 64 && bs != 128 && bs != 256) bs = 256;
+    const int ppt = b->tun.stream_ppt == 2 || b->tun.stream_ppt == 4 ? b->tun.stream_ppt : 1;
+    const int wpc = CHUNK / (bs * ppt), wpc1 = CHUNK / bs;
+    const dim3 gp(nch * wpc);
+    if (!fused) {
         Timer tm(b, KN_STREAM, s);
-        // stream_block threads holding stream_ppt particles each (1, 2 or 4)
-        int bs = b->tun.stream_block;
-        if (bs != 64 && bs != 128 && bs != 256) bs = 256;
-        const int ppt = b->tun.stream_ppt == 2 || b->tun.stream_ppt == 4 ? b->tun.stream_ppt : 1;
-        const int wpc = CHUNK / (bs * ppt);
-        const dim3 g(nch * wpc);
-        if (ppt == 4) hipLaunchKernelGGL((k_stream_bin<T, 4>), g, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
-        else if (ppt == 2) hipLaunchKernelGGL((k_stream_bin<T, 2>), g, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
-        else hipLaunchKernelGGL((k_stream_bin<T, 1>), g, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        const Work w = work(b, PF_CHUNK);
+        if (b->any_free && ppt == 4) hipLaunchKernelGGL((k_stream<T, 4, false>), gp, dim3(bs), 0, s, w, wpc);
+        else if (b->any_free && ppt == 2) hipLaunchKernelGGL((k_stream<T, 2, false>), gp, dim3(bs), 0, s, w, wpc);
+        else if (b->any_free) hipLaunchKernelGGL((k_stream<T, 1, false>), gp, dim3(bs), 0, s, w, wpc);
+        if (b->any_flow) hipLaunchKernelGGL((k_stream<T, 1, true>), dim3(nch * wpc1), dim3(bs), 0, s, w, wpc1);
     }
     if (!serial) {
         HIPCHK(hipEventRecord(b->join, b->side));
@@ -899,13 +963,15 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
         hipLaunchKernelGGL(k_scan_final, dim3(b->totals[PF_SCAN]), dim3(1024), 0, s, work(b, PF_SCAN), direct);
     }
     {
-        Timer tm(b, KN_SCATTER, s);
-        hipLaunchKernelGGL((k_scatter<T>), dim3(nch), dim3(256), 0, s, work(b, PF_CHUNK));
+        Timer tm(b, KN_PERM, s);
+        if (ppt == 4) hipLaunchKernelGGL((k_perm<4>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        else if (ppt == 2) hipLaunchKernelGGL((k_perm<2>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        else hipLaunchKernelGGL((k_perm<1>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
     }
     {
         Timer tm(b, KN_COLLIDE, s);
         for (int rule = 0; rule < 2; ++rule)
-            if (b->have_rule[rule]) launch_collide<T>(b, s, rule);
+            if (b->have_rule[rule][0] || b->have_rule[rule][1] || b->have_rule[rule][2]) launch_collide<T>(b, s, rule);
     }
     {
         Timer tm(b, KN_CHUNKSCAN, s);
@@ -913,7 +979,7 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
     }
     {
         Timer tm(b, KN_CANDW, s);
-        hipLaunchKernelGGL(k_cand_write, dim3(nch), dim3(256), 0, s, work(b, PF_CHUNK));
+        hipLaunchKernelGGL((k_cand_write<T>), dim3(nch), dim3(256), 0, s, work(b, PF_CHUNK));
     }
     if (b->any_analysis) {
         Timer tm(b, KN_ANALYSIS, s);
@@ -1112,7 +1178,7 @@ void batch_release(rmp_batch* b)
     if (b->join) (void)hipEventDestroy(b->join);
     if (b->side) (void)hipStreamDestroy(b->side);
     if (b->capture) (void)hipStreamDestroy(b->capture);
-    b->gexec = nullptr; b->graph = nullptr; b->fork = b->join = nullptr; b->side = nullptr;
+    b->gexec = nullptr; b->graph = nullptr; b->fork = b->join = nullptr; b->side = nullptr; 
     b->capture = nullptr;
     b->ev.clear();
 }
@@ -1201,29 +1267,33 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
     return rs.flags ? RMP_EDEVICE : RMP_OK;
 }
 
+// The state is exchanged field by field: a kernel splits one field off the
+// records into the workspace's exchange array (or merges it in), a plain copy
+// moves it from or to the caller's buffer.
 template <class T>
 rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
 {
     Replica& R = b->reps[slot];
+    rmp_status st = sync_ctl(b);
+    if (st != RMP_OK) return st;
     hipStream_t s = b->stream;
     HIPCHK(hipStreamSynchronize(s));
     RepState rs;
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));
     const int cur = (int)(rs.coll_step & 1);
     const int64_t n = R.sz.n;
-    if (dst->x || dst->v) {
-        std::vector<T> buf((size_t)3 * n);
-        if (dst->x) {
-            HIPCHK(hipMemcpy(buf.data(), R.ws + R.lay.x[cur], 3 * n * sizeof(T), hipMemcpyDeviceToHost));
-            for (int64_t i = 0; i < 3 * n; ++i) dst->x[i] = (double)buf[i];
-        }
-        if (dst->v) {
-            HIPCHK(hipMemcpy(buf.data(), R.ws + R.lay.v[cur], 3 * n * sizeof(T), hipMemcpyDeviceToHost));
-            for (int64_t i = 0; i < 3 * n; ++i) dst->v[i] = (double)buf[i];
-        }
+    for (int f = 0; f < 8 && n > 0; ++f) {
+        char* to = f < 3 ? (char*)dst->x : f < 6 ? (char*)dst->v : f == 6 ? (char*)dst->id : (char*)dst->state;
+        if (!to) continue;
+        const size_t w = f < 6 ? 8 : f == 6 ? 4 : 1;
+        hipLaunchKernelGGL((k_field_out<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const RepDesc*)(b->d_desc + slot), cur, f);
+        st = last_launch("k_field_out");
+        if (st != RMP_OK) return st;
+        HIPCHK(hipMemcpyAsync(to + (f < 6 ? (size_t)(f % 3) * n * 8 : 0), R.ws + R.lay.xchg, w * n,
+                              hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
     }
-    if (dst->id) HIPCHK(hipMemcpy(dst->id, R.ws + R.lay.id[cur], 4 * n, hipMemcpyDeviceToHost));
-    if (dst->state) HIPCHK(hipMemcpy(dst->state, R.ws + R.lay.st[cur], n, hipMemcpyDeviceToHost));
     for (int c = 0; c < R.p.n_colloids; ++c)
         for (int d = 0; d < 3; ++d) {
             if (dst->X) dst->X[3 * c + d] = rs.X[c][d];
@@ -1296,24 +1366,26 @@ rmp_status set_state_t(rmp_batch* b, int slot, const rmp_host_state* src)
     Replica& R = b->reps[slot];
     rmp_status cst = check_state(&R.p, src);
     if (cst != RMP_OK) return cst;
+    cst = sync_ctl(b);
+    if (cst != RMP_OK) return cst;
     hipStream_t s = b->stream;
     HIPCHK(hipStreamSynchronize(s));
     RepState rs;
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));
     const int64_t n = R.sz.n;
     const int cur = (int)(src->coll_step & 1);
-    std::vector<T> buf((size_t)3 * n);
-    for (int d = 0; d < 3; ++d)
-        for (int64_t i = 0; i < n; ++i) {
-            T xt = (T)src->x[d * n + i];
-            if ((double)xt >= (double)R.p.L[d]) xt = (T)0;
-            buf[d * n + i] = xt;
-        }
-    HIPCHK(hipMemcpy(R.ws + R.lay.x[cur], buf.data(), 3 * n * sizeof(T), hipMemcpyHostToDevice));
-    for (int64_t i = 0; i < 3 * n; ++i) buf[i] = (T)src->v[i];
-    HIPCHK(hipMemcpy(R.ws + R.lay.v[cur], buf.data(), 3 * n * sizeof(T), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(R.ws + R.lay.id[cur], src->id, 4 * n, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(R.ws + R.lay.st[cur], src->state, n, hipMemcpyHostToDevice));
+    for (int f = 0; f < 8 && n > 0; ++f) {
+        const char* from = f < 3 ? (const char*)src->x : f < 6 ? (const char*)src->v
+                         : f == 6 ? (const char*)src->id : (const char*)src->state;
+        const size_t w = f < 6 ? 8 : f == 6 ? 4 : 1;
+        HIPCHK(hipMemcpyAsync(R.ws + R.lay.xchg, from + (f < 6 ? (size_t)(f % 3) * n * 8 : 0), w * n,
+                              hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL((k_field_in<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const RepDesc*)(b->d_desc + slot), cur, f);
+        cst = last_launch("k_field_in");
+        if (cst != RMP_OK) return cst;
+        HIPCHK(hipStreamSynchronize(s));
+    }
     for (int c = 0; c < R.p.n_colloids; ++c)
         for (int d = 0; d < 3; ++d) {
             rs.X[c][d] = src->X[3 * c + d];
@@ -1322,6 +1394,7 @@ rmp_status set_state_t(rmp_batch* b, int slot, const rmp_host_state* src)
         }
     rs.md_step = src->md_step;
     rs.coll_step = src->coll_step;
+    rs.list_nmd = -1;           // list and cells of the coming collision are stale
     HIPCHK(hipMemcpy(R.ws + R.lay.rs, &rs, sizeof(rs), hipMemcpyHostToDevice));
     // the MD chain's exchange words carry epochs derived from the step
     // counters; a state that sets the counters back must not meet words left

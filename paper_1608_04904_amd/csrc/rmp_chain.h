@@ -3,19 +3,11 @@
 // rmp_chain_f32.hip, next to the other kernels, so that the library builds in
 // parallel.
 #pragma once
-#include "rmp_util.h"
+#include "rmp_stream.h"
 
 namespace rmp {
 
 // ------------------------------------------------------------- MD chain
-
-// ordering of LDS accesses between lanes of one wave (no workgroup barrier)
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ __forceinline__ double shfl_d(double v, int src)
 {
@@ -302,18 +294,6 @@ __device__ __forceinline__ void rattle_vel_lane(const BondLane& L, const double 
 // Chain workgroup g of a replica holds Verlet-list positions
 // [g*B, (g+1)*B), B = NT*K (NT = 256 or 512 threads), K consecutive
 // positions per thread, in registers for the whole interval.
-__device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ double uniform_d(double v)
-{
-    return __longlong_as_double((long long)uniform_u64((uint64_t)__double_as_longlong(v)));
-}
-
 // Descriptor fields used in every MD step, copied to scalar registers once:
 // read through the descriptor they are fetched again after each fence of
 // the exchange.
@@ -1216,11 +1196,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
     const int cur = (int)(coll & 1);
     const int64_t md0 = rs->md_step;
     const int nmd = D.n_md;
-    const int64_t n = D.n;
-    const gptr<T> xb[3] = {G(comp<T>(D.x[cur], n, 0)), G(comp<T>(D.x[cur], n, 1)), G(comp<T>(D.x[cur], n, 2))};
-    const gptr<T> vb[3] = {G(comp<T>(D.v[cur], n, 0)), G(comp<T>(D.v[cur], n, 1)), G(comp<T>(D.v[cur], n, 2))};
-    const gptr<uint8_t> stb = G(D.st[cur]);
-    const gptr<const uint32_t> idb = G(D.id[cur]);
+    const gptr<Rec<T>> rb = G(recs<T>(D, cur));
     const gptr<const uint32_t> cand = G(D.cand_idx);
 
     bool valid[K];
@@ -1236,11 +1212,11 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
         valid[j] = pos < ncand;
         idx[j] = valid[j] ? (int64_t)cand[pos] : 0;
         for (int d = 0; d < 3; ++d) {
-            x[j][d] = valid[j] ? xb[d][idx[j]] : (T)0;
-            v[j][d] = valid[j] ? vb[d][idx[j]] : (T)0;
+            x[j][d] = valid[j] ? rb[idx[j]].x[d] : (T)0;
+            v[j][d] = valid[j] ? rb[idx[j]].v[d] : (T)0;
         }
-        st[j] = valid[j] ? stb[idx[j]] : 0;
-        pid[j] = valid[j] ? idb[idx[j]] : 0;
+        st[j] = valid[j] ? (uint8_t)(rb[idx[j]].st & ST_PUBLIC) : (uint8_t)0;
+        pid[j] = valid[j] ? rb[idx[j]].id : 0;
         for (int d = 0; d < 3; ++d) x0[j][d] = x[j][d];
     }
     __syncthreads();
@@ -1412,17 +1388,16 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
     }
     __syncthreads();
     // write back list entries and bin them for the coming collision
-    double s3[3];
-    shift_of(D.seed, coll, s3);
+    const double s3[3] = {rs->shift[0], rs->shift[1], rs->shift[2]};
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         if (!valid[j]) continue;
         const int64_t i = idx[j];
         for (int d = 0; d < 3; ++d) {
-            xb[d][i] = x[j][d];
-            vb[d][i] = v[j][d];
+            rb[i].x[d] = x[j][d];
+            rb[i].v[d] = v[j][d];
         }
-        stb[i] = st[j];
+        rb[i].st = (uint32_t)st[j] | ST_LIST;
         uint32_t key = cell_key(D, (double)x[j][0], (double)x[j][1], (double)x[j][2], s3);
         const uint32_t rank = __hip_atomic_fetch_add(G(D.count) + key, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         G(D.keyrank)[i] = ((uint64_t)key << 32) | rank;
@@ -1480,7 +1455,17 @@ __global__ __launch_bounds__(NT) void k_chain(Work w)
     // only in the one- and two-colloid variants: with the priority code in
     // the generic variant its 128^3 launches ran 10 % slower even with the
     // flag off
-    if constexpr (NC == 1 || NC == 2)
+    if constexpr (!TICKET && NC > 0) {
+        // the workgroups past the chain's stream, where the streaming shares
+        // the launch (they start after the chain's and wait for nothing)
+        const int sb = (int)blockIdx.x - w.n_chain;
+        if (sb >= 0) {
+            stream_body<T, 1, false, NT>(w.desc, w.chunks, w.nrep, xcd_range(sb, (int)gridDim.x - w.n_chain),
+                                         CHUNK / NT);
+            return;
+        }
+    }
+    if constexpr (NC > 0)
         if (w.flags & WORK_CHAIN_PRIO) __builtin_amdgcn_s_setprio(3);
     if (!TICKET) {
         chain_run<T, K, NC, NT>(w, (int)blockIdx.x);

@@ -63,6 +63,9 @@ __device__ __forceinline__ double u01o(uint64_t w) { return ((double)(w >> 11) +
 __device__ __forceinline__ double tfma(double a, double b, double c) { return fma(a, b, c); }
 __device__ __forceinline__ float tfma(float a, float b, float c) { return fmaf(a, b, c); }
 
+__device__ __forceinline__ double tabs(double a) { return fabs(a); }
+__device__ __forceinline__ float tabs(float a) { return fabsf(a); }
+
 // periodic wrap of a solvent coordinate after a drift
 template <class T>
 __device__ __forceinline__ T wrap_coord(T x, T L)

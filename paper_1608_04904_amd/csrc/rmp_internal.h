@@ -60,6 +60,8 @@ struct RepState {
     uint32_t bar;              // inter-workgroup barrier counter of the MD chain
     double U, e_rxn;
     double T_sum, T_cells;     // temperature estimator of the last collision
+    double shift[3];           // grid shift of the coming collision (k_chunk_scan)
+    double Xw[MAXC][3];        // periodic images of the colloids at the coming collision (k_perm)
     double X[MAXC][3], V[MAXC][3], F[MAXC][3];
 };
 
@@ -77,23 +79,26 @@ struct Analysis {
     double* msd;               // [nb][cap]
 };
 
-// A particle's record in the staging array that the scatter fills in cell
-// order for the collision: one aligned 64-byte record in FP64 (32 bytes in
-// FP32), so that the scatter writes and the collision reads whole sectors.
-// FP64: x[3], v[3], id, old index, state byte.  FP32: x[3], v[3], then id and
-// old index (both < 2^31) with the state's catalysis bit in bit 31 of the id
-// word and its species bit in bit 31 of the index word.
+// A particle's record, the form in which the solvent state is held in device
+// memory: one aligned 64-byte record in FP64, 32 bytes in FP32, so that the
+// collision gathers each particle through the sort permutation with whole
+// sectors and writes whole sectors back.  st: bit 0 species, bit 1 catalysis
+// flag, bit 2 Verlet-list member for the coming interval (library internal).
+// The position and the first velocity component fill the record's first 32
+// (16) bytes, so that streaming rewrites whole sectors.
 template <class T> struct Rec;
 template <> struct alignas(64) Rec<double> {
     double x[3], v[3];
-    uint32_t id, idx;
-    uint32_t st, pad;
+    uint32_t id, st;
+    uint32_t pad[2];
 };
 template <> struct alignas(32) Rec<float> {
     float x[3], v[3];
-    uint32_t id_f, idx_s;
+    uint32_t id, st;
 };
 static_assert(sizeof(Rec<double>) == 64 && sizeof(Rec<float>) == 32, "record sizes");
+constexpr uint32_t ST_PUBLIC = 3u;   // species and catalysis flag
+constexpr uint32_t ST_LIST = 4u;     // Verlet-list member
 
 // Per-replica descriptor, written by the host.
 struct RepDesc {
@@ -104,9 +109,12 @@ struct RepDesc {
     int32_t n_chunks, n_tiles, n_scanblk, tile_cells;
     int32_t cand_cap, G;       // Verlet-list capacity, MD-chain workgroups
     int32_t chain_k;
+    int32_t nc;                // colloids
+    int32_t dense;             // collision form: 0 a wave per run of cells, 1 a workgroup per group of cells
     int32_t hbits;             // cell sort rank: >= 0 Hilbert index with hbits bits, KEY_TABLE, KEY_ROW
     double Ld[3], halfL[3];
     double dt, h, tau, vscale, mass, ca, sa, cat_prob, skin_half2;
+    double vcap;               // speed up to which tilemask holds
     double cull_me, cull_margin; // MD chain cull: entry displacement allowed per interval; + skin/2
     int32_t bulk_on, pad1;
     int32_t flow;              // constant acceleration and/or walls: every particle streams
@@ -115,16 +123,14 @@ struct RepDesc {
     int32_t pad2;
     double g[3];               // constant acceleration
     uint64_t seed;
-    void* x[2];                // [3][n] storage-type arrays, double-buffered
-    void* v[2];
-    uint32_t* id[2];
-    uint8_t* st[2];
-    uint64_t* keyrank;         // (key << 32) | rank
-    void* stage;               // [n] particle records in cell order (Rec<T>), written by the scatter
-    uint32_t* count;           // [ncell]
+    void* rec[2];              // [n] particle records (Rec<T>) in array order; buffer coll_step & 1 is the state
+    uint64_t* keyrank;         // [n] (key << 32) | rank in the coming collision, by array position
+    uint32_t* perm;            // [n] array position of the particle in each slot of the coming collision
+    uint32_t* count;           // [ncell] particles per cell of the coming collision; zero between intervals
     uint32_t* start;           // [ncell + 1]
     uint32_t* scanblk;         // [n_scanblk]
-    uint8_t* cflag;            // [n] Verlet-list membership for the coming interval
+    double* xchg;              // [n] one component of the state, for the exchange with the host
+    uint64_t* lbits;           // [16 n_chunks] Verlet-list membership bits; zero outside chunks with members
     uint32_t* chunk_cnt;       // [n_chunks]
     uint32_t* chunk_off;       // [n_chunks]
     uint32_t* cand_idx;        // [cand_cap]
@@ -132,6 +138,9 @@ struct RepDesc {
     const uint32_t* cell_of;   // [ncell] cell of a sort rank
     double* partials;          // [2][G * ROWW + BCW] 64-bit exchange words of the MD chain
     double* epart;             // [G][2] reaction energy / flips of the interval
+    double* axes;              // [ncell][3] rotation axes of the coming collision, by sort rank (k_perm)
+    double* bulk;              // [ncell][2] its bulk-reaction uniforms
+    uint32_t* tilemask;        // [n_tiles] colloids whose list reach meets the tile at speeds up to vcap
     double* tpart;             // [n_tiles][4] collision partials: temperature sum, cells, reaction energy, flips
     uint64_t* bigmask;         // [n_tiles] cells of a tile beyond a collision group's capacity
     double* ptable;            // [RMP_PTABLE]
@@ -153,6 +162,10 @@ struct Work {
     int32_t nrep;
     int32_t flags;    // WORK_CHAIN_PRIO: the MD chain raises its waves' issue priority
     uint64_t budget;  // MD chain: longest wait for the other workgroups, 100 MHz ticks
+    // MD chain launch: its own workgroups, and the prefixes of the particle
+    // chunks that the workgroups after them stream
+    int32_t n_chain;
+    const int32_t* chunks;
 };
 
 }  // namespace rmp

@@ -6,27 +6,30 @@
 // randomly shifted grid with the RMPCD bulk reaction.  Kernels of one
 // interval, in stream order:
 //
-//   k_stream_bin   particles outside the Verlet list: n_md drifts held in
-//                  registers, then the cell key of the next collision and an
-//                  atomic rank (HBM-bound, one pass over x, v)
+//   k_stream       particles outside the Verlet list: n_md drifts held in
+//                  registers, the cell of the coming collision and an atomic
+//                  rank in it; the collision's random numbers per cell
 //   k_chain        Verlet-list particles and colloids: n_md MD steps in
 //                  persistent workgroups; colloid forces reduced with a fixed
-//                  binary tree over list positions; inter-workgroup barrier
-//                  per step when the list spans several workgroups
+//                  binary tree over list positions; inter-workgroup exchange
+//                  per step when the list spans several workgroups; then the
+//                  list particles' cells and ranks
 //   k_scan_*       exclusive scan of the cell counts -> cell_start
-//   k_scatter      each particle's record (x, v, id, old index, state) to
-//                  slot cell_start[key] + rank of the staging array
-//   k_collide      per tile of cells: read the tile's records (contiguous),
-//                  restore the stable (old-index) order inside each cell,
-//                  FP64 centre-of-mass sums,
-//                  rotation about a random axis (or Anderson thermostat),
-//                  bulk B->A reaction, Verlet-list flags for the next
-//                  interval, coalesced write of the cell-ordered arrays
+//   k_perm         array position of each particle to slot
+//                  cell_start[key] + rank of the sort permutation
+//   k_collide      per tile of cells: gather the records through the
+//                  permutation, restore the stable (old-index) order inside
+//                  each cell, FP64 centre-of-mass sums, rotation about a random
+//                  axis (or Anderson thermostat), bulk B->A reaction,
+//                  Verlet-list flags for the next interval, contiguous write
+//                  of the cell-ordered records
 //   k_chunk_scan   list compaction offsets, per-interval bookkeeping
 //   k_cand_write   compacted Verlet list
 //
-// Data layout in HBM: structure-of-arrays, x[3][N] and v[3][N] in the
-// storage precision (double or float), double-buffered across collisions.
+// Data layout in HBM: one record per particle (position, velocity, id, state
+// bits; 64 bytes in FP64, 32 in FP32), double-buffered across collisions, so
+// that the sort moves only a 4-byte permutation and the collision gathers
+// each particle with whole sectors.
 #include "rmp_chain.h"
 
 namespace rmp {
@@ -77,16 +80,16 @@ __global__ __launch_bounds__(256) void k_init(const RepDesc* Dp)
         double z[3];
         philox(0, (uint64_t)i, 0, D.seed, TAG_INIT_VEL, w);
         normals3(w, z);
+        Rec<T> q{};
         for (int d = 0; d < 3; ++d) {
             T xv = (T)xi[d];
             if (xv >= (T)D.Ld[d]) xv = (T)0;    // FP32 rounding up to L
-            comp<T>(D.x[0], n, d)[i] = xv;
-            T vv = (T)(D.vscale * z[d]);
-            comp<T>(D.v[0], n, d)[i] = vv;
-            sum[d] += (double)vv;
+            q.x[d] = xv;
+            q.v[d] = (T)(D.vscale * z[d]);
+            sum[d] += (double)q.v[d];
         }
-        D.id[0][i] = (uint32_t)i;
-        D.st[0][i] = 0;
+        q.id = (uint32_t)i;
+        recs<T>(D, 0)[i] = q;
     }
     if (bad) atomicOr(&rs->flags, RMP_FLAG_INIT);
     for (int d = 0; d < 3; ++d) {
@@ -117,16 +120,20 @@ __global__ __launch_bounds__(256) void k_init_sub(const RepDesc* Dp, const doubl
     for (int j = threadIdx.x; j < CHUNK; j += 256) {
         int64_t i = base + j;
         if (i >= n) break;
-        for (int d = 0; d < 3; ++d) {
-            T* v = comp<T>(D.v[0], n, d);
-            v[i] = (T)((double)v[i] - mean[d]);
-        }
+        T* v = recs<T>(D, 0)[i].v;
+        for (int d = 0; d < 3; ++d) v[d] = (T)((double)v[d] - mean[d]);
     }
 }
 
 // ------------------------------------------------------- Verlet list build
 
-// Stand-alone list flags (first interval, or a change of n_md).
+// Stand-alone list flags (first interval, a new state, or a change of n_md);
+// replicas whose list is valid for their n_md are left alone.
+__device__ __forceinline__ bool list_is_valid(const RepDesc& D, const RepState* rs)
+{
+    return rs->list_nmd == (int64_t)D.n_md;
+}
+
 template <class T>
 __global__ __launch_bounds__(256) void k_list(Work w)
 {
@@ -137,6 +144,7 @@ __global__ __launch_bounds__(256) void k_list(Work w)
     if (!D.active) return;
     const ColloidParams* cp = D.cp;
     RepState* rs = D.rs;
+    if (list_is_valid(D, rs)) return;
     __shared__ double sXw[MAXC][3];
     __shared__ uint32_t sred[4];
     const int nc = cp->nc;
@@ -144,19 +152,21 @@ __global__ __launch_bounds__(256) void k_list(Work w)
     if (t < nc)
         for (int d = 0; d < 3; ++d) sXw[t][d] = colloid_image(rs->X[t][d], D.Ld[d]);
     __syncthreads();
-    const int cur = (int)(rs->coll_step & 1);
+    Rec<T>* rec = recs<T>(D, (int)(rs->coll_step & 1));
     const int64_t n = D.n;
     const int64_t base = (int64_t)chunk * CHUNK;
     uint32_t cnt = 0;
     for (int j = t; j < CHUNK; j += 256) {
-        int64_t i = base + j;
-        if (i >= n) break;
-        double x0 = comp<T>(D.x[cur], n, 0)[i], x1 = comp<T>(D.x[cur], n, 1)[i],
-               x2 = comp<T>(D.x[cur], n, 2)[i];
-        double v0 = comp<T>(D.v[cur], n, 0)[i], v1 = comp<T>(D.v[cur], n, 1)[i],
-               v2 = comp<T>(D.v[cur], n, 2)[i];
-        bool c = is_candidate(D, cp, nc, sXw, D.st[cur][i], x0, x1, x2, v0, v1, v2);
-        D.cflag[i] = c ? 1 : 0;
+        const int64_t i = base + j;
+        bool c = false;
+        if (i < n) {
+            Rec<T>* r = rec + i;
+            const uint32_t st = r->st & ST_PUBLIC;
+            c = is_candidate(D, cp, nc, sXw, (uint8_t)st, r->x[0], r->x[1], r->x[2], r->v[0], r->v[1], r->v[2]);
+            r->st = st | (c ? ST_LIST : 0u);
+        }
+        const uint64_t m = __ballot(c);
+        if ((t & 63) == 0) D.lbits[i >> 6] = m;
         cnt += c ? 1u : 0u;
     }
     uint32_t tot = block_sum_u32<256>(cnt, sred);
@@ -173,6 +183,7 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(Work w, int after_collision
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     RepState* rs = D.rs;
+    if (!after_collision && list_is_valid(D, rs)) return;
     __shared__ uint32_t sbuf[16];
     __shared__ double dbuf[17 * 6];
     const int t = threadIdx.x;
@@ -272,7 +283,6 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(Work w, int after_collision
             rs->e_rxn += v[2] + v[4];
             rs->n_bulk += (int64_t)v[3];
             rs->n_cat += (int64_t)v[5];
-            rs->coll_step += 1;
         }
     }
     if (!after_collision) {
@@ -282,7 +292,12 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(Work w, int after_collision
         uint64_t* part = reinterpret_cast<uint64_t*>(D.partials);
         for (int64_t k = t; k < 2 * ((int64_t)D.G * ROWW + BCW); k += 1024) part[k] = 0ull;
     }
+    // (read before thread 0 advances the counter below)
+    const int64_t coll = rs->coll_step + (after_collision ? 1 : 0);
+    __syncthreads();
+    if (t == 64) shift_of(D.seed, coll, rs->shift);
     if (t == 0) {
+        rs->coll_step = coll;
         rs->n_cand = total;
         if ((int64_t)total > (int64_t)D.cand_cap) rs->flags |= RMP_FLAG_LIST_OVERFLOW;
         rs->bar = 0;
@@ -291,6 +306,7 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(Work w, int after_collision
 }
 
 // Compacted Verlet list in array order.
+template <class T>
 __global__ __launch_bounds__(256) void k_cand_write(Work w)
 {
     const int item = blockIdx.x;
@@ -299,238 +315,35 @@ __global__ __launch_bounds__(256) void k_cand_write(Work w)
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     // most chunks hold no list member (the list gathers around the
-    // colloids): their flags are not read at all, and their count is zero
-    // already
+    // colloids): their count is zero already, and so are their bits
     if (D.chunk_cnt[chunk] == 0u) return;
     __shared__ uint32_t sbuf[4];
     const int64_t n = D.n;
     const int64_t base = (int64_t)chunk * CHUNK;
     constexpr int PER = CHUNK / 256;
+    static_assert(PER == 4, "sixteen threads share a word of membership bits");
     const int t = threadIdx.x;
-    uint32_t f[PER];
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        int64_t i = base + (int64_t)t * PER + k;
-        f[k] = (i < n) ? (uint32_t)D.cflag[i] : 0u;
-        cnt += f[k];
-    }
+    const uint32_t f = (uint32_t)(D.lbits[(base >> 6) + (t >> 4)] >> ((t & 15) * PER)) & 15u;
     uint32_t total;
-    uint32_t pre = block_exscan_u32<256>(cnt, sbuf, &total) + D.chunk_off[chunk];
+    uint32_t pre = block_exscan_u32<256>((uint32_t)__popc(f), sbuf, &total) + D.chunk_off[chunk];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        if (f[k]) {
+        if ((f >> k) & 1u) {
             const int64_t i = base + (int64_t)t * PER + k;
             if ((int64_t)pre < (int64_t)D.cand_cap) {
                 D.cand_idx[pre] = (uint32_t)i;
-            } else {
+            } else if (i < n) {
                 // beyond the list capacity (RMP_FLAG_LIST_OVERFLOW is set):
                 // the particle is streamed freely so that every particle is
                 // still binned exactly once
-                D.cflag[i] = 0;
+                Rec<T>* r = recs<T>(D, (int)(D.rs->coll_step & 1)) + i;
+                r->st = r->st & ST_PUBLIC;
             }
             pre++;
         }
     }
+    if (t < CHUNK / 64) D.lbits[(base >> 6) + t] = 0ull;
     if (t == 0) D.chunk_cnt[chunk] = 0;
-}
-
-// ------------------------------------------------- free streaming + binning
-
-// Rank of this lane's particle within its cell, with one atomic per run of
-// equal keys in consecutive lanes (particles arrive sorted by the previous
-// collision's cells, so runs are common).  All 64 lanes must call it.
-struct RankIssue {
-    uint32_t base;             // the run head's atomic result (head lanes only)
-    int h;                     // lane of this lane's run head
-};
-
-__device__ __forceinline__ RankIssue wave_rank_issue(gptr<uint32_t> count, uint32_t key, bool valid)
-{
-    const int lane = threadIdx.x & 63;
-    const uint32_t k = valid ? key : 0xffffffffu;
-    const uint32_t prev = __shfl_up(k, 1, 64);
-    const bool head = (lane == 0) || (k != prev);
-    const uint64_t H = __ballot(head);
-    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-    const int h = 63 - __clzll(H & upto);
-    const uint64_t above = (h == 63) ? 0ull : (H & (~0ull << (h + 1)));
-    const int nexth = above ? (__ffsll((long long)above) - 1) : 64;
-    RankIssue r;
-    r.base = 0;
-    r.h = h;
-    if (head && valid)
-        r.base = __hip_atomic_fetch_add(count + key, (uint32_t)(nexth - h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return r;
-}
-
-__device__ __forceinline__ uint32_t wave_rank_finish(const RankIssue& r)
-{
-    const int lane = threadIdx.x & 63;
-    return __shfl(r.base, r.h, 64) + (uint32_t)(lane - r.h);
-}
-
-__device__ __forceinline__ uint32_t wave_rank(gptr<uint32_t> count, uint32_t key, bool valid)
-{
-    return wave_rank_finish(wave_rank_issue(count, key, valid));
-}
-
-// One streaming step under the constant acceleration g, with the plates at
-// z = 0 and z = L_z when present: half kick, drift, half kick; a drift that
-// crosses a plate is cut at the crossing time, the velocity reversed
-// (bounce-back) and the rest of the step travelled back.
-template <class T>
-__device__ __forceinline__ T below(T L);
-template <>
-__device__ __forceinline__ double below<double>(double L) { return nextafter(L, 0.0); }
-template <>
-__device__ __forceinline__ float below<float>(float L) { return nextafterf(L, 0.0f); }
-
-template <class T>
-__device__ __forceinline__ void flow_step(T (&x)[3], T (&v)[3], const T (&g)[3], T dt, T hdt,
-                                          const T (&L)[3], bool walls)
-{
-    T y[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        v[d] = tfma(hdt, g[d], v[d]);
-        y[d] = tfma(dt, v[d], x[d]);
-    }
-    if (walls) {
-        if (y[2] < (T)0 || y[2] >= L[2]) {
-            const T wz = y[2] < (T)0 ? (T)0 : L[2];
-            const T ts = (wz - x[2]) / v[2];
-            const T rem = dt - ts;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const T xc = tfma(ts, v[d], x[d]);
-                v[d] = -v[d];
-                y[d] = tfma(rem, v[d], xc);
-            }
-            if (y[2] >= L[2]) y[2] = below<T>(L[2]);
-            if (y[2] < (T)0) y[2] = (T)0;
-        }
-        x[0] = wrap_coord<T>(y[0], L[0]);
-        x[1] = wrap_coord<T>(y[1], L[1]);
-        x[2] = y[2];
-    } else {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) x[d] = wrap_coord<T>(y[d], L[d]);
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) v[d] = tfma(hdt, g[d], v[d]);
-}
-
-// Flows (constant acceleration, plates) stream every particle with flow_step
-// and write back positions and velocities.  Otherwise:
-// particles outside the Verlet list feel no force during the interval: n_md
-// drifts x <- fma(dt, v, x) with a periodic wrap after each.  The drift of a
-// coordinate is monotone, so if its final value is still inside the box no
-// wrap occurred and the per-step wrap can be skipped; otherwise the drifts
-// are replayed with the wrap.  Then the key of the shifted cell of the coming
-// collision and a rank within the cell.  Workgroup `sub` of a chunk covers
-// particles [sub*span, (sub+1)*span) of it, span = blockDim.x * PPT; thread t
-// holds particles t, t + blockDim.x, ... of its span: every load is issued
-// before the drifts, every rank atomic before the first of them is waited
-// for.
-template <class T, int PPT>
-__global__ __launch_bounds__(256) void k_stream_bin(Work w, int wg_per_chunk)
-{
-    const int item = blockIdx.x / wg_per_chunk;
-    const int sub = blockIdx.x - item * wg_per_chunk;
-    const int rep = find_rep(w.prefix, w.nrep, item);
-    const int chunk = item - w.prefix[rep];
-    const RepDesc& D = w.desc[rep];
-    if (!D.active) return;
-    RepState* rs = D.rs;
-    __shared__ double sshift[3];
-    const int64_t coll = rs->coll_step;
-    if (threadIdx.x == 0) shift_of(D.seed, coll, sshift);
-    __syncthreads();
-    const double s[3] = {sshift[0], sshift[1], sshift[2]};
-    const int cur = (int)(coll & 1);
-    const int64_t n = D.n;
-    const int nmd = D.n_md;
-    const T dt = (T)D.dt;
-    const T Lt[3] = {(T)D.Ld[0], (T)D.Ld[1], (T)D.Ld[2]};
-    const gptr<T> xs[3] = {G(comp<T>(D.x[cur], n, 0)), G(comp<T>(D.x[cur], n, 1)), G(comp<T>(D.x[cur], n, 2))};
-    const gptr<T> vs[3] = {G(comp<T>(D.v[cur], n, 0)), G(comp<T>(D.v[cur], n, 1)), G(comp<T>(D.v[cur], n, 2))};
-    const gptr<const uint8_t> cflag = G(D.cflag);
-    const gptr<uint64_t> keyrank = G(D.keyrank);
-    const gptr<uint32_t> count = G(D.count);
-    const int span = CHUNK / wg_per_chunk;
-    const int64_t base = (int64_t)chunk * CHUNK + (int64_t)sub * span;
-    if (D.flow) {
-        const T g[3] = {(T)D.g[0], (T)D.g[1], (T)D.g[2]};
-        const T hdt = (T)(0.5 * D.dt);
-        for (int j0 = 0; j0 < span; j0 += blockDim.x) {
-            const int64_t i = base + j0 + threadIdx.x;
-            bool valid = (j0 + (int)threadIdx.x < span) && (i < n);
-            if (valid) valid = cflag[i] == 0;
-            uint32_t key = 0;
-            if (valid) {
-                T x[3], v[3];
-#pragma unroll
-                for (int d = 0; d < 3; ++d) { x[d] = xs[d][i]; v[d] = vs[d][i]; }
-                for (int k = 0; k < nmd; ++k) flow_step<T>(x, v, g, dt, hdt, Lt, D.walls != 0);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) { xs[d][i] = x[d]; vs[d][i] = v[d]; }
-                key = cell_key(D, (double)x[0], (double)x[1], (double)x[2], s);
-            }
-            const uint32_t rank = wave_rank(count, key, valid);
-            if (valid) keyrank[i] = ((uint64_t)key << 32) | rank;
-        }
-        return;
-    }
-    bool valid[PPT];
-    int64_t ii[PPT];
-    T x[PPT][3], v[PPT][3];
-    const int bs = (int)blockDim.x;
-    // the flag and the state are loaded side by side, so one memory latency
-    // precedes the drifts (a list entry's state, which the MD chain on the
-    // side stream may be writing meanwhile, is loaded and never used)
-    uint8_t fl[PPT];
-#pragma unroll
-    for (int u = 0; u < PPT; ++u) {
-        ii[u] = base + u * bs + threadIdx.x;
-        valid[u] = (u * bs + (int)threadIdx.x < span) && (ii[u] < n);
-        fl[u] = valid[u] ? cflag[ii[u]] : (uint8_t)1;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            x[u][d] = valid[u] ? xs[d][ii[u]] : (T)0;
-            v[u][d] = valid[u] ? vs[d][ii[u]] : (T)0;
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < PPT; ++u) valid[u] = valid[u] && fl[u] == 0;
-    uint32_t key[PPT];
-#pragma unroll
-    for (int u = 0; u < PPT; ++u) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            T y = x[u][d];
-            for (int k = 0; k < nmd; ++k) y = tfma(dt, v[u][d], y);
-            const bool inside = (v[u][d] >= (T)0) ? (y < Lt[d]) : (y >= (T)0);
-            if (!inside) {
-                y = x[u][d];
-                for (int k = 0; k < nmd; ++k) y = wrap_coord<T>(tfma(dt, v[u][d], y), Lt[d]);
-            }
-            x[u][d] = y;
-        }
-        key[u] = valid[u] ? cell_key(D, (double)x[u][0], (double)x[u][1], (double)x[u][2], s) : 0u;
-    }
-    RankIssue ri[PPT];
-#pragma unroll
-    for (int u = 0; u < PPT; ++u) ri[u] = wave_rank_issue(count, key[u], valid[u]);
-#pragma unroll
-    for (int u = 0; u < PPT; ++u) {
-        const uint32_t rank = wave_rank_finish(ri[u]);
-        if (valid[u]) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xs[d][ii[u]] = x[u][d];
-            keyrank[ii[u]] = ((uint64_t)key[u] << 32) | rank;
-        }
-    }
 }
 
 // ------------------------------------------------------------- cell scan
@@ -543,11 +356,12 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(Work w)
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     __shared__ uint32_t sbuf[16];
+    const gptr<const uint32_t> count = G((const uint32_t*)D.count);
     const int64_t c0 = (int64_t)blk * SCAN_BLK;
     uint32_t s = 0;
     for (int k = 0; k < SCAN_BLK / 1024; ++k) {
         int64_t c = c0 + (int64_t)threadIdx.x * (SCAN_BLK / 1024) + k;
-        if (c < D.ncell) s += D.count[c];
+        if (c < D.ncell) s += count[c];
     }
     uint32_t tot = block_sum_u32<1024>(s, sbuf);
     if (threadIdx.x == 0) D.scanblk[blk] = tot;
@@ -564,6 +378,7 @@ __global__ __launch_bounds__(1024) void k_scan_final(Work w, int direct)
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     __shared__ uint32_t sbuf[16];
+    const gptr<const uint32_t> count = G((const uint32_t*)D.count);
     uint32_t pre = 0;
     if (direct) {
         // counts of cells [0, blk * SCAN_BLK): 4 loads in flight per thread
@@ -571,7 +386,7 @@ __global__ __launch_bounds__(1024) void k_scan_final(Work w, int direct)
         for (int64_t c = threadIdx.x; c < m; c += 4 * 1024) {
             uint32_t q[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) q[u] = c + u * 1024 < m ? D.count[c + u * 1024] : 0u;
+            for (int u = 0; u < 4; ++u) q[u] = c + u * 1024 < m ? count[c + u * 1024] : 0u;
             pre += (q[0] + q[1]) + (q[2] + q[3]);
         }
     } else {
@@ -585,7 +400,7 @@ __global__ __launch_bounds__(1024) void k_scan_final(Work w, int direct)
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         int64_t c = c0 + k;
-        cnt[k] = c < D.ncell ? D.count[c] : 0u;
+        cnt[k] = c < D.ncell ? count[c] : 0u;
         loc += cnt[k];
     }
     uint32_t total;
@@ -601,145 +416,147 @@ __global__ __launch_bounds__(1024) void k_scan_final(Work w, int direct)
     if (blk == D.n_scanblk - 1 && threadIdx.x == 0) D.start[D.ncell] = pre + total;
 }
 
-// Particle records of the staging array (Rec<T>): packed and unpacked with
-// the state byte split into the spare top bits of id and index in FP32.
-__device__ __forceinline__ void rec_put(Rec<double>* r, const double (&x)[3], const double (&v)[3],
-                                        uint32_t id, uint32_t idx, uint8_t st)
+// The colloids whose list reach can meet a tile after the coming collision,
+// for the tiles [tlo, thi): one wave, one colloid per lane.
+__device__ __forceinline__ void tile_masks(const RepDesc& D, int64_t tlo, int64_t thi)
 {
-    Rec<double> q;
-    q.x[0] = x[0]; q.x[1] = x[1]; q.x[2] = x[2];
-    q.v[0] = v[0]; q.v[1] = v[1]; q.v[2] = v[2];
-    q.id = id; q.idx = idx; q.st = st; q.pad = 0u;
-    *r = q;
-}
-__device__ __forceinline__ void rec_put(Rec<float>* r, const float (&x)[3], const float (&v)[3],
-                                        uint32_t id, uint32_t idx, uint8_t st)
-{
-    Rec<float> q;
-    q.x[0] = x[0]; q.x[1] = x[1]; q.x[2] = x[2];
-    q.v[0] = v[0]; q.v[1] = v[1]; q.v[2] = v[2];
-    q.id_f = id | ((uint32_t)((st >> 1) & 1u) << 31);
-    q.idx_s = idx | ((uint32_t)(st & 1u) << 31);
-    *r = q;
-}
-template <class RP>
-__device__ __forceinline__ void rec_get(RP r, double (&x)[3], double (&v)[3], uint32_t& id, uint32_t& idx,
-                                        uint8_t& st)
-{
-    x[0] = r->x[0]; x[1] = r->x[1]; x[2] = r->x[2];
-    v[0] = r->v[0]; v[1] = r->v[1]; v[2] = r->v[2];
-    id = r->id; idx = r->idx; st = (uint8_t)r->st;
-}
-template <class RP>
-__device__ __forceinline__ void rec_get(RP r, float (&x)[3], float (&v)[3], uint32_t& id, uint32_t& idx,
-                                        uint8_t& st)
-{
-    x[0] = r->x[0]; x[1] = r->x[1]; x[2] = r->x[2];
-    v[0] = r->v[0]; v[1] = r->v[1]; v[2] = r->v[2];
-    const uint32_t id_f = r->id_f, idx_s = r->idx_s;
-    id = id_f & 0x7fffffffu;
-    idx = idx_s & 0x7fffffffu;
-    st = (uint8_t)(((idx_s >> 31) & 1u) | (((id_f >> 31) & 1u) << 1));
+    const int lane = threadIdx.x & 63;
+    const RepState* rs = D.rs;
+    const ColloidParams* cp = D.cp;
+    const int nc = cp->nc;
+    if (nc == 0 || D.flow) return;
+    const uint32_t L0 = (uint32_t)D.L[0], L1 = (uint32_t)D.L[1];
+    for (int64_t tile = tlo; tile < thi; ++tile) {
+        // the tile's box from its cells: a cell c of the grid shifted by
+        // s in [0, 1)^3 holds the points with c + s <= x < c + 1 + s,
+        // inside [c, c + 2) whatever the shift; cell offsets from the
+        // first cell by minimum image, so a tile across the periodic
+        // boundary stays compact
+        const int64_t r0 = tile * D.tile_cells;
+        const int64_t r1 = r0 + D.tile_cells < D.ncell ? r0 + D.tile_cells : D.ncell;
+        const int ncl = (int)(r1 - r0);
+        int ref[3], lo3[3] = {0, 0, 0}, hi3[3] = {0, 0, 0};
+        const uint32_t first = (uint32_t)(D.hbits == KEY_ROW ? r0 : G(D.cell_of)[r0]);
+        ref[0] = (int)(first % L0);
+        ref[1] = (int)((first / L0) % L1);
+        ref[2] = (int)(first / (L0 * L1));
+        if (lane < ncl) {
+            const uint32_t lin = (uint32_t)(D.hbits == KEY_ROW ? r0 + lane : G(D.cell_of)[r0 + lane]);
+            const int cc[3] = {(int)(lin % L0), (int)((lin / L0) % L1), (int)(lin / (L0 * L1))};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                int o = cc[d] - ref[d];
+                if (2 * o >= D.L[d]) o -= D.L[d];
+                else if (2 * o < -D.L[d]) o += D.L[d];
+                lo3[d] = hi3[d] = o;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) wave_min_max_i(lo3[d], hi3[d]);
+        bool near = false;
+        if (lane < nc) {
+            // colloid c can reach a particle of the tile only if its
+            // reach sphere, widened by the largest speed after the
+            // collision (|u| + |v - u| <= 3 vcap) times tau, meets the box
+            // (minimum image per axis, margin far above rounding)
+            const double reach = ((3.0 * D.vcap) * D.tau + cp->reachR[lane]) * (1.0 + 1e-6) + 1e-6;
+            double r2 = 0.0;
+            bool wide = !(reach < 1e200);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const double blo = (double)lo3[d], bhi = (double)hi3[d] + 2.0;
+                if (!(bhi - blo < 0.5 * D.Ld[d])) { wide = true; continue; }
+                const double oc = min_image(colloid_image(rs->X[lane][d], D.Ld[d]) - (double)ref[d], D.Ld[d],
+                                            D.halfL[d]);
+                double dd = 1e300;
+#pragma unroll
+                for (int img = -1; img <= 1; ++img) {
+                    const double ci = oc + (double)img * D.Ld[d];
+                    double e = blo - ci > ci - bhi ? blo - ci : ci - bhi;
+                    e = e > 0.0 ? e : 0.0;
+                    dd = e < dd ? e : dd;
+                }
+                r2 += dd * dd;
+            }
+            near = wide || r2 < reach * reach;
+        }
+        const uint64_t m = __ballot(near);
+        if (lane == 0) D.tilemask[tile] = (uint32_t)m;
+    }
 }
 
-// single fields of a record (the oversized-cell path reads them one by one)
-__device__ __forceinline__ uint32_t rec_idx(const Rec<double>* r) { return r->idx; }
-__device__ __forceinline__ uint32_t rec_idx(const Rec<float>* r) { return r->idx_s & 0x7fffffffu; }
-__device__ __forceinline__ uint8_t rec_st(const Rec<double>* r) { return (uint8_t)r->st; }
-__device__ __forceinline__ uint8_t rec_st(const Rec<float>* r)
+template <class T, int PPT, bool FLOW>
+__global__ __launch_bounds__(256) void k_stream(Work w, int wg_per_chunk)
 {
-    return (uint8_t)(((r->idx_s >> 31) & 1u) | (((r->id_f >> 31) & 1u) << 1));
+    stream_body<T, PPT, FLOW, 256>(w.desc, w.prefix, w.nrep, xcd_range(blockIdx.x, gridDim.x), wg_per_chunk);
 }
-__device__ __forceinline__ uint32_t rec_id(const Rec<double>* r) { return r->id; }
-__device__ __forceinline__ uint32_t rec_id(const Rec<float>* r) { return r->id_f & 0x7fffffffu; }
-template <class T>
-__device__ __forceinline__ double rec_v(const Rec<T>* r, int d) { return (double)r->v[d]; }
 
-// Counting-sort scatter: particle i (read in array order, coalesced) goes to
-// slot start[key] + rank of the staging array as one whole record, so the
-// collision reads each tile of cells as one contiguous run.
-template <class T>
-__global__ __launch_bounds__(256) void k_scatter(Work w)
+// Sort permutation of the coming collision: particle i goes to slot
+// start[key] + rank.  Thread t of a workgroup holds particles t, t +
+// blockDim.x, ... of its span (PPT of them).  The replica's workgroups share
+// its tiles (colloid masks).
+template <int PPT>
+__global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
 {
-    const int item = blockIdx.x;
+    const int b = xcd_range(blockIdx.x, gridDim.x);
+    const int item = b / wg_per_chunk;
+    const int sub = b - item * wg_per_chunk;
     const int rep = find_rep(w.prefix, w.nrep, item);
     const int chunk = item - w.prefix[rep];
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     const int64_t n = D.n;
-    const int cur = (int)(D.rs->coll_step & 1);
-    const gptr<const T> xs[3] = {G(comp<T>(D.x[cur], n, 0)), G(comp<T>(D.x[cur], n, 1)),
-                                 G(comp<T>(D.x[cur], n, 2))};
-    const gptr<const T> vs[3] = {G(comp<T>(D.v[cur], n, 0)), G(comp<T>(D.v[cur], n, 1)),
-                                 G(comp<T>(D.v[cur], n, 2))};
-    const gptr<const uint32_t> ids = G(D.id[cur]);
-    const gptr<const uint8_t> sts = G(D.st[cur]);
-    const gptr<const uint64_t> keyrank = G(D.keyrank);
-    const gptr<const uint32_t> start = G(D.start);
-    const int64_t base = (int64_t)chunk * CHUNK;
-    // the chunk's four particles per thread: every load before the stores
-    constexpr int P = CHUNK / 256;
-    constexpr int RW = (int)(sizeof(Rec<T>) / 16);
-    int64_t ii[P];
-    uint32_t key[P], rank[P];
+    const gptr<const uint64_t> keyrank = G((const uint64_t*)D.keyrank);
+    const gptr<const uint32_t> start = G((const uint32_t*)D.start);
+    const gptr<uint32_t> perm = G(D.perm);
+    const int span = CHUNK / wg_per_chunk;
+    const int64_t base = (int64_t)chunk * CHUNK + (int64_t)sub * span;
+    uint64_t kr[PPT];
+    int64_t slot[PPT];
 #pragma unroll
-    for (int u = 0; u < P; ++u) {
-        ii[u] = base + u * 256 + threadIdx.x;
-        const uint64_t kr = ii[u] < n ? keyrank[ii[u]] : 0ull;
-        key[u] = (uint32_t)(kr >> 32);
-        rank[u] = (uint32_t)kr;
+    for (int u = 0; u < PPT; ++u) {
+        const int64_t i = base + u * (int)blockDim.x + threadIdx.x;
+        kr[u] = i < n ? keyrank[i] : 0ull;
     }
-    int64_t slot[P];
 #pragma unroll
-    for (int u = 0; u < P; ++u) slot[u] = ii[u] < n ? (int64_t)start[key[u]] + rank[u] : n;
-    T x[P][3], v[P][3];
-    uint32_t idv[P];
-    uint8_t stv[P];
+    for (int u = 0; u < PPT; ++u) slot[u] = (int64_t)start[kr[u] >> 32] + (uint32_t)kr[u];
 #pragma unroll
-    for (int u = 0; u < P; ++u) {
-        const int64_t i = ii[u] < n ? ii[u] : 0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) { x[u][d] = xs[d][i]; v[u][d] = vs[d][i]; }
-        idv[u] = ids[i];
-        stv[u] = sts[i];
+    for (int u = 0; u < PPT; ++u) {
+        const int64_t i = base + u * (int)blockDim.x + threadIdx.x;
+        if (i < n && slot[u] < n) perm[slot[u]] = (uint32_t)i;
     }
-    // each record through LDS, then written by RW consecutive lanes (one
-    // 16-byte word each), so a record leaves as one contiguous request
-    __shared__ Rec<T> s_out[256];
-    __shared__ int64_t s_slot[256];
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4* s_out4 = reinterpret_cast<const u32x4*>(s_out);
-    const gptr<u32x4> stage4 = G(reinterpret_cast<u32x4*>(D.stage));
-#pragma unroll
-    for (int u = 0; u < P; ++u) {
-        if (u) __syncthreads();
-        rec_put(&s_out[threadIdx.x], x[u], v[u], idv[u], (uint32_t)ii[u], stv[u]);
-        s_slot[threadIdx.x] = (ii[u] < n && slot[u] < n) ? slot[u] : -1;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < RW; ++q) {
-            const int k4 = q * 256 + (int)threadIdx.x;
-            const int r = k4 / RW, part = k4 - r * RW;
-            const int64_t sl = s_slot[r];
-            if (sl >= 0) stage4[sl * RW + part] = s_out4[k4];
-        }
+    const Share sh{(int64_t)chunk * wg_per_chunk + sub, (int64_t)D.n_chunks * wg_per_chunk};
+    if (threadIdx.x < 64) tile_masks(D, sh.lo(D.n_tiles), sh.hi(D.n_tiles));
+    if (sh.me == 0 && (int)threadIdx.x < D.nc) {
+        RepState* rs = D.rs;
+        for (int d = 0; d < 3; ++d) rs->Xw[threadIdx.x][d] = colloid_image(rs->X[threadIdx.x][d], D.Ld[d]);
     }
 }
 
 // ------------------------------------------------------------- collision
 
-// Add the Verlet-list flags of the wave's particles to their chunks' counts.
-// The particles of one collision group occupy slots [q0, q0 + ns) with
-// ns <= CHUNK, so they span the chunks c_lo = q0 / CHUNK and c_lo + 1 at
-// most: one atomic per chunk and wave.  All 64 lanes must call it.
-__device__ __forceinline__ void count_flag(gptr<uint32_t> chunk_cnt, int64_t o, bool f, int64_t c_lo)
+// Verlet-list membership of the wave's slots: lane l holds slot o0 + l (o0
+// uniform).  The bits go to their words (the wave's slots touch two at most)
+// and their number to their chunks' counts, one atomic each, only where some
+// slot is a member.  All 64 lanes must call it.
+__device__ __forceinline__ void list_flags(const RepDesc& D, int64_t o0, bool f)
 {
-    const int64_t ch = o / CHUNK;
-    const uint32_t n_lo = (uint32_t)__popcll(__ballot(f && ch == c_lo));
-    const uint32_t n_hi = (uint32_t)__popcll(__ballot(f && ch != c_lo));
+    const uint64_t m = __ballot(f);
+    if (m == 0ull) return;
+    const int sh = (int)(o0 & 63);
+    const uint64_t lo = m << sh, hi = sh ? m >> (64 - sh) : 0ull;
     if ((threadIdx.x & 63) == 0) {
-        if (n_lo) g_add(chunk_cnt + c_lo, n_lo);
-        if (n_hi) g_add(chunk_cnt + c_lo + 1, n_hi);
+        const int64_t w0 = o0 >> 6;
+        const gptr<uint64_t> bits = G(D.lbits);
+        const gptr<uint32_t> cnt = G(D.chunk_cnt);
+        if (lo) {
+            (void)__hip_atomic_fetch_or(bits + w0, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            g_add(cnt + w0 / (CHUNK / 64), (uint32_t)__popcll(lo));
+        }
+        if (hi) {
+            (void)__hip_atomic_fetch_or(bits + w0 + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            g_add(cnt + (w0 + 1) / (CHUNK / 64), (uint32_t)__popcll(hi));
+        }
     }
 }
 
@@ -771,10 +588,10 @@ __device__ __forceinline__ bool is_candidate_masked(const RepDesc& D, const Coll
 constexpr int COLL_TCMAX = 64;       // cells per tile at most
 
 // One cell of the tile holding more particles than a collision group (rare:
-// hundreds of particles in one cell).  Its records are contiguous in the
-// staging array; the stable order is found by counting ranks of the old
-// indices into scratch (the key/rank array is dead after the scatter), then
-// the per-cell quantities by one thread in that order, then every particle.
+// hundreds of particles in one cell).  Its particles go to their output slots
+// in the stable order, found by counting ranks of the old indices; then the
+// per-cell quantities by one thread in that order, then every particle in
+// place.
 template <class T, int RULE, int NT>
 __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int nc, const double (*s_Xw)[3],
                                  int64_t coll, int64_t cell, uint32_t q0, int nn,
@@ -783,41 +600,41 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
 {
     RepState* rs = D.rs;
     const int t = threadIdx.x;
-    const int64_t n = D.n;
     const int cur = (int)(coll & 1), nxt = cur ^ 1;
-    T* xn[3] = {comp<T>(D.x[nxt], n, 0), comp<T>(D.x[nxt], n, 1), comp<T>(D.x[nxt], n, 2)};
-    T* vn[3] = {comp<T>(D.v[nxt], n, 0), comp<T>(D.v[nxt], n, 1), comp<T>(D.v[nxt], n, 2)};
-    uint32_t* idn = D.id[nxt];
-    uint8_t* stn = D.st[nxt];
-    const Rec<T>* rec = reinterpret_cast<const Rec<T>*>(D.stage) + q0;
     const double ca = D.ca, sa = D.sa, oma = 1.0 - D.ca;
-    uint32_t* srt = reinterpret_cast<uint32_t*>(D.keyrank) + q0;   // stable rank -> record
+    // the particles into the output slots, in stable order
+    // (the collision then changes them in place)
+    const Rec<T>* src = recs<T>(D, cur);
+    Rec<T>* rec = recs<T>(D, nxt) + q0;
+    const uint32_t* perm = D.perm + q0;
     for (int j = t; j < nn; j += NT) {
-        const uint32_t pj = rec_idx(&rec[j]);
+        const uint32_t pj = perm[j];
         int r = 0;
-        for (int q = 0; q < nn; ++q) r += rec_idx(&rec[q]) < pj ? 1 : 0;
-        srt[r] = (uint32_t)j;
+        for (int q = 0; q < nn; ++q) r += perm[q] < pj ? 1 : 0;
+        Rec<T> a = src[pj];
+        a.st &= ST_PUBLIC;
+        rec[r] = a;
     }
     __syncthreads();
     if (t == 0) {
         double S0 = 0.0, S1 = 0.0, S2 = 0.0;
         for (int k = 0; k < nn; ++k) {
-            const Rec<T>* q = &rec[srt[k] < (uint32_t)nn ? srt[k] : 0u];
-            S0 = S0 + rec_v(q, 0);
-            S1 = S1 + rec_v(q, 1);
-            S2 = S2 + rec_v(q, 2);
+            const Rec<T>* q = &rec[k];
+            S0 = S0 + (double)q->v[0];
+            S1 = S1 + (double)q->v[1];
+            S2 = S2 + (double)q->v[2];
         }
         const double u0 = S0 / (double)nn, u1 = S1 / (double)nn, u2 = S2 / (double)nn;
         double tsum = 0.0, G0 = 0.0, G1 = 0.0, G2 = 0.0;
         int nB = 0;
         for (int k = 0; k < nn; ++k) {
-            const Rec<T>* q = &rec[srt[k] < (uint32_t)nn ? srt[k] : 0u];
-            double w0 = rec_v(q, 0) - u0, w1 = rec_v(q, 1) - u1, w2 = rec_v(q, 2) - u2;
+            const Rec<T>* q = &rec[k];
+            double w0 = (double)q->v[0] - u0, w1 = (double)q->v[1] - u1, w2 = (double)q->v[2] - u2;
             tsum = tsum + dot3(w0, w1, w2, w0, w1, w2);
-            nB += rec_st(q) & 1;
+            nB += (int)(q->st & 1u);
             if constexpr (RULE == 1) {
                 uint64_t wv[4]; double z[3];
-                philox<true>((uint64_t)coll, rec_id(q), 0, D.seed, TAG_THERMO, wv);
+                philox<true>((uint64_t)coll, q->id, 0, D.seed, TAG_THERMO, wv);
                 normals3(wv, z);
                 G0 = G0 + (D.vscale * z[0]);
                 G1 = G1 + (D.vscale * z[1]);
@@ -840,7 +657,7 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
                 int jb = (int)(u01(wv[1]) * (double)nB);
                 if (jb >= nB) jb = nB - 1;
                 for (int k = 0; k < nn; ++k)
-                    if (rec_st(&rec[srt[k] < (uint32_t)nn ? srt[k] : 0u]) & 1) {
+                    if (rec[k].st & 1u) {
                         if (jb == 0) { flipk = k; break; }
                         jb--;
                     }
@@ -854,11 +671,10 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
     for (int k0 = 0; k0 < nn; k0 += NT) {
         const int k = k0 + t;
         bool cnd = false;
-        const int64_t o = (int64_t)q0 + k;
         if (k < nn) {
-            T xt[3], vq[3]; uint32_t idq, pq; uint8_t s;
-            rec_get(&rec[srt[k] < (uint32_t)nn ? srt[k] : 0u], xt, vq, idq, pq, s);
-            const double vv0 = (double)vq[0], vv1 = (double)vq[1], vv2 = (double)vq[2];
+            Rec<T>* q = &rec[k];
+            const double vv0 = (double)q->v[0], vv1 = (double)q->v[1], vv2 = (double)q->v[2];
+            uint32_t s = q->st;
             double v3[3];
             if constexpr (RULE == 0) {
                 const double nax[3] = {s_n[0], s_n[1], s_n[2]};
@@ -867,74 +683,486 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
                 v3[0] = u0 + rw[0]; v3[1] = u1 + rw[1]; v3[2] = u2 + rw[2];
             } else {
                 uint64_t wv[4]; double z[3];
-                philox<true>((uint64_t)coll, idq, 0, D.seed, TAG_THERMO, wv);
+                philox<true>((uint64_t)coll, q->id, 0, D.seed, TAG_THERMO, wv);
                 normals3(wv, z);
                 v3[0] = u0 + ((D.vscale * z[0]) - s_n[0]);
                 v3[1] = u1 + ((D.vscale * z[1]) - s_n[1]);
                 v3[2] = u2 + ((D.vscale * z[2]) - s_n[2]);
             }
+            const double x0 = (double)q->x[0], x1 = (double)q->x[1], x2 = (double)q->x[2];
             if (k == flipk) {
-                du_sum += species_dU(D, cp, nc, s_Xw, (double)xt[0], (double)xt[1], (double)xt[2], 1, 0);
+                du_sum += species_dU(D, cp, nc, s_Xw, x0, x1, x2, 1, 0);
                 n_flip += 1.0;
-                s = 0;
+                s = 0u;
             }
             const T vt[3] = {(T)v3[0], (T)v3[1], (T)v3[2]};
-            for (int d = 0; d < 3; ++d) { xn[d][o] = xt[d]; vn[d][o] = vt[d]; }
-            idn[o] = idq;
-            stn[o] = s;
-            cnd = is_candidate(D, cp, nc, s_Xw, s, (double)xt[0], (double)xt[1], (double)xt[2],
-                               (double)vt[0], (double)vt[1], (double)vt[2]);
-            D.cflag[o] = cnd ? 1 : 0;
+            cnd = is_candidate(D, cp, nc, s_Xw, (uint8_t)s, x0, x1, x2, (double)vt[0], (double)vt[1], (double)vt[2]);
+            for (int d = 0; d < 3; ++d) q->v[d] = vt[d];
+            q->st = s | (cnd ? ST_LIST : 0u);
         }
-        // the wave's slots lie in [q0 + k0, q0 + k0 + NT): at most two chunks
-        count_flag(G(D.chunk_cnt), o, cnd, ((int64_t)q0 + k0) / CHUNK);
+        list_flags(D, (int64_t)q0 + k0 + (t & ~63), cnd);
     }
     __syncthreads();
 }
 
+// The wave's records of slots [0, ns) to dst, by lane and 64 u: through buf (64
+// records of LDS), so that four lanes (FP32: two) write one record and each
+// store instruction a contiguous kilobyte.  The 16-byte words of record r are
+// rotated within it by its number, which spreads both accesses over the
+// banks.  The buffer's old contents may be read until the call.
+template <class T, int PPT>
+__device__ __forceinline__ void records_out(char* buf, gptr<Rec<T>> dst, int ns, const T (&x)[PPT][3],
+                                            const T (&v)[PPT][3], const uint32_t (&id)[PPT], const uint32_t (&st)[PPT])
+{
+    constexpr int W = RecWords<T>::W;
+    const int lane = threadIdx.x & 63;
+    u32x4* b = reinterpret_cast<u32x4*>(buf);
+    const gptr<u32x4> out = (gptr<u32x4>)dst;
+#pragma unroll
+    for (int u = 0; u < PPT; ++u) {
+        if (u * 64 >= ns) break;
+        RecWords<T> r;
+        r.pack(x[u], v[u], id[u], st[u]);
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < W; ++k) b[lds_word<W>(lane, k)] = r.w[k];
+        wave_sync();
+        const int nw = (ns - u * 64 < 64 ? ns - u * 64 : 64) * W;
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int p = k * 64 + lane;
+            const u32x4 q = b[lds_word<W>(p / W, p % W)];
+            if (p < nw) out[(int64_t)u * 64 * W + p] = q;
+        }
+    }
+}
+
+// tile-local cell of slot q (a map of the tile's leading slots; binary search
+// over the cell starts of the group [ga, gb) past its end)
+__device__ __forceinline__ int cell_of_slot(const uint32_t* s_start, const uint8_t* s_cellof, int cap, uint32_t q,
+                                            int ga, int gb)
+{
+    if (q - s_start[0] < (uint32_t)cap) return s_cellof[q - s_start[0]];
+    int lo = ga, hi = gb - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_start[mid] <= q) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
 // MPCD collision on one tile of cells of the shifted grid (sort ranks
-// [c0, c0 + TC)).  The scatter has put the tile's particles in the
-// contiguous slots [start[c0], start[c0 + TC)) of the staging array, cell
-// by cell (in scatter order within a cell).  The tile's cells are taken in
-// groups whose particles fit the workgroup (NT threads holding PPT particles
-// each); usually the whole tile is one group.  Per group:
-//   B  each thread reads whole records of the group's slots (coalesced) and
-//      looks up each slot's cell (a slot-to-cell map of the tile built at
-//      tile start; binary search over the cell starts past its end);
-//   C  it ranks its particle by old index among its cell's records (the
-//      stable order), writes position and id to the output slot of that
-//      rank, velocity and species to LDS at that slot for the per-cell sums;
-//   D  one thread per cell: sequential FP64 sums in the stable order,
-//      centre-of-mass velocity, temperature term, bulk reaction decision;
-//      one lane per colloid: is the colloid within reach of any particle of
-//      the tile (the box of the tile's cells, the particles' largest speed)?
-//   E  each thread rotates its particles about their cell's axis, applies
-//      the reaction, and writes velocity, species and Verlet-list flag.
-// The random axes and bulk-reaction uniforms of all cells of the tile, the
-// slot-to-cell map and the tile's box are made at tile start (they depend on
-// nothing loaded), next to the loads.
-// The register file is held to 96 VGPRs (five waves per SIMD) with one
-// particle per thread, or two in FP32, and to 128 (four waves) with two in
-// FP64; a few bytes of values spill.
+// [c0, c0 + TC)).  The sort permutation lists the tile's particles in the
+// contiguous slots [start[c0], start[c0 + TC)), cell by cell (in any order
+// within a cell).  The tile's cells are cut, in order, into runs of whole cells
+// of at most CAP = 64 PPT particles; wave w of the workgroup takes runs w, w +
+// NT / 64, ...  A wave works on its own: no workgroup barrier, so the waves of
+// a compute unit wait for memory at different times.  Per run, lane l holding
+// the slots l and l + 64:
+//   B  gather the records of the slots' particles (the index loads went out a
+//      run earlier);
+//   C  rank each particle by old index among its cell's slots (the stable
+//      order) and put it to LDS at its rank's slot;
+//   D  one lane per cell and component: sequential FP64 sums in the stable
+//      order, centre-of-mass velocity; the particles' |v - u|^2; one lane per
+//      cell: temperature term, bulk reaction decision;
+//   E  rotate about the cell's axis, apply the reaction, decide the
+//      Verlet-list membership, write the records (through LDS, four lanes a
+//      record, so that they leave as whole lines).
+// A cell beyond CAP is left to k_collide_big.
+// Bound by memory: the records once in and once out, 2.8 GB in FP64 for 20.97 M
+// particles, 530 us at the rate of a copy, measured 664 (FP32 426).  Scattering
+// the records into cell order first and reading them back cost 557 + 714.
+constexpr int RUN_CELLS = 24;        // cells per run at most
+
+template <class T, int PPT, int RULE>
+struct alignas(16) CollideWave {
+    static constexpr int CAP = 64 * PPT;
+    T x[3][CAP], v[3][CAP];                  // by slot
+    union {
+        double sq[CAP];                      // |v - u|^2 (then thermostat draws) by slot
+        uint32_t old[CAP];                   // old index by arrival
+    };
+    uint32_t id[CAP];
+    uint8_t st[CAP];
+    double u[RUN_CELLS][3];                  // centre-of-mass velocity
+    double n[RUN_CELLS][3];                  // rotation axis; under the thermostat the mean draw
+    double du[2];                            // reaction energy and flips
+    int16_t flip[RUN_CELLS];
+    uint8_t go[RUN_CELLS];
+};
+
+template <class T, int RULE, int NT, int PPT, bool FLOW>
+__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 5 : 4) void k_collide(Work w, int xcd_map)
+{
+    constexpr int CAP = 64 * PPT, NW = NT / 64;
+    const int item = xcd_map ? xcd_range(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int rep = w.nrep == 1 ? 0 : find_rep(w.prefix, w.nrep, item);
+    const int tile = w.nrep == 1 ? item : item - w.prefix[rep];
+    const RepDesc& D = w.desc[rep];
+    if (!D.active || D.rule != RULE || D.dense || (D.flow != 0) != FLOW) return;
+    __shared__ CollideWave<T, PPT, RULE> s_w[NW];
+    using Ctx = CollideWave<T, PPT, RULE>;
+    static_assert(sizeof(Ctx) - 128 >= 64 * sizeof(Rec<T>), "room for 64 records before du");
+    __shared__ uint32_t s_start[COLL_TCMAX + 1];
+    RepState* rs = D.rs;
+    const ColloidParams* cp = D.cp;
+    const int nc = D.nc;
+    const int t = threadIdx.x, lane0 = t & 63;
+    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(t >> 6);
+    CollideWave<T, PPT, RULE>& S = s_w[wave];
+    const int TC = D.tile_cells;
+    const int64_t c0 = (int64_t)tile * TC;
+    const int ncl = (int)((c0 + TC < D.ncell ? c0 + TC : D.ncell) - c0);
+    // lane l: first slot of cell l of the tile, and of the cell after it
+    const uint32_t sl0 = G(D.start)[c0 + (lane0 < ncl ? lane0 : ncl)];
+    const uint32_t tend = G(D.start)[c0 + ncl];
+    const bool cull = RULE == 0 && nc > 0 && !FLOW;
+    const uint32_t all_mask = nc >= 32 ? 0xffffffffu : ((1u << nc) - 1u);
+    const uint32_t tmask = cull ? G(D.tilemask)[tile] : all_mask;
+    const int64_t coll = rs->coll_step;
+    const double (*Xw)[3] = rs->Xw;
+    const int cur = (int)(coll & 1), nxt = cur ^ 1;
+    uint32_t sl1 = __shfl_down(sl0, 1, 64);
+    if (lane0 >= ncl - 1) sl1 = tend;
+    if (t < ncl) G(D.count)[c0 + t] = 0u;      // for the next binning
+    // cell starts: every wave writes the same values, and so may read them
+    // after its own write
+    if (lane0 < ncl) s_start[lane0] = sl0;
+    if (lane0 == 0) {
+        s_start[ncl] = tend;
+        S.du[0] = S.du[1] = 0.0;
+    }
+
+    const gptr<const Rec<T>> src = G((const Rec<T>*)recs<T>(D, cur));
+    const gptr<Rec<T>> dst = G(recs<T>(D, nxt));
+    const gptr<const uint32_t> perm = G((const uint32_t*)D.perm);
+    const gptr<const double> axes = G((const double*)D.axes);
+    const double ca = D.ca, sa = D.sa, oma = 1.0 - D.ca;
+
+    double t_sum = 0.0;        // temperature terms of this lane's cells
+    int t_cells = 0;           // (uniform)
+    uint64_t big = 0;          // cells left to k_collide_big (uniform)
+    int ga = 0, nrun = 0;
+    // this wave's next run: cells [a, a + nrc) of the tile, slots [q0, q0 + ns)
+    int a = 0, nrc = 0, ns = 0;
+    uint32_t q0 = 0;
+    auto next_run = [&]() {
+        while (ga < ncl) {
+            // the longest run of cells from ga whose particles fit
+            q0 = (uint32_t)__builtin_amdgcn_readlane((int)sl0, ga);
+            const uint64_t fit =
+                __ballot(lane0 >= ga && lane0 < ncl && lane0 < ga + RUN_CELLS && sl1 - q0 <= (uint32_t)CAP);
+            if (fit == 0ull) {
+                big |= 1ull << ga;     // one cell beyond the capacity
+                ++ga;
+                continue;
+            }
+            a = ga;
+            nrc = __popcll(fit);
+            ga += nrc;
+            ns = (int)((uint32_t)__builtin_amdgcn_readlane((int)sl1, ga - 1) - q0);
+            if ((nrun++ & (NW - 1)) == wave && ns > 0) return;
+        }
+        ns = 0;
+    };
+    uint32_t pj[PPT];          // array positions of the run's particles, loaded a run ahead
+    auto load_perm = [&]() {
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            const int j = lane0 + u * 64;
+            pj[u] = j < ns ? perm[q0 + j] : 0u;
+        }
+    };
+    next_run();
+    load_perm();
+    while (ns > 0) {
+        wave_sync();                                             // the last run's reads are done
+        // an opaque copy per run: per-lane addresses are formed where they are
+        // used; hoisted out of the loop they spilled, and their reloads waited
+        // behind the stores in flight
+        int lane = lane0;
+        asm volatile("" : "+v"(lane));
+        // ---- B
+        T xq[PPT][3], vq[PPT][3];
+        uint32_t idq[PPT], stq[PPT], pc[PPT];
+        int lc[PPT];                                             // cell of the slot, from a
+        const int a0 = a, nr = nrc, n1 = ns;
+        const uint32_t q1 = q0;
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) rec_load<T>(src + (int64_t)pj[u], xq[u], vq[u], idq[u], stq[u]);
+        double ax[2] = {0.0, 0.0};
+        if constexpr (RULE == 0)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (lane + 64 * q < 3 * nr) ax[q] = axes[3 * (c0 + a0) + lane + 64 * q];
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            pc[u] = pj[u];
+            if (lane + u * 64 < n1) S.old[lane + u * 64] = pc[u];
+        }
+        // the run after this one
+        next_run();
+        load_perm();
+        // cell of each slot: the run's cell boundaries at or below it (the
+        // same by arrival and by slot: a cell's slots are one range)
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) lc[u] = 0;
+        for (int k = 1; k < nr; ++k) {
+            const int bound = (int)((uint32_t)__builtin_amdgcn_readlane((int)sl0, a0 + k) - q1);
+#pragma unroll
+            for (int u = 0; u < PPT; ++u) lc[u] += lane + u * 64 >= bound ? 1 : 0;
+        }
+        wave_sync();
+        // ---- C
+        float gv2 = 0.0f;
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            const int j = lane + u * 64;
+            if (j < n1) {
+                const int cb = (int)(s_start[a0 + lc[u]] - q1), ce = (int)(s_start[a0 + lc[u] + 1] - q1);
+                const uint32_t p = pc[u];
+                const T (&xr)[3] = xq[u];
+                const T (&vr)[3] = vq[u];
+                int r = 0, q = cb;
+                for (; q + 4 <= ce; q += 4)
+                    r += (S.old[q] < p ? 1 : 0) + (S.old[q + 1] < p ? 1 : 0) + (S.old[q + 2] < p ? 1 : 0) +
+                         (S.old[q + 3] < p ? 1 : 0);
+                for (; q < ce; ++q) r += S.old[q] < p ? 1 : 0;
+                const int sl = cb + r;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) { S.x[d][sl] = xr[d]; S.v[d][sl] = vr[d]; }
+                S.id[sl] = idq[u];
+                S.st[sl] = (uint8_t)(stq[u] & ST_PUBLIC);
+                if (cull) {
+                    // largest |v|^2 rounded up in FP32, for the tile mask (inf
+                    // or NaN: no cull)
+                    const double vv = dot3((double)vr[0], (double)vr[1], (double)vr[2], (double)vr[0], (double)vr[1],
+                                           (double)vr[2]);
+                    const float f = vv <= 1e30 ? (float)vv * 1.000001f : 3e38f;
+                    gv2 = f > gv2 ? f : gv2;
+                }
+            }
+        }
+        if constexpr (RULE == 0)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (lane + 64 * q < 3 * nr) (&S.n[0][0])[lane + 64 * q] = ax[q];
+        uint32_t cmask = tmask;
+        if (cull && cmask != all_mask && __ballot((double)gv2 > D.vcap * D.vcap) != 0ull) cmask = all_mask;
+        wave_sync();
+        // every particle by slot now (read back from LDS where it is needed)
+        uint64_t mB[PPT];
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) mB[u] = __ballot(lane + u * 64 < n1 && (S.st[lane + u * 64] & 1) != 0);
+        // ---- D: sums by cell and component
+        for (int q = lane; q < 3 * nr; q += 64) {
+            const int k = q / 3, d = q - 3 * k;
+            const int cb = (int)(s_start[a0 + k] - q1), ce = (int)(s_start[a0 + k + 1] - q1);
+            const int nn = ce - cb;
+            // Lamura et al. (2001): a cell of the first or last layer (cut by
+            // a plate) with fewer than n0 particles holds n0 - n virtual ones
+            // at rest on average; only their summed momentum enters, a normal
+            // vector of variance (n0 - n) kT / m per component
+            bool virt = false;
+            uint64_t cell = 0;
+            if (FLOW && D.walls && nn >= 1 && nn < D.wall_n0) {
+                cell = (uint64_t)(D.hbits == KEY_ROW ? c0 + a0 + k : G(D.cell_of)[c0 + a0 + k]);
+                const int64_t cz = (int64_t)cell / ((int64_t)D.L[0] * D.L[1]);
+                virt = cz == 0 || cz == D.L[2] - 1;
+            }
+            double s = 0.0;
+            for (int i = cb; i < ce; ++i) s = s + (double)S.v[d][i];
+            double um;
+            if (FLOW && virt) {
+                uint64_t wv[4]; double z[3];
+                philox<true>((uint64_t)coll, cell, 0, D.seed, TAG_VIRT, wv);
+                normals3(wv, z);
+                const double sd = sqrt((double)(D.wall_n0 - nn)) * D.vscale;
+                um = (s + (sd * (d == 0 ? z[0] : d == 1 ? z[1] : z[2]))) / (double)D.wall_n0;
+            } else {
+                um = s / (double)nn;
+            }
+            const bool go = nn >= 2 || virt;
+            // a non-finite centre-of-mass velocity would spread through its
+            // cell: latched for the caller
+            if (go && !isfinite(um)) atomicOr(&rs->flags, RMP_FLAG_NONFINITE);
+            S.u[k][d] = um;
+            if (d == 0) {
+                S.go[k] = (uint8_t)((go ? 1 : 0) | (virt ? 2 : 0));
+                S.flip[k] = -1;
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            const int sl = lane + u * 64;
+            const double w0 = (double)S.v[0][sl] - S.u[lc[u]][0], w1 = (double)S.v[1][sl] - S.u[lc[u]][1],
+                         w2 = (double)S.v[2][sl] - S.u[lc[u]][2];
+            S.sq[sl] = dot3(w0, w1, w2, w0, w1, w2);
+        }
+        wave_sync();
+        {
+            bool tc = false, flips = false;
+            if (lane < nr) {
+                const int cb = (int)(s_start[a0 + lane] - q1), ce = (int)(s_start[a0 + lane + 1] - q1);
+                if (S.go[lane] == 1) {
+                    double tsum = 0.0;
+                    for (int i = cb; i < ce; ++i) tsum = tsum + S.sq[i];
+                    t_sum += (D.mass * tsum) / (double)(ce - cb - 1);
+                    tc = true;
+                }
+                if (D.bulk_on) {
+                    // the cell's B particles: bits [cb, ce) of the species masks
+                    int nB = 0;
+                    uint64_t mine[PPT];
+#pragma unroll
+                    for (int u = 0; u < PPT; ++u) {
+                        const int l0 = cb - 64 * u > 0 ? cb - 64 * u : 0, l1 = ce - 64 * u < 64 ? ce - 64 * u : 64;
+                        const uint64_t ones = l1 - l0 >= 64 ? ~0ull : ((1ull << ((l1 - l0) & 63)) - 1ull);
+                        mine[u] = l1 > l0 ? mB[u] & (ones << (l0 & 63)) : 0ull;
+                        nB += __popcll(mine[u]);
+                    }
+                    if (nB > 0) {
+                        const double P = G(D.ptable)[nB < RMP_PTABLE ? nB : RMP_PTABLE - 1];
+                        const gptr<const double> bulk = G((const double*)D.bulk) + 2 * (c0 + a0 + lane);
+                        if (bulk[0] < P) {
+                            int jb = (int)(bulk[1] * (double)nB);
+                            if (jb >= nB) jb = nB - 1;
+                            flips = true;
+#pragma unroll
+                            for (int u = 0; u < PPT; ++u)
+                                for (uint64_t m = mine[u]; m; m &= m - 1ull)
+                                    if (jb-- == 0) S.flip[lane] = (int16_t)(64 * u + __ffsll((long long)m) - 1);
+                        }
+                    }
+                }
+            }
+            t_cells += __popcll(__ballot(tc));
+            if (__ballot(flips) != 0ull) {
+                // potential change of the flipped particles (one per cell at most)
+                wave_sync();
+                double du = 0.0, nf = 0.0;
+                if (flips) {
+                    const int sl = S.flip[lane];
+                    du = species_dU(D, cp, nc, Xw, (double)S.x[0][sl], (double)S.x[1][sl], (double)S.x[2][sl], 1, 0);
+                    nf = 1.0;
+                }
+                du = wave_tree_sum(du);
+                nf = wave_tree_sum(nf);
+                if (lane == 0) {
+                    S.du[0] += du;
+                    S.du[1] += nf;
+                }
+            }
+        }
+        // the velocity after the collision is u + (draw - mean draw) under the
+        // thermostat: the draws by slot, their cell means by cell, component
+        // by component
+        double gd[RULE ? PPT : 1][3];
+        if constexpr (RULE == 1) {
+#pragma unroll
+            for (int u = 0; u < PPT; ++u) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) gd[u][d] = 0.0;
+                if (lane + u * 64 < n1) {
+                    uint64_t wv[4]; double z[3];
+                    philox<true>((uint64_t)coll, S.id[lane + u * 64], 0, D.seed, TAG_THERMO, wv);
+                    normals3(wv, z);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) gd[u][d] = D.vscale * z[d];
+                }
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                wave_sync();
+#pragma unroll
+                for (int u = 0; u < PPT; ++u) S.sq[lane + u * 64] = gd[u][d];
+                wave_sync();
+                if (lane < nr) {
+                    const int cb = (int)(s_start[a0 + lane] - q1), ce = (int)(s_start[a0 + lane + 1] - q1);
+                    double g = 0.0;
+                    for (int i = cb; i < ce; ++i) g = g + S.sq[i];
+                    S.n[lane][d] = g / (double)(ce - cb);
+                }
+            }
+        }
+        wave_sync();
+        // ---- E
+        T xr[PPT][3], vr[PPT][3];
+        uint32_t idr[PPT], so[PPT];
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            const int sl = lane + u * 64, k = lc[u];
+            bool cnd = false;
+            so[u] = idr[u] = 0u;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) xr[u][d] = vr[u][d] = (T)0;
+            if (sl < n1) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) { xr[u][d] = S.x[d][sl]; vr[u][d] = S.v[d][sl]; }
+                idr[u] = S.id[sl];
+                so[u] = S.st[sl];
+                if ((S.go[k] & 1) != 0) {
+                    const double u0 = S.u[k][0], u1 = S.u[k][1], u2 = S.u[k][2];
+                    double v3[3];
+                    if constexpr (RULE == 0) {
+                        const double nax[3] = {S.n[k][0], S.n[k][1], S.n[k][2]};
+                        double rw[3];
+                        rotate(nax, ca, sa, oma, (double)vr[u][0] - u0, (double)vr[u][1] - u1, (double)vr[u][2] - u2, rw);
+                        v3[0] = u0 + rw[0]; v3[1] = u1 + rw[1]; v3[2] = u2 + rw[2];
+                    } else {
+                        v3[0] = u0 + (gd[u][0] - S.n[k][0]);
+                        v3[1] = u1 + (gd[u][1] - S.n[k][1]);
+                        v3[2] = u2 + (gd[u][2] - S.n[k][2]);
+                    }
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) vr[u][d] = (T)v3[d];
+                }
+                if (S.flip[k] == sl) so[u] = 0u;
+                cnd = !FLOW && is_candidate_masked(D, cp, cmask, Xw, (uint8_t)so[u], (double)xr[u][0], (double)xr[u][1],
+                                          (double)xr[u][2], (double)vr[u][0], (double)vr[u][1], (double)vr[u][2]);
+                so[u] |= cnd ? ST_LIST : 0u;
+            }
+            list_flags(D, (int64_t)q1 + u * 64, cnd);
+        }
+        records_out<T, PPT>(reinterpret_cast<char*>(&S), dst + (int64_t)q1, n1, xr, vr, idr, so);
+    }
+    const int lane = lane0;
+    // the wave's sums, then the waves in order
+    const double red = wave_tree_sum(t_sum);
+    if (t == 0) G(D.bigmask)[tile] = big;
+    if constexpr (NW == 1) {
+        if (lane < 4)
+            G(D.tpart)[(int64_t)tile * 4 + lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
+    } else {
+        __shared__ double s_red[NW][4];
+        if (lane < 4) s_red[wave][lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
+        __syncthreads();
+        if (t < 4) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) s = s + s_red[q][t];
+            G(D.tpart)[(int64_t)tile * 4 + t] = s;
+        }
+    }
+}
+
+// The same collision for dense systems (more than DENSE_RHO particles per
+// cell), where a wave's 128 slots would hold too few whole cells.  The tile's
+// cells are taken in groups whose particles fit the workgroup (NT threads
+// holding PPT particles each); usually the whole tile is one group.  Phases as
+// above, with workgroup barriers between them.
 template <class T, int RULE, int NT, int PPT>
-__global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_collide(Work w, int xcd_map)
+__global__ __launch_bounds__(NT, RULE ? 3 : 4) void k_collide_dense(Work w, int xcd_map)
 {
     constexpr int CAP = NT * PPT;
     constexpr int FILLCAP = 2 * CAP;    // leading slots of the tile with their cell in s_cellof
-    static_assert(CAP <= CHUNK, "a collision group spans at most two chunks");
-    static_assert(NT >= 256, "the tile-start draws use the last two waves");
-    int item = blockIdx.x;
-    if (xcd_map && (gridDim.x & 7) == 0) {
-        // workgroups are dealt to the eight XCDs in turn: give each XCD a
-        // contiguous range of tiles so that neighbouring tiles, which gather
-        // from the same source lines, share an L2
-        const int per = (int)(gridDim.x >> 3);
-        item = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    }
+    const int item = xcd_map ? xcd_range(blockIdx.x, gridDim.x) : (int)blockIdx.x;
     const int rep = find_rep(w.prefix, w.nrep, item);
     const int tile = item - w.prefix[rep];
     const RepDesc& D = w.desc[rep];
-    if (!D.active || D.rule != RULE) return;
+    if (!D.active || D.rule != RULE || !D.dense) return;
     RepState* rs = D.rs;
     const ColloidParams* cp = D.cp;
     const int nc = cp->nc;
@@ -944,7 +1172,9 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
     __shared__ uint32_t s_start[COLL_TCMAX + 1];
     __shared__ uint8_t s_cellof[FILLCAP];
     __shared__ uint32_t s_perm[CAP];
+    __shared__ T s_x[3][CAP];
     __shared__ T s_v[3][CAP];
+    __shared__ uint32_t s_id[CAP];
     __shared__ double s_g[3][RULE ? CAP : 1];
     __shared__ uint8_t s_st[CAP];
     __shared__ double s_u[COLL_TCMAX][3], s_n[COLL_TCMAX][3];
@@ -953,15 +1183,11 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
     __shared__ int32_t s_flip[COLL_TCMAX];
     __shared__ uint8_t s_go[COLL_TCMAX];
     __shared__ double s_Xw[MAXC][3];
-    __shared__ double s_box[6];        // the tile's box: lower, upper offsets from s_ref
-    __shared__ double s_ref[3];        // lower corner of the tile's first cell (unshifted)
     __shared__ uint64_t s_vmax2;       // max |v|^2 (bit patterns order like the values)
-    __shared__ uint32_t s_cmask;
     __shared__ double sred[(NT / 64 + 1) * 4];
 
     const int64_t coll = rs->coll_step;
-    const int nxt = (int)(coll & 1) ^ 1;
-    const int64_t n = D.n;
+    const int cur = (int)(coll & 1), nxt = cur ^ 1;
     const int TC = D.tile_cells;
     const int64_t c0 = (int64_t)tile * TC;
     const int64_t c1 = (c0 + TC < D.ncell) ? c0 + TC : D.ncell;
@@ -970,85 +1196,32 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
     // the rotation gives one (below), the thermostat's fresh draws do not
     const bool cull = RULE == 0 && nc > 0 && !D.flow;
 
-    // ---- A: cell starts (and the counters zeroed for the next binning);
-    //         per-cell random draws; colloid images
+    // ---- A: cell starts (and the counters zeroed for the next binning); the
+    //         cells' draws; colloid images
     for (int k = t; k <= ncl; k += NT) {
         s_start[k] = G(D.start)[c0 + k];
         if (k < ncl) G(D.count)[c0 + k] = 0;
     }
-    if (t >= NT - 128 && t < NT - 64) {
-        if constexpr (RULE == 0) {
-            for (int lc = t - (NT - 128); lc < ncl; lc += 64) {
-                const int64_t cell = D.hbits == KEY_ROW ? c0 + lc : G(D.cell_of)[c0 + lc];
-                double nax[3];
-                marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, nax);
-                s_n[lc][0] = nax[0]; s_n[lc][1] = nax[1]; s_n[lc][2] = nax[2];
+    if constexpr (RULE == 0)
+        for (int q = t; q < 3 * ncl; q += NT) s_n[q / 3][q % 3] = G(D.axes)[3 * c0 + q];
+    if (D.bulk_on)
+        for (int q = t; q < 2 * ncl; q += NT) s_b[q / 2][q % 2] = G(D.bulk)[2 * c0 + q];
+    if (D.walls) {
+        // plates (flows have no colloids): the virtual-momentum normal of
+        // every cell of the first and last layer, used if the cell turns
+        // out to be cut and under-filled
+        for (int lc = t; lc < ncl; lc += NT) {
+            const int64_t cell = D.hbits == KEY_ROW ? c0 + lc : G(D.cell_of)[c0 + lc];
+            const int64_t cz = cell / ((int64_t)D.L[0] * D.L[1]);
+            if (cz == 0 || cz == D.L[2] - 1) {
+                uint64_t wv[4]; double z[3];
+                philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
+                normals3(wv, z);
+                s_z[lc][0] = z[0]; s_z[lc][1] = z[1]; s_z[lc][2] = z[2];
             }
         }
-    } else if (t >= NT - 64) {
-        if (D.bulk_on)
-            for (int lc = t - (NT - 64); lc < ncl; lc += 64) {
-                const int64_t cell = D.hbits == KEY_ROW ? c0 + lc : G(D.cell_of)[c0 + lc];
-                uint64_t wv[4];
-                philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_BULK, wv);
-                s_b[lc][0] = u01(wv[0]);
-                s_b[lc][1] = u01(wv[1]);
-            }
-    } else if (t >= 64 && t < 128) {
-        if (D.walls) {
-            // plates (flows have no colloids): the virtual-momentum normal of
-            // every cell of the first and last layer, used if the cell turns
-            // out to be cut and under-filled
-            for (int lc = t - 64; lc < ncl; lc += 64) {
-                const int64_t cell = D.hbits == KEY_ROW ? c0 + lc : G(D.cell_of)[c0 + lc];
-                const int64_t cz = cell / ((int64_t)D.L[0] * D.L[1]);
-                if (cz == 0 || cz == D.L[2] - 1) {
-                    uint64_t wv[4]; double z[3];
-                    philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
-                    normals3(wv, z);
-                    s_z[lc][0] = z[0]; s_z[lc][1] = z[1]; s_z[lc][2] = z[2];
-                }
-            }
-        } else if (t < 64 + nc) {
-            for (int d = 0; d < 3; ++d) s_Xw[t - 64][d] = colloid_image(G(rs)->X[t - 64][d], D.Ld[d]);
-        }
-    }
-    if (cull && t < 64) {
-        // the tile's box for the colloid cull, from its cells: a cell
-        // (c0, c1, c2) of the grid shifted by s in [0, 1)^3 holds the points
-        // with c + s <= x < c + 1 + s, inside [c, c + 2) whatever the shift;
-        // cell offsets from the first cell by minimum image, so a tile
-        // across the periodic boundary stays compact
-        const uint32_t L0 = (uint32_t)D.L[0], L1 = (uint32_t)D.L[1];
-        int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-        int ref[3];
-        {
-            const uint32_t lin = (uint32_t)(D.hbits == KEY_ROW ? c0 : G(D.cell_of)[c0]);
-            ref[0] = (int)(lin % L0);
-            ref[1] = (int)((lin / L0) % L1);
-            ref[2] = (int)(lin / (L0 * L1));
-        }
-        if (lane < ncl) {
-            const uint32_t lin = (uint32_t)(D.hbits == KEY_ROW ? c0 + lane : G(D.cell_of)[c0 + lane]);
-            const int cc[3] = {(int)(lin % L0), (int)((lin / L0) % L1), (int)(lin / (L0 * L1))};
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                int o = cc[d] - ref[d];
-                if (2 * o >= D.L[d]) o -= D.L[d];
-                else if (2 * o < -D.L[d]) o += D.L[d];
-                lo[d] = hi[d] = o;
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < 3; ++d) wave_min_max_i(lo[d], hi[d]);
-        if (lane == 0) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                s_ref[d] = (double)ref[d];
-                s_box[d] = (double)lo[d];
-                s_box[3 + d] = (double)hi[d] + 2.0;
-            }
-        }
+    } else if (t < nc) {
+        for (int d = 0; d < 3; ++d) s_Xw[t][d] = colloid_image(G(rs)->X[t][d], D.Ld[d]);
     }
     if (t < 64 && lane < ncl) {
         // tile-local cell of each of the tile's first FILLCAP slots (the
@@ -1057,15 +1230,12 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
         const uint32_t e = b - base < (uint32_t)FILLCAP ? b - base : (uint32_t)FILLCAP;
         for (uint32_t r = a - base; r < e; ++r) s_cellof[r] = (uint8_t)lane;
     }
-    if (t == 64) { s_vmax2 = 0ull; s_cmask = 0u; }
+    if (t == 64) s_vmax2 = 0ull;
     __syncthreads();
 
-    const gptr<const Rec<T>> stage = G(reinterpret_cast<const Rec<T>*>(D.stage));
-    const gptr<T> xn[3] = {G(comp<T>(D.x[nxt], n, 0)), G(comp<T>(D.x[nxt], n, 1)), G(comp<T>(D.x[nxt], n, 2))};
-    const gptr<T> vn[3] = {G(comp<T>(D.v[nxt], n, 0)), G(comp<T>(D.v[nxt], n, 1)), G(comp<T>(D.v[nxt], n, 2))};
-    const gptr<uint32_t> idn = G(D.id[nxt]);
-    const gptr<uint8_t> stn = G(D.st[nxt]);
-    const gptr<uint8_t> cflag = G(D.cflag);
+    const gptr<const Rec<T>> src = G((const Rec<T>*)recs<T>(D, cur));
+    const gptr<Rec<T>> dst = G(recs<T>(D, nxt));
+    const gptr<const uint32_t> perm = G((const uint32_t*)D.perm);
     const double ca = D.ca, sa = D.sa, oma = 1.0 - D.ca;
 
     double t_sum = 0.0, t_cells = 0.0, du_sum = 0.0, n_flip = 0.0;
@@ -1090,43 +1260,29 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
             ga = gb;
             continue;
         }
-        // ---- B: records of the group's slots, cell of each slot
-        T xr[PPT][3], vq[PPT][3];
-        uint32_t idq[PPT], pj[PPT];
-        uint8_t sr[PPT];
-        int lcj[PPT];
+        // ---- B: records of the group's slots
+        T xr[PPT][3], vr[PPT][3];
+        uint32_t idr[PPT], pj[PPT], sr[PPT];
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             const int j = t + u * NT;
-            lcj[u] = ga;
-            pj[u] = 0u;
-            sr[u] = 0;
-            if (j < ns) {
-                rec_get(&stage[q0 + j], xr[u], vq[u], idq[u], pj[u], sr[u]);
-                s_perm[j] = pj[u];
-                const uint32_t q = q0 + (uint32_t)j;
-                if (q - s_start[0] < (uint32_t)FILLCAP) {
-                    lcj[u] = s_cellof[q - s_start[0]];
-                } else {
-                    int lo = ga, hi = gb - 1;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (s_start[mid] <= q) lo = mid; else hi = mid - 1;
-                    }
-                    lcj[u] = lo;
-                }
-            }
+            pj[u] = j < ns ? perm[q0 + j] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) {
+            const int j = t + u * NT;
+            rec_load<T>(src + (int64_t)pj[u], xr[u], vr[u], idr[u], sr[u]);
+            if (j < ns) s_perm[j] = pj[u];
         }
         __syncthreads();
-        // ---- C: stable rank; position and id written at the rank's slot
-        int slot[PPT];
+        // ---- C: stable rank; the particle to LDS at the rank's slot
         double gv2 = 0.0;
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             const int j = t + u * NT;
-            slot[u] = -1;
             if (j < ns) {
-                const int cb = (int)(s_start[lcj[u]] - q0), ce = (int)(s_start[lcj[u] + 1] - q0);
+                const int lc = cell_of_slot(s_start, s_cellof, FILLCAP, q0 + (uint32_t)j, ga, gb);
+                const int cb = (int)(s_start[lc] - q0), ce = (int)(s_start[lc + 1] - q0);
                 const uint32_t p = pj[u];
                 int r = 0, q = cb;
                 for (; q + 4 <= ce; q += 4)
@@ -1134,17 +1290,13 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
                          (s_perm[q + 3] < p ? 1 : 0);
                 for (; q < ce; ++q) r += s_perm[q] < p ? 1 : 0;
                 const int sl = cb + r;
-                slot[u] = sl;
-                const int64_t o = (int64_t)q0 + sl;
-                const T (&xr_)[3] = xr[u];
-                const T (&vq_)[3] = vq[u];
 #pragma unroll
-                for (int d = 0; d < 3; ++d) { xn[d][o] = xr_[d]; s_v[d][sl] = vq_[d]; }
-                idn[o] = idq[u];
-                s_st[sl] = sr[u];
+                for (int d = 0; d < 3; ++d) { s_x[d][sl] = xr[u][d]; s_v[d][sl] = vr[u][d]; }
+                s_id[sl] = idr[u];
+                s_st[sl] = (uint8_t)(sr[u] & ST_PUBLIC);
                 if constexpr (RULE == 1) {
                     uint64_t wv[4]; double z[3];
-                    philox<true>((uint64_t)coll, idq[u], 0, D.seed, TAG_THERMO, wv);
+                    philox<true>((uint64_t)coll, idr[u], 0, D.seed, TAG_THERMO, wv);
                     normals3(wv, z);
                     s_g[0][sl] = D.vscale * z[0];
                     s_g[1][sl] = D.vscale * z[1];
@@ -1154,8 +1306,8 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
                     // the largest speed vmax of the tile's particles, for the
                     // colloid cull: after the rotation a speed is at most
                     // |u| + |v - u| <= 3 vmax
-                    const double vv = dot3((double)vq_[0], (double)vq_[1], (double)vq_[2],
-                                           (double)vq_[0], (double)vq_[1], (double)vq_[2]);
+                    const double vv = dot3((double)vr[u][0], (double)vr[u][1], (double)vr[u][2],
+                                           (double)vr[u][0], (double)vr[u][1], (double)vr[u][2]);
                     gv2 = vv > gv2 ? vv : gv2;
                     if (!(vv <= 1e300)) gv2 = 1e300;          // inf or NaN: no cull
                 }
@@ -1168,7 +1320,7 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
             if (lane == 0) atomicMax((unsigned long long*)&s_vmax2, (unsigned long long)__double_as_longlong(gv2));
         }
         __syncthreads();
-        // ---- D: per cell (one thread each); colloid cull (second wave)
+        // ---- D: per cell (one thread each)
         for (int cl = ga + t; cl < gb; cl += NT) {
             const int cb = (int)(s_start[cl] - q0), ce = (int)(s_start[cl + 1] - q0);
             const int nn = ce - cb;
@@ -1241,57 +1393,21 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
                 }
             }
         }
-        if (cull && t >= 64 && t < 128) {
-            // colloid c can reach a particle of the tile only if its reach
-            // sphere, widened by the largest speed times tau, meets the
-            // tile's box (minimum image per axis, margin far above rounding)
-            bool near = false;
-            // c is made opaque here so that the per-thread addresses below
-            // are formed inside the group loop: hoisted out of it, they were
-            // held across the whole tile and spilled to scratch (FP32 form)
-            int c = t - 64;
-            asm volatile("" : "+v"(c));
-            if (c < nc) {
-                const double vmax2 = __longlong_as_double((long long)s_vmax2);
-                const double reach = ((3.0 * sqrt(vmax2)) * D.tau + cp->reachR[c]) * (1.0 + 1e-6) + 1e-6;
-                double r2 = 0.0;
-                bool wide = !(reach < 1e200);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    // box [lo, hi] of offsets from s_ref; the colloid's offset
-                    // and its periodic images: the nearest one counts
-                    const double lo = s_box[d], hi = s_box[3 + d];
-                    if (!(hi - lo < 0.5 * D.Ld[d])) { wide = true; continue; }
-                    const double oc = min_image(s_Xw[c][d] - s_ref[d], D.Ld[d], D.halfL[d]);
-                    double dd = 1e300;
-#pragma unroll
-                    for (int img = -1; img <= 1; ++img) {
-                        const double ci = oc + (double)img * D.Ld[d];
-                        double e = lo - ci > ci - hi ? lo - ci : ci - hi;
-                        e = e > 0.0 ? e : 0.0;
-                        dd = e < dd ? e : dd;
-                    }
-                    r2 += dd * dd;
-                }
-                near = wide || r2 < reach * reach;
-            }
-            const uint64_t m = __ballot(near);
-            if (lane == 0) s_cmask = (uint32_t)m;
-        }
         __syncthreads();
         // ---- E: rotate (or thermostat), react, write, Verlet-list flag
-        // without the cull every colloid is tested
-        const uint32_t cmask = cull ? s_cmask : (nc >= 32 ? 0xffffffffu : ((1u << nc) - 1u));
-        const int64_t c_lo = (int64_t)q0 / CHUNK;
-        bool fl[PPT];
+        // the tile's mask holds up to the speed vcap; beyond it, and under the
+        // thermostat's fresh draws, every colloid is tested
+        const bool slow = __longlong_as_double((long long)s_vmax2) <= D.vcap * D.vcap;
+        const uint32_t cmask = cull && slow ? G(D.tilemask)[tile] : (nc >= 32 ? 0xffffffffu : ((1u << nc) - 1u));
+        int fl[PPT];               // slot of a flipped particle, or -1
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
+            const int sl = t + u * NT;
             bool cnd = false;
-            fl[u] = false;
-            int64_t o = (int64_t)q0;
-            if (slot[u] >= 0) {
-                const int cl = lcj[u];
-                double v3[3] = {(double)s_v[0][slot[u]], (double)s_v[1][slot[u]], (double)s_v[2][slot[u]]};
+            fl[u] = -1;
+            if (sl < ns) {
+                const int cl = cell_of_slot(s_start, s_cellof, FILLCAP, q0 + (uint32_t)sl, ga, gb);
+                double v3[3] = {(double)s_v[0][sl], (double)s_v[1][sl], (double)s_v[2][sl]};
                 if (s_go[cl]) {
                     const double u0 = s_u[cl][0], u1 = s_u[cl][1], u2 = s_u[cl][2];
                     if constexpr (RULE == 0) {
@@ -1300,45 +1416,33 @@ __global__ __launch_bounds__(NT, (PPT == 1 || sizeof(T) == 4) ? 5 : 4) void k_co
                         rotate(nax, ca, sa, oma, v3[0] - u0, v3[1] - u1, v3[2] - u2, rw);
                         v3[0] = u0 + rw[0]; v3[1] = u1 + rw[1]; v3[2] = u2 + rw[2];
                     } else {
-                        v3[0] = u0 + (s_g[0][slot[u]] - s_n[cl][0]);
-                        v3[1] = u1 + (s_g[1][slot[u]] - s_n[cl][1]);
-                        v3[2] = u2 + (s_g[2][slot[u]] - s_n[cl][2]);
+                        v3[0] = u0 + (s_g[0][sl] - s_n[cl][0]);
+                        v3[1] = u1 + (s_g[1][sl] - s_n[cl][1]);
+                        v3[2] = u2 + (s_g[2][sl] - s_n[cl][2]);
                     }
                 }
-                uint8_t s = sr[u];
-                o = (int64_t)q0 + slot[u];
-                const bool flip = s_flip[cl] == slot[u];
-                // the position (written to the output slot in C by this
-                // thread) is read back only for a colloid within reach of
-                // the tile
-                T xo3[3] = {(T)0, (T)0, (T)0};
-                if (cmask != 0u)
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) xo3[d] = xn[d][o];
-                if (flip) {
-                    fl[u] = true;
+                uint32_t s = s_st[sl];
+                if (s_flip[cl] == sl) {
+                    fl[u] = sl;
                     n_flip += 1.0;
-                    s = 0;
+                    s = 0u;
                 }
-                const T vt[3] = {(T)v3[0], (T)v3[1], (T)v3[2]};
-#pragma unroll
-                for (int d = 0; d < 3; ++d) vn[d][o] = vt[d];
-                stn[o] = s;
-                cnd = is_candidate_masked(D, cp, cmask, s_Xw, s, (double)xo3[0], (double)xo3[1],
-                                          (double)xo3[2], (double)vt[0], (double)vt[1], (double)vt[2]);
-                cflag[o] = cnd ? 1 : 0;
+                const T xo[3] = {s_x[0][sl], s_x[1][sl], s_x[2][sl]};
+                const T vo[3] = {(T)v3[0], (T)v3[1], (T)v3[2]};
+                cnd = is_candidate_masked(D, cp, cmask, s_Xw, (uint8_t)s, (double)xo[0], (double)xo[1], (double)xo[2],
+                                          (double)vo[0], (double)vo[1], (double)vo[2]);
+                rec_store<T, RecWords<T>::W>(dst + ((int64_t)q0 + sl), xo, vo, s_id[sl], s | (cnd ? ST_LIST : 0u));
             }
-            count_flag(G(D.chunk_cnt), o, cnd, c_lo);
+            list_flags(D, (int64_t)q0 + u * NT + (t & ~63), cnd);
         }
         // the potential change of a flipped particle, in the same order per
         // thread, after the writes: inside their loop its colloid loop
         // raised the register peak beyond the budget (spills to scratch)
 #pragma unroll
         for (int u = 0; u < PPT; ++u)
-            if (fl[u]) {
-                const int64_t o = (int64_t)q0 + slot[u];
-                du_sum += species_dU(D, cp, nc, s_Xw, (double)xn[0][o], (double)xn[1][o], (double)xn[2][o], 1, 0);
-            }
+            if (fl[u] >= 0)
+                du_sum += species_dU(D, cp, nc, s_Xw, (double)s_x[0][fl[u]], (double)s_x[1][fl[u]],
+                                     (double)s_x[2][fl[u]], 1, 0);
         ga = gb;
         if (ga < ncl) __syncthreads();   // the next group reuses the LDS
     }
@@ -1456,11 +1560,11 @@ __global__ __launch_bounds__(256) void k_observe(Work w, double* part)
     for (int j = threadIdx.x; j < CHUNK; j += 256) {
         int64_t i = base + j;
         if (i >= n) break;
-        double v0 = comp<T>(D.v[cur], n, 0)[i], v1 = comp<T>(D.v[cur], n, 1)[i],
-               v2 = comp<T>(D.v[cur], n, 2)[i];
+        const Rec<T>* q = recs<T>(D, cur) + i;
+        const double v0 = q->v[0], v1 = q->v[1], v2 = q->v[2];
         P0 += v0; P1 += v1; P2 += v2;
         ke += dot3(v0, v1, v2, v0, v1, v2);
-        nb += (double)(D.st[cur][i] & 1);
+        nb += (double)(q->st & 1u);
     }
     double r[5] = {P0, P1, P2, ke, nb};
     double* out = part ? part : D.obs_part;
@@ -1480,6 +1584,40 @@ __global__ __launch_bounds__(64) void k_observe_total(const double* part, int cn
     double s = 0.0;
     for (int c = 0; c < cnt; ++c) s += part[(int64_t)c * 8 + k];
     tot[k] = s;
+}
+
+// --------------------------------------------------- exchange with the host
+// One field of the records of buffer b as a contiguous array: 0..2 position,
+// 3..5 velocity (double, exact from FP32, rounded to it), 6 id, 7 state byte.
+template <class T>
+__global__ __launch_bounds__(256) void k_field_out(const RepDesc* Dp, int b, int field)
+{
+    const RepDesc& D = *Dp;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= D.n) return;
+    const Rec<T>* r = recs<T>(D, b) + i;
+    if (field < 6) D.xchg[i] = (double)(field < 3 ? r->x[field] : r->v[field - 3]);
+    else if (field == 6) reinterpret_cast<uint32_t*>(D.xchg)[i] = r->id;
+    else reinterpret_cast<uint8_t*>(D.xchg)[i] = (uint8_t)(r->st & ST_PUBLIC);
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_field_in(const RepDesc* Dp, int b, int field)
+{
+    const RepDesc& D = *Dp;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= D.n) return;
+    Rec<T>* r = recs<T>(D, b) + i;
+    if (field < 3) {
+        const T xt = (T)D.xchg[i];
+        r->x[field] = (double)xt >= D.Ld[field] ? (T)0 : xt;    // FP32 rounding up to L
+    } else if (field < 6) {
+        r->v[field - 3] = (T)D.xchg[i];
+    } else if (field == 6) {
+        r->id = reinterpret_cast<const uint32_t*>(D.xchg)[i];
+    } else {
+        r->st = reinterpret_cast<const uint8_t*>(D.xchg)[i];
+    }
 }
 
 // ------------------------------------------------------------ dimer analysis
@@ -1543,10 +1681,11 @@ __global__ __launch_bounds__(256) void k_analysis(Work w)
         const int64_t i = base + t + 256 * q;
         pv[q] = i < n;
         const int64_t ic = pv[q] ? i : base;
-        px[q][0] = (double)comp<T>(D.x[cur], n, 0)[ic];
-        px[q][1] = (double)comp<T>(D.x[cur], n, 1)[ic];
-        px[q][2] = (double)comp<T>(D.x[cur], n, 2)[ic];
-        psp[q] = D.st[cur][ic] & 1;
+        const Rec<T>* r = recs<T>(D, cur) + ic;
+        px[q][0] = (double)r->x[0];
+        px[q][1] = (double)r->x[1];
+        px[q][2] = (double)r->x[2];
+        psp[q] = (int)(r->st & 1u);
     }
     if (t < nb) {
         double rec[RMP_SERIES_FIELDS];
@@ -1663,23 +1802,47 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_init<T>(const RepDesc*);                          \
     template __global__ void k_init_sub<T>(const RepDesc*, const double*);       \
     template __global__ void k_list<T>(Work);                                    \
-    template __global__ void k_stream_bin<T, 1>(Work, int);                      \
-    template __global__ void k_stream_bin<T, 2>(Work, int);                      \
-    template __global__ void k_stream_bin<T, 4>(Work, int);                      \
-    template __global__ void k_scatter<T>(Work);                                 \
+    template __global__ void k_cand_write<T>(Work);                              \
+    template __global__ void k_stream<T, 1, false>(Work, int);                   \
+    template __global__ void k_stream<T, 2, false>(Work, int);                   \
+    template __global__ void k_stream<T, 4, false>(Work, int);                   \
+    template __global__ void k_stream<T, 1, true>(Work, int);                    \
+    template __global__ void k_field_out<T>(const RepDesc*, int, int);           \
+    template __global__ void k_field_in<T>(const RepDesc*, int, int);            \
     template __global__ void k_collide_big<T, 0>(Work, int);                     \
     template __global__ void k_collide_big<T, 1>(Work, int);                     \
-    template __global__ void k_collide<T, 0, 256, 2>(Work, int);                 \
-    template __global__ void k_collide<T, 1, 256, 2>(Work, int);                 \
-    template __global__ void k_collide<T, 0, 512, 2>(Work, int);                 \
-    template __global__ void k_collide<T, 1, 512, 2>(Work, int);                 \
-    template __global__ void k_collide<T, 0, 256, 1>(Work, int);                 \
-    template __global__ void k_collide<T, 1, 256, 1>(Work, int);                 \
-    template __global__ void k_collide<T, 0, 512, 1>(Work, int);                 \
-    template __global__ void k_collide<T, 1, 512, 1>(Work, int);                 \
+    template __global__ void k_collide<T, 0, 64, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 64, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 64, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 64, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 0, 64, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 64, 1, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 64, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 64, 1, true>(Work, int); \
+    template __global__ void k_collide<T, 0, 256, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 256, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 256, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 256, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 0, 512, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 512, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 512, 2, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 512, 2, true>(Work, int); \
+    template __global__ void k_collide<T, 0, 256, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 256, 1, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 256, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 256, 1, true>(Work, int); \
+    template __global__ void k_collide<T, 0, 512, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 0, 512, 1, true>(Work, int); \
+    template __global__ void k_collide<T, 1, 512, 1, false>(Work, int); \
+    template __global__ void k_collide<T, 1, 512, 1, true>(Work, int); \
+    template __global__ void k_collide_dense<T, 0, 256, 2>(Work, int);           \
+    template __global__ void k_collide_dense<T, 1, 256, 2>(Work, int);           \
     template __global__ void k_observe<T>(Work, double*);                     \
     template __global__ void k_analysis<T>(Work);
 
+template __global__ void k_perm<1>(Work, int);
+template __global__ void k_perm<2>(Work, int);
+template __global__ void k_perm<4>(Work, int);
 RMP_INST(double)
 RMP_INST(float)
 

@@ -1,5 +1,5 @@
 // Device helpers shared by the kernels: wave and block reductions, scans,
-// the cell key, the Verlet-list test.
+// the cell key, the Verlet-list test, streaming and in-cell ranks.
 #pragma once
 #include "rmp_device.h"
 
@@ -208,6 +208,27 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* sbuf)
     return r;
 }
 
+// ordering of LDS accesses between lanes of one wave (no workgroup barrier)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a value known to be the same in all lanes, in scalar registers
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
+__device__ __forceinline__ double uniform_d(double v)
+{
+    return __longlong_as_double((long long)uniform_u64((uint64_t)__double_as_longlong(v)));
+}
+
 // exclusive block scan of u32, returns the prefix of this thread; *total set
 template <int NT>
 __device__ __forceinline__ uint32_t block_exscan_u32(uint32_t v, uint32_t* sbuf, uint32_t* total)
@@ -246,24 +267,22 @@ __device__ __forceinline__ void shift_of(uint64_t seed, int64_t coll, double s[3
 // x + Lx (y + Ly z) in the row-major order; in the compact-Hilbert order its
 // rank along the curve, computed for a cubic power-of-two box and otherwise
 // looked up by the linear index.
+// FLOW false: known not to be a flow (no plates).
+template <bool FLOW = true>
 __device__ __forceinline__ uint32_t cell_key(const RepDesc& D, double x0, double x1, double x2,
                                              const double s[3])
 {
-    int64_t c[3];
+    int c[3];
     const double xs[3] = {x0, x1, x2};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        double fq = floor(xs[d] - s[d]);
-        if (d == 2 && D.walls) {
-            // plates: layers floor(z - s) + 1 in [0, L_z], not periodic
-            c[d] = (fq >= -1.0 && fq < (double)(D.L[d] - 1)) ? (int64_t)fq + 1 : 0;
-            continue;
-        }
-        int64_t q = (fq >= -1.0 && fq < (double)D.L[d]) ? (int64_t)fq : 0;   // NaN-safe
-        if (q < 0) q += D.L[d];
-        c[d] = q;
+        const double fq = floor(xs[d] - s[d]);
+        const bool in = fq >= -1.0 && fq < D.Ld[d];        // NaN-safe
+        const int q = in ? (int)fq : (FLOW && d == 2 && D.walls ? -1 : 0);
+        // plates: layers floor(z - s) + 1 in [0, L_z], not periodic
+        c[d] = FLOW && d == 2 && D.walls ? q + 1 : (q < 0 ? q + D.L[d] : q);
     }
-    const uint32_t lin = (uint32_t)(c[0] + (int64_t)D.L[0] * (c[1] + (int64_t)D.L[1] * c[2]));
+    const uint32_t lin = (uint32_t)c[0] + (uint32_t)D.L[0] * ((uint32_t)c[1] + (uint32_t)D.L[1] * (uint32_t)c[2]);
     if (D.hbits == KEY_ROW) return lin;
     if (D.hbits >= 0) return hilbert_index((uint32_t)c[0], (uint32_t)c[1], (uint32_t)c[2], D.hbits);
     return D.rank_of[lin];
@@ -313,10 +332,247 @@ __device__ __forceinline__ double species_dU(const RepDesc& D, const ColloidPara
     return du;
 }
 
+// the records of buffer b
 template <class T>
-__device__ __forceinline__ T* comp(void* base, int64_t n, int d)
+__device__ __forceinline__ Rec<T>* recs(const RepDesc& D, int b)
 {
-    return reinterpret_cast<T*>(base) + (int64_t)d * n;
+    return reinterpret_cast<Rec<T>*>(D.rec[b]);
+}
+
+// ------------------------------------------------- free streaming + binning
+
+// Rank of this lane's particle within its cell, with one atomic per run of
+// equal keys in consecutive lanes (particles arrive sorted by the previous
+// collision's cells, so runs are common).  All 64 lanes must call it.
+struct RankIssue {
+    uint32_t base;             // the run head's atomic result (head lanes only)
+    int h;                     // lane of this lane's run head
+};
+
+__device__ __forceinline__ RankIssue wave_rank_issue(gptr<uint32_t> count, uint32_t key, bool valid)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t k = valid ? key : 0xffffffffu;
+    const uint32_t prev = __shfl_up(k, 1, 64);
+    const bool head = (lane == 0) || (k != prev);
+    const uint64_t H = __ballot(head);
+    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
+    const int h = 63 - __clzll(H & upto);
+    const uint64_t above = (h == 63) ? 0ull : (H & (~0ull << (h + 1)));
+    const int nexth = above ? (__ffsll((long long)above) - 1) : 64;
+    RankIssue r;
+    r.base = 0;
+    r.h = h;
+    if (head && valid)
+        r.base = __hip_atomic_fetch_add(count + key, (uint32_t)(nexth - h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return r;
+}
+
+__device__ __forceinline__ uint32_t wave_rank_finish(const RankIssue& r)
+{
+    const int lane = threadIdx.x & 63;
+    return __shfl(r.base, r.h, 64) + (uint32_t)(lane - r.h);
+}
+
+// One streaming step under the constant acceleration g, with the plates at
+// z = 0 and z = L_z when present: half kick, drift, half kick; a drift that
+// crosses a plate is cut at the crossing time, the velocity reversed
+// (bounce-back) and the rest of the step travelled back.
+template <class T>
+__device__ __forceinline__ T below(T L);
+template <>
+__device__ __forceinline__ double below<double>(double L) { return nextafter(L, 0.0); }
+template <>
+__device__ __forceinline__ float below<float>(float L) { return nextafterf(L, 0.0f); }
+
+template <class T>
+__device__ __forceinline__ void flow_step(T (&x)[3], T (&v)[3], const T (&g)[3], T dt, T hdt,
+                                          const T (&L)[3], bool walls)
+{
+    T y[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        v[d] = tfma(hdt, g[d], v[d]);
+        y[d] = tfma(dt, v[d], x[d]);
+    }
+    if (walls) {
+        if (y[2] < (T)0 || y[2] >= L[2]) {
+            const T wz = y[2] < (T)0 ? (T)0 : L[2];
+            const T ts = (wz - x[2]) / v[2];
+            const T rem = dt - ts;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T xc = tfma(ts, v[d], x[d]);
+                v[d] = -v[d];
+                y[d] = tfma(rem, v[d], xc);
+            }
+            if (y[2] >= L[2]) y[2] = below<T>(L[2]);
+            if (y[2] < (T)0) y[2] = (T)0;
+        }
+        x[0] = wrap_coord<T>(y[0], L[0]);
+        x[1] = wrap_coord<T>(y[1], L[1]);
+        x[2] = y[2];
+    } else {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) x[d] = wrap_coord<T>(y[d], L[d]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) v[d] = tfma(hdt, g[d], v[d]);
+}
+
+// Streaming of P particles over an interval in registers (those with go[u];
+// all lanes of a wave call it).  Flows (constant acceleration, plates) take
+// n_md flow_steps.  Otherwise a particle outside the Verlet list feels no
+// force: n_md drifts x <- fma(dt, v, x) with a periodic wrap after each.
+//
+// A coordinate moving down is negated (rounding is symmetric), so every
+// coordinate m grows by |v| dt per step and leaves the box at one upper bound:
+// moving up at m >= L, moving down at -m < 0, that is m >= the smallest
+// positive number; either way the wrap is then m - L (and -L, where y + L
+// rounded to L and the wrap subtracts L again, becomes zero).  If no lane's m
+// is outside after all n_md drifts, none wrapped; otherwise the drifts are
+// done again in runs of DRIFT_RUN, and a run in which a coordinate of some
+// lane left the box once more for that coordinate with the wrap after each
+// drift, without branches.  (Doing all n_md drifts again with branches, one
+// coordinate after the other, held up whole collision tiles behind one wave.)  A coordinate that
+// starts outside the box, or a step longer than it, takes the drifts as they
+// are defined (drift_wrapped).
+constexpr int DRIFT_RUN = 10;
+
+template <class T> __device__ __forceinline__ T tiny();
+template <> __device__ __forceinline__ double tiny<double>() { return 4.9406564584124654e-324; }
+template <> __device__ __forceinline__ float tiny<float>() { return 1.401298464e-45f; }
+
+// the drifts as they are defined, for a coordinate outside the box or a step
+// beyond its edge (both leave it outside)
+template <class T, int P>
+__device__ __forceinline__ void drift_wrapped(int nmd, T dt, const T (&Lt)[3], T (&x)[P][3], const T (&v)[P][3],
+                                              const bool (&go)[P])
+{
+    for (int k = 0; k < nmd; ++k)
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T y = wrap_coord<T>(tfma(dt, v[u][d], x[u][d]), Lt[d]);
+                x[u][d] = go[u] ? y : x[u][d];
+            }
+}
+
+template <class T, int P, bool FLOW = true>
+__device__ __forceinline__ void advance(const RepDesc& D, T (&x)[P][3], T (&v)[P][3], const bool (&go)[P])
+{
+    const int nmd = D.n_md;
+    const T dt = (T)D.dt;
+    const T Lt[3] = {(T)D.Ld[0], (T)D.Ld[1], (T)D.Ld[2]};
+    if (FLOW && D.flow) {
+        const T g[3] = {(T)D.g[0], (T)D.g[1], (T)D.g[2]};
+        const T hdt = (T)(0.5 * D.dt);
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+            if (go[u])
+                for (int k = 0; k < nmd; ++k) {
+                    // v is opaque at the head of each step: without this hipcc 7.2 lost the
+                    // copy of v[1] that starts a step (its registers then held other data)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) asm volatile("" : "+v"(v[u][d]));
+                    flow_step<T>(x[u], v[u], g, dt, hdt, Lt, D.walls != 0);
+                }
+        return;
+    }
+    T m[P][3];
+#pragma unroll
+    for (int u = 0; u < P; ++u)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) m[u][d] = v[u][d] < (T)0 ? -x[u][d] : x[u][d];
+    {
+        T z[P][3];
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) z[u][d] = m[u][d];
+#pragma unroll 5
+        for (int k = 0; k < nmd; ++k)
+#pragma unroll
+            for (int u = 0; u < P; ++u)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) z[u][d] = tfma(dt, tabs(v[u][d]), z[u][d]);
+        bool out = false, odd = false;
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                out = out || (go[u] && z[u][d] >= (v[u][d] < (T)0 ? tiny<T>() : Lt[d]));
+                odd = odd || (go[u] && !(m[u][d] > (v[u][d] < (T)0 ? -Lt[d] : -tiny<T>())));
+            }
+        if (__ballot(out || odd) == 0ull) {
+#pragma unroll
+            for (int u = 0; u < P; ++u)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) x[u][d] = go[u] ? (v[u][d] < (T)0 ? -z[u][d] : z[u][d]) : x[u][d];
+            return;
+        }
+    }
+    {
+        bool odd = false;
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                odd = odd || (go[u] && (!(m[u][d] > (v[u][d] < (T)0 ? -Lt[d] : -tiny<T>())) ||
+                                        !(dt * tabs(v[u][d]) < Lt[d])));
+        if (__ballot(odd) != 0ull) {
+            drift_wrapped<T, P>(nmd, dt, Lt, x, v, go);
+            return;
+        }
+    }
+    for (int k0 = 0; k0 < nmd; k0 += DRIFT_RUN) {
+        const int nk = nmd - k0 < DRIFT_RUN ? nmd - k0 : DRIFT_RUN;
+        T z[P][3];
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) z[u][d] = m[u][d];
+#pragma unroll 2
+        for (int k = 0; k < nk; ++k)
+#pragma unroll
+            for (int u = 0; u < P; ++u)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) z[u][d] = tfma(dt, tabs(v[u][d]), z[u][d]);
+#pragma unroll
+        for (int u = 0; u < P; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const T top = v[u][d] < (T)0 ? tiny<T>() : Lt[d];
+                if (__ballot(go[u] && z[u][d] >= top) != 0ull) {
+                    T y = m[u][d];
+                    for (int k = 0; k < nk; ++k) {
+                        y = tfma(dt, tabs(v[u][d]), y);
+                        T w = y - Lt[d];
+                        w = w <= -Lt[d] ? (T)0 : w;
+                        y = y >= top ? w : y;
+                    }
+                    z[u][d] = y;
+                }
+                m[u][d] = z[u][d];
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < P; ++u)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const T y = v[u][d] < (T)0 ? (T)0 - m[u][d] : m[u][d];
+            x[u][d] = go[u] ? y : x[u][d];
+        }
+}
+
+// Workgroups are dealt to the eight XCDs in turn: work item of workgroup b of
+// a launch of g such that each XCD takes a contiguous range of items, so that
+// neighbouring items, which touch the same lines, share an L2.
+__device__ __forceinline__ int xcd_range(unsigned b, unsigned g)
+{
+    const unsigned x = b & 7u, per = g >> 3, rem = g & 7u;
+    return (int)(x * per + (x < rem ? x : rem) + (b >> 3));
 }
 
 }  // namespace rmp
