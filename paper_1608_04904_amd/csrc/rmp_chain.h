@@ -291,6 +291,12 @@ __device__ __forceinline__ void rattle_vel_lane(const BondLane& L, const double 
     }
 }
 
+// Bound by the latency of its dependent steps: 32^3 with one dimer, 34
+// workgroups, 4.6 us per MD step, of which the colloid update takes 1.0, the
+// forces with the workgroup's tree 1.3 and the exchange 2.0 (5.2 before the
+// trees gave each lane one value and the image of a colloid near the box
+// needed no division).
+//
 // Chain workgroup g of a replica holds Verlet-list positions
 // [g*B, (g+1)*B), B = NT*K (NT = 256 or 512 threads), K consecutive
 // positions per thread, in registers for the whole interval.
@@ -335,7 +341,10 @@ __device__ __forceinline__ ChainConst chain_const(const RepDesc& D, uint64_t bud
 // unrolled for one or two colloids, which never run it).
 template <int NT, int NB>
 struct ChainCtx {
-    double sXw[MAXC][3];       // periodic images of the colloid positions
+    // periodic images of the colloid positions, the buffer step & 1 for MD step
+    // `step` (0 at the start): wave 0 sets those of the next step while the
+    // other waves still read this step's
+    double sXw[2][MAXC][3];
     // colloid constants read in every MD step, staged once per interval
     double cRc2[MAXC], cSig2[MAXC], cEpsA[MAXC], cEpsB[MAXC], cSigma[MAXC];
     double cCull2[MAXC];       // (cut-off + reach margin)^2 of the interval's cull
@@ -376,14 +385,14 @@ struct ChainCtx {
 // species_dU for an A -> B flip inside the MD chain, with the colloid
 // constants from LDS (same arithmetic)
 template <class Ctx>
-__device__ __forceinline__ double species_dU_lds(const Ctx& S, const ChainConst& cc, int nc, double x0, double x1,
-                                                 double x2)
+__device__ __forceinline__ double species_dU_lds(const Ctx& S, const double (*Xw)[3], const ChainConst& cc, int nc,
+                                                 double x0, double x1, double x2)
 {
     double du = 0.0;
     for (int c = 0; c < nc; ++c) {
-        double dx = min_image(x0 - S.sXw[c][0], cc.L(0), cc.h(0));
-        double dy = min_image(x1 - S.sXw[c][1], cc.L(1), cc.h(1));
-        double dz = min_image(x2 - S.sXw[c][2], cc.L(2), cc.h(2));
+        double dx = min_image(x0 - Xw[c][0], cc.L(0), cc.h(0));
+        double dy = min_image(x1 - Xw[c][1], cc.L(1), cc.h(1));
+        double dz = min_image(x2 - Xw[c][2], cc.L(2), cc.h(2));
         double r2 = dot3(dx, dy, dz, dx, dy, dz);
         if (r2 < S.cRc2[c]) {
             double cf, p0, p1;
@@ -400,15 +409,15 @@ __device__ __forceinline__ double species_dU_lds(const Ctx& S, const ChainConst&
 // images; `on` is 0 when the two are of one rigid body or beyond the cut-off
 // (then the values are not used)
 template <class Ctx>
-__device__ __forceinline__ void pair_force(const Ctx& S, const ChainConst& cc, const ColloidParams* cp, int a,
+__device__ __forceinline__ void pair_force(const Ctx& S, const double (*Xw)[3], const ChainConst& cc, const ColloidParams* cp, int a,
                                            int b, double (&out)[4], uint8_t& on)
 {
     on = 0;
     out[0] = 0.0; out[1] = 0.0; out[2] = 0.0; out[3] = 0.0;
     if (S.cBody[a] == S.cBody[b]) return;
-    const double dx = min_image(S.sXw[a][0] - S.sXw[b][0], cc.L(0), cc.h(0));
-    const double dy = min_image(S.sXw[a][1] - S.sXw[b][1], cc.L(1), cc.h(1));
-    const double dz = min_image(S.sXw[a][2] - S.sXw[b][2], cc.L(2), cc.h(2));
+    const double dx = min_image(Xw[a][0] - Xw[b][0], cc.L(0), cc.h(0));
+    const double dy = min_image(Xw[a][1] - Xw[b][1], cc.L(1), cc.h(1));
+    const double dz = min_image(Xw[a][2] - Xw[b][2], cc.L(2), cc.h(2));
     const double r2 = dot3(dx, dy, dz, dx, dy, dz);
     const double sab = S.cSigma[a] + S.cSigma[b];
     const double rc = 0x1.1f59ac3c7d6c0p+0 * sab;
@@ -427,7 +436,7 @@ __device__ __forceinline__ void pair_force(const Ctx& S, const ChainConst& cc, c
 // waves).  With several workgroups the node values are then published for
 // the others (chain_collect completes the tree over workgroups).
 template <class T, int K, int NT, int NB>
-__device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const ChainConst& cc, const ColloidParams* cp,
+__device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const double (*Xw)[3], const ChainConst& cc, const ColloidParams* cp,
                               int nc, const bool* valid, const T (*x)[3], const T (*x0)[3], const uint8_t* st,
                               double (*f)[3], bool* inside, int g, int Gact, bool solo,
                               uint32_t& wmask, double me2, uint32_t& nbar, uint32_t epoch0)
@@ -468,14 +477,14 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const ChainCo
     constexpr int CB = 2;
     bool hit_any = false;        // some entry of this wave hit some colloid so far
     for (int c0 = 0; c0 < nc; c0 += CB) {
-        double tv[3 * CB + 1];
+        double tv[8];
         bool hit_chunk = false;  // ... one of this pair of colloids
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int c = c0 + cb;
             tv[3 * cb + 0] = 0.0; tv[3 * cb + 1] = 0.0; tv[3 * cb + 2] = 0.0;
             if (c >= nc || !((reach_mask >> c) & 1u)) continue;
-            const double Xc0 = S.sXw[c][0], Xc1 = S.sXw[c][1], Xc2 = S.sXw[c][2];
+            const double Xc0 = Xw[c][0], Xc1 = Xw[c][1], Xc2 = Xw[c][2];
             const double rc2 = S.cRc2[c], sig2 = S.cSig2[c];
             const double eA = S.cEpsA[c], eB = S.cEpsB[c];
             const bool cat = S.cCat[c] != 0;
@@ -527,7 +536,7 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const ChainCo
             tv[3 * cb + 0] = gx[0]; tv[3 * cb + 1] = gy[0]; tv[3 * cb + 2] = gz[0];
         }
         const bool last = c0 + CB >= nc;
-        tv[3 * CB] = 0.0;
+        tv[3 * CB] = tv[7] = 0.0;
         if (last) {
             double a[K];
 #pragma unroll
@@ -541,19 +550,11 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const ChainCo
         hit_any = hit_any || hit_chunk;
         // no entry of the wave inside either colloid's cut-off (and, for the
         // potential, inside any): every value is +0.0, and so is its tree
-        if (hit_chunk || (last && hit_any)) wave_tree_sum_n<3 * CB + 1>(tv);
-        if (lane == 0) {
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                const int c = c0 + cb;
-                if (c < nc) {
-                    S.sRed[wave][3 * c + 0] = tv[3 * cb + 0];
-                    S.sRed[wave][3 * c + 1] = tv[3 * cb + 1];
-                    S.sRed[wave][3 * c + 2] = tv[3 * cb + 2];
-                }
-            }
-            if (last) S.sRed[wave][3 * nc] = tv[3 * CB];
-        }
+        // (lane k: component k of the pair, lane 6 the potential)
+        double sum = 0.0;
+        if (hit_chunk || (last && hit_any)) sum = wave_tree_spread<8>(tv);
+        const int o = lane == 3 * CB ? 3 * nc : 3 * c0 + lane;
+        if (lane < 3 * CB ? o < 3 * nc : (lane == 3 * CB && last)) S.sRed[wave][o] = sum;
     }
     if (nc == 0) {
         // no colloid: the potential of the list is zero (tree of zeros)
@@ -619,7 +620,7 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const ChainCo
 // the cut-off plus the reach margin (me plus half the skin, cCull2), one lane
 // per colloid.  Systems of one or two colloids test them all.
 template <class T, int K, int NT, int NB>
-__device__ __forceinline__ uint32_t reach_box(const ChainCtx<NT, NB>& S, const ChainConst& cc, int nc,
+__device__ __forceinline__ uint32_t reach_box(const ChainCtx<NT, NB>& S, const double (*Xw)[3], const ChainConst& cc, int nc,
                                               const bool* valid, const T (*x)[3])
 {
     const int lane = threadIdx.x & 63;
@@ -646,7 +647,7 @@ __device__ __forceinline__ uint32_t reach_box(const ChainCtx<NT, NB>& S, const C
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             if (!(hi[d] - lo[d] < cc.h(d))) continue;          // wide (or no entry): no bound
-            const double oc = min_image(S.sXw[lane][d] - ref[d], cc.L(d), cc.h(d));
+            const double oc = min_image(Xw[lane][d] - ref[d], cc.L(d), cc.h(d));
             double dd = 1e300;
 #pragma unroll
             for (int img = -1; img <= 1; ++img) {
@@ -819,14 +820,14 @@ __device__ __forceinline__ void exchange_master(ChainCtx<NT, NB>& S, const Chain
 // sXw) for the other workgroups, each double as two words tagged with the
 // barrier's epoch, then the flag word (sFull << 32 | epoch).  Wave 0.
 template <int NT, int NB>
-__device__ __forceinline__ void broadcast_images(ChainCtx<NT, NB>& S, const ChainConst& cc, int nc, uint32_t nbar,
+__device__ __forceinline__ void broadcast_images(ChainCtx<NT, NB>& S, const double (*Xw)[3], const ChainConst& cc, int nc, uint32_t nbar,
                                                  uint32_t epoch0)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t epoch = epoch0 + nbar;
     const gptr<uint64_t> B = cc.part() + (int64_t)(nbar & 1) * cc.stride() + cc.G() * (int64_t)ROWW;
     for (int k = lane; k < 3 * nc; k += 64) {
-        const double val = S.sXw[k / 3][k % 3];
+        const double val = Xw[k / 3][k % 3];
         const uint64_t lo = ((uint64_t)(uint32_t)__double2loint(val) << 32) | epoch;
         const uint64_t hi = ((uint64_t)(uint32_t)__double2hiint(val) << 32) | epoch;
         __hip_atomic_store(&B[2 * k], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -841,7 +842,7 @@ __device__ __forceinline__ void broadcast_images(ChainCtx<NT, NB>& S, const Chai
 // MD step into sXw and sFull.  Wave 0: lane 0 polls the flag word, then the
 // wave reads the positions (read again if a word is not yet current).
 template <int NT, int NB>
-__device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, const ChainConst& cc, int nc, uint32_t nbar,
+__device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, double (*Xw)[3], const ChainConst& cc, int nc, uint32_t nbar,
                                              uint32_t epoch0)
 {
     const int lane = threadIdx.x & 63;
@@ -874,7 +875,7 @@ __device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, const ChainCon
             const uint64_t lo = __hip_atomic_load(&B[2 * k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint64_t hi = __hip_atomic_load(&B[2 * k + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             good = good && (uint32_t)lo == epoch && (uint32_t)hi == epoch;
-            S.sXw[k / 3][k % 3] = __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
+            Xw[k / 3][k % 3] = __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
         }
         if (__ballot(!good) == 0) break;
         if (wall_clock64() - t_start > cc.budget()) {
@@ -889,12 +890,12 @@ __device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, const ChainCon
 // v < nv) of workgroups [0, Gact) at this barrier, then reduce each value
 // over the workgroups with the fixed tree: lane l holds workgroups
 // [l*Q, l*Q+Q) (Q <= QM), summed pairwise, then the wave tree, padded with
-// zeros to a power of two.  out[vb] is the same in every lane.  Only slots
+// zeros to a power of two.  Lane l returns value v0 + (l % VB) vs.  Only slots
 // that exist are loaded (wave-uniform guards): a co-resident workgroup that
 // is still computing must not be starved by polling traffic.
 template <int VB, int QM, class Ctx>
-__device__ __forceinline__ void poll_reduce(Ctx& S, gptr<const uint64_t> part, int64_t Gs, int v0, int vs, int nv,
-                                            int Gact, int Q, uint32_t epoch, uint64_t budget, double (&out)[VB])
+__device__ __forceinline__ double poll_reduce(Ctx& S, gptr<const uint64_t> part, int64_t Gs, int v0, int vs, int nv,
+                                            int Gact, int Q, uint32_t epoch, uint64_t budget)
 {
     const int lane = threadIdx.x & 63;
     double b4[VB][QM];
@@ -947,6 +948,7 @@ __device__ __forceinline__ void poll_reduce(Ctx& S, gptr<const uint64_t> part, i
         // a long wait backs off (128 clocks a round after the first 16)
         if (++nap > 16) __builtin_amdgcn_s_sleep(2);
     }
+    double out[VB];
 #pragma unroll
     for (int vb = 0; vb < VB; ++vb) {
         double a2 = b4[vb][0];
@@ -955,7 +957,7 @@ __device__ __forceinline__ void poll_reduce(Ctx& S, gptr<const uint64_t> part, i
             a2 = (b4[vb][0] + b4[vb][QM >= 4 ? 1 : 0]) + (b4[vb][QM >= 4 ? 2 : 0] + b4[vb][QM >= 4 ? 3 : 0]);
         out[vb] = a2;
     }
-    wave_tree_sum_n<VB>(out);
+    return wave_tree_spread<VB>(out);
 }
 
 // Second half: wait for the other workgroups' node values of this
@@ -975,7 +977,7 @@ struct PairLane {
 };
 
 template <class T, int K, int NT, int NB>
-__device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const ChainConst& cc, const ColloidParams* cp,
+__device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const double (*Xw)[3], const ChainConst& cc, const ColloidParams* cp,
                               int nc, int g, int Gact, int Gpad, uint32_t nbar, uint32_t epoch0,
                               bool want_potential, double (&cF)[3], const PairLane& PL)
 {
@@ -994,7 +996,7 @@ __device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const ChainCo
             int a = 0, rem = p;
             while (rem >= nc - 1 - a) { rem -= nc - 1 - a; ++a; }
             const int b = a + 1 + rem;
-            pair_force(S, cc, cp, a, b, S.sPairF[p], S.sPairOn[p]);
+            pair_force(S, Xw, cc, cp, a, b, S.sPairF[p], S.sPairOn[p]);
             if (S.sPairOn[p]) {
                 atomicOr(&S.sPairMask[a], 1u << b);
                 atomicOr(&S.sPairMask[b], 1u << a);
@@ -1005,12 +1007,8 @@ __device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const ChainCo
         if (solo) {
             const uint32_t epoch = epoch0 + nbar;
             const gptr<const uint64_t> part = cc.part() + (int64_t)(nbar & 1) * cc.stride();
-            double out[8];
-            poll_reduce<8, 1>(S, part, cc.G(), 0, 1, nv, Gact, 1, epoch, cc.budget(), out);
-            if (lane == 0)
-#pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    if (v < nv) S.sNode[v] = out[v];
+            const double out = poll_reduce<8, 1>(S, part, cc.G(), 0, 1, nv, Gact, 1, epoch, cc.budget());
+            if (lane < nv) S.sNode[lane] = out;
         } else {
             exchange_master(S, cc, nc, Gact, nbar, epoch0);
         }
@@ -1055,9 +1053,9 @@ __device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const ChainCo
             const int ct_a = S.cType[a];
             const bool c_lo = c < a;
             const int lo = c_lo ? c : a, hi = c_lo ? a : c;
-            double dx = min_image(S.sXw[lo][0] - S.sXw[hi][0], cc.L(0), cc.h(0));
-            double dy = min_image(S.sXw[lo][1] - S.sXw[hi][1], cc.L(1), cc.h(1));
-            double dz = min_image(S.sXw[lo][2] - S.sXw[hi][2], cc.L(2), cc.h(2));
+            double dx = min_image(Xw[lo][0] - Xw[hi][0], cc.L(0), cc.h(0));
+            double dy = min_image(Xw[lo][1] - Xw[hi][1], cc.L(1), cc.h(1));
+            double dz = min_image(Xw[lo][2] - Xw[hi][2], cc.L(2), cc.h(2));
             double r2 = dot3(dx, dy, dz, dx, dy, dz);
             double sab = c_lo ? PL.sigma + sig_a : sig_a + PL.sigma;
             double rc = 0x1.1f59ac3c7d6c0p+0 * sab;
@@ -1078,9 +1076,9 @@ __device__ __forceinline__ void chain_collect(ChainCtx<NT, NB>& S, const ChainCo
         for (int a = 0; a < nc; ++a)
             for (int b = a + 1; b < nc; ++b) {
                 if (cp->body[a] == cp->body[b]) continue;
-                double dx = min_image(S.sXw[a][0] - S.sXw[b][0], cc.L(0), cc.h(0));
-                double dy = min_image(S.sXw[a][1] - S.sXw[b][1], cc.L(1), cc.h(1));
-                double dz = min_image(S.sXw[a][2] - S.sXw[b][2], cc.L(2), cc.h(2));
+                double dx = min_image(Xw[a][0] - Xw[b][0], cc.L(0), cc.h(0));
+                double dy = min_image(Xw[a][1] - Xw[b][1], cc.L(1), cc.h(1));
+                double dz = min_image(Xw[a][2] - Xw[b][2], cc.L(2), cc.h(2));
                 double r2 = dot3(dx, dy, dz, dx, dy, dz);
                 double sab = cp->sigma[a] + cp->sigma[b];
                 double rc = 0x1.1f59ac3c7d6c0p+0 * sab;
@@ -1157,7 +1155,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             cX[d] = rs->X[t][d];
             cV[d] = rs->V[t][d];
             cX0[d] = cX[d];
-            S.sXw[t][d] = colloid_image(cX[d], cc.L(d));
+            S.sXw[0][t][d] = colloid_image(cX[d], cc.L(d));
         }
         S.cRc2[t] = cp->rc2[t];
         {
@@ -1221,7 +1219,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
     }
     __syncthreads();
     // this wave's colloids within reach for the interval
-    uint32_t wmask = reach_box<T, K>(S, cc, nc, valid, x);
+    uint32_t wmask = reach_box<T, K>(S, S.sXw[0], cc, nc, valid, x);
     const double me2 = D.cull_me * D.cull_me;
     // Roles: with one workgroup, or in the solo form, every workgroup
     // completes the exchange and updates the colloids itself; otherwise
@@ -1241,8 +1239,8 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
     const bool colloid_wave = t < 64;
 
     // forces at the start of the interval
-    chain_compute<T, K, NT>(S, cc, cp, nc, valid, x, x0, st, f, inside, g, Gact, solo, wmask, me2, nbar, epoch0);
-    if (updates) chain_collect<T, K, NT>(S, cc, cp, nc, g, Gact, Gpad, nbar, epoch0, false, cF, PL);
+    chain_compute<T, K, NT>(S, S.sXw[0], cc, cp, nc, valid, x, x0, st, f, inside, g, Gact, solo, wmask, me2, nbar, epoch0);
+    if (updates) chain_collect<T, K, NT>(S, S.sXw[0], cc, cp, nc, g, Gact, Gpad, nbar, epoch0, false, cF, PL);
     // list entries: first half kick and drift of step 0
 #pragma unroll
     for (int j = 0; j < K; ++j)
@@ -1254,11 +1252,12 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
 
     double eu = 0.0, ef = 0.0;
     for (int step = 0; step < nmd; ++step) {
+        double (*Xw)[3] = S.sXw[(step + 1) & 1];
         const int64_t md = md0 + step;
         // colloids (wave 0, in registers): half kick, drift, RATTLE
         // position stage, periodic images for the force evaluation
         if (worker) {
-            if (colloid_wave) await_images(S, cc, nc, nbar, epoch0);
+            if (colloid_wave) await_images(S, Xw, cc, nc, nbar, epoch0);
         } else if (colloid_wave) {
             double cXo[3];
             if (t < nc) {
@@ -1296,7 +1295,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             }
             if (lflags) atomicOr(&S.sflags, lflags);
             if (t < nc) {
-                for (int d = 0; d < 3; ++d) S.sXw[t][d] = colloid_image(cX[d], cc.L(d));
+                for (int d = 0; d < 3; ++d) Xw[t][d] = colloid_image(cX[d], cc.L(d));
                 // a colloid beyond half the skin from its interval-start
                 // position voids the reach masks of the interval
                 const double dx = cX[0] - cX0[0], dy = cX[1] - cX0[1], dz = cX[2] - cX0[2];
@@ -1305,11 +1304,11 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             }
             if (Gact > 1 && !solo) {
                 wave_sync();
-                broadcast_images(S, cc, nc, nbar, epoch0);
+                broadcast_images(S, Xw, cc, nc, nbar, epoch0);
             }
         }
         __syncthreads();
-        chain_compute<T, K, NT>(S, cc, cp, nc, valid, x, x0, st, f, inside, g, Gact, solo, wmask, me2, nbar,
+        chain_compute<T, K, NT>(S, Xw, cc, cp, nc, valid, x, x0, st, f, inside, g, Gact, solo, wmask, me2, nbar,
                                 epoch0);
         // while the other workgroups' sums arrive: the list entries' second
         // half kick, catalysis, and (except after the last step) the next
@@ -1338,7 +1337,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
                 if (flip) {
                     st[j] = 1;
                     ef += 1.0;
-                    eu += species_dU_lds(S, cc, nc, (double)x[j][0], (double)x[j][1], (double)x[j][2]);
+                    eu += species_dU_lds(S, Xw, cc, nc, (double)x[j][0], (double)x[j][1], (double)x[j][2]);
                 } else {
                     st[j] = 0;
                 }
@@ -1355,7 +1354,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
         }
         // the potential energy is an observable of the last force evaluation
         if (updates)
-            chain_collect<T, K, NT>(S, cc, cp, nc, g, Gact, Gpad, nbar, epoch0, step == nmd - 1, cF, PL);
+            chain_collect<T, K, NT>(S, Xw, cc, cp, nc, g, Gact, Gpad, nbar, epoch0, step == nmd - 1, cF, PL);
         // colloids (wave 0, in registers): second half kick, RATTLE
         // velocity stage, Verlet-list soundness check (displacement within
         // the interval)
@@ -1449,8 +1448,14 @@ __device__ __forceinline__ void chain_run(Work w, int item)
     chain_body<T, K, NC, NT>(w, g, D, chain_const(D, w.budget));
 }
 
+// Waves per SIMD that the chain's registers leave room for: two (one with four
+// entries per thread).  Launches in waves of one- and two-colloid systems take
+// three, so that more systems run at once (64 dimer systems, one interval:
+// FP64 1989 -> 1921 us, FP32 1752 -> 1619; four spill: 2090).
+constexpr int chain_waves(int k, bool ticket, int nc) { return k == 4 ? 1 : ticket && nc > 0 ? 3 : 2; }
+
 template <class T, int K, bool TICKET, int NC, int NT>
-__global__ __launch_bounds__(NT) void k_chain(Work w)
+__global__ __launch_bounds__(NT, chain_waves(K, TICKET, NC)) void k_chain(Work w)
 {
     // only in the one- and two-colloid variants: with the priority code in
     // the generic variant its 128^3 launches ran 10 % slower even with the

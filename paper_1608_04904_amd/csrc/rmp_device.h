@@ -90,6 +90,13 @@ __device__ __forceinline__ double min_image(double d, double L, double halfL)
 // image in [0, L) of an unwrapped colloid coordinate
 __device__ __forceinline__ double colloid_image(double X, double L)
 {
+    // within a box length of the box, what the general form below gives, without
+    // its division: X - L is exact in [L, 2 L), and the general form's quotient
+    // rounds past an integer only where its last correction undoes that
+    if (X >= -L && X < L + L) {
+        double w = X < 0.0 ? X + L : (X >= L ? X - L : X);
+        return w >= L ? w - L : w;
+    }
     double k = floor(X / L);
     double w = X - k * L;
     if (w >= L) {

@@ -61,6 +61,62 @@ __device__ __forceinline__ void wave_tree_sum_n(double (&v)[N])
     }
 }
 
+// wave_tree_sum of N = 4 or 8 values, lane l returning that of value l % N: at
+// each of the first levels a lane keeps one of two values and gives the other
+// to its partner, so that a level handles half the values of the one before
+// (8 values: 64 instructions where wave_tree_sum_n takes 160).  The same two
+// operands are added at every level as above.
+__device__ __forceinline__ double sel_d(bool c, double a, double b)
+{
+    return __hiloint2double(c ? __double2hiint(a) : __double2hiint(b), c ? __double2loint(a) : __double2loint(b));
+}
+
+// the value of lane l ^ 4
+__device__ __forceinline__ int dpp_xor4(int v)
+{
+    const int up = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, false);    // row_shl:4 into banks 0, 2
+    return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);           // row_shr:4 into banks 1, 3
+}
+
+// x of the lanes' 16- or 32-lane block and of the adjacent one, added
+template <int B>
+__device__ __forceinline__ double add_block(double v)
+{
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    if constexpr (B == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ double wave_tree_spread(const double (&v)[N])
+{
+    static_assert(N == 4 || N == 8, "values");
+    const int lane = threadIdx.x & 63;
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0, b2 = (lane & 4) != 0;
+    double w[N / 2], u[N / 4];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i)
+        w[i] = sel_d(b0, v[2 * i + 1], v[2 * i]) + dpp_d<0xB1, 0xF>(sel_d(b0, v[2 * i], v[2 * i + 1]));
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i)
+        u[i] = sel_d(b1, w[2 * i + 1], w[2 * i]) + dpp_d<0x4E, 0xF>(sel_d(b1, w[2 * i], w[2 * i + 1]));
+    double q = u[0], p = u[0];
+    if constexpr (N == 8) {
+        q = sel_d(b2, u[1], u[0]);
+        p = sel_d(b2, u[0], u[1]);
+    }
+    q = q + __hiloint2double(dpp_xor4(__double2hiint(p)), dpp_xor4(__double2loint(p)));
+    q = q + dpp_d<0x128, 0xF>(q);                                                // row_ror:8
+    return add_block<32>(add_block<16>(q));
+}
+
 // minimum of lo and maximum of hi over the 64 lanes (DPP within rows of 16,
 // then the four rows' results read from lanes 15, 31, 47, 63); exact, in
 // every lane

@@ -86,3 +86,17 @@ def test_streaming_places_and_shapes(tuning):
     p["bulk_rate"] = 0.01
     p["n_solvent"] -= 37
     _same(p, W.random_state(p, 3, species_B_fraction=0.2), 12, 3, tuning)
+
+
+@pytest.mark.parametrize("shift", [(0, 0, 0), (1, -1, 0), (-1, 1, 1), (2, -2, 5)])
+@pytest.mark.parametrize("nc", [1, 2, 3])
+def test_colloid_images_within_and_beyond_a_box_length(nc, shift):
+    """Unwrapped colloid positions in every range of the periodic image, up to
+    the faces, for every variant of the chain by colloid count."""
+    p = W.base_params(L=(15, 14, 16), rho=4, dt=0.01, n_md=8)
+    L = np.array(p["L"], dtype=float)
+    for k, x in enumerate([(0.0, 3.0, 4.0), (7.5, np.nextafter(L[1], 0.0), 8.0), (11.0, 7.0, 13.0)][:nc]):
+        W.add_colloid(p, x, sigma=1.2 + 0.1 * k, catalytic=k % 2)
+    s = W.random_state(p, 21 + nc)
+    s["X"] = np.asarray(s["X"]) + np.array(shift) * L
+    _same(p, s, 8, 3)
