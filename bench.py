@@ -82,7 +82,7 @@ def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
         return n_cand * (12 * tb + 2)
     if kernel == "analysis":
         return n * (3 * tb + 1)
-    if kernel in ("chunk_scan", "cand_write"):
+    if kernel == "close":
         return n * 1 + 8 * math.ceil(n / 1024)
     return 0.0
 

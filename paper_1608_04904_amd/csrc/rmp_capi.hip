@@ -7,7 +7,7 @@
 //
 //   [ k_chain  ||  k_stream ]  (in large launches on a side stream, in small
 //   ones in one launch), k_scan_blocks, k_scan_final, k_perm, k_collide,
-//   k_chunk_scan, k_cand_write
+//   k_close
 //
 // optionally replayed from a captured hipGraph.
 #include "rmp_kernels.hip"
@@ -148,7 +148,7 @@ Sizes sizes_of(const rmp_params* p)
 // offsets of every array inside a replica workspace
 struct Layout {
     size_t cp, rs, rec[2], keyrank, perm, xchg, lbits, count, start, scanblk, axes, bulk, tilemask,
-        chunk_cnt, chunk_off, cand_idx, order, partials, epart, tpart, bigmask, ptable, obs_part, mean, total;
+        chunk_cnt, gpart, done, cand_idx, order, partials, epart, tpart, bigmask, ptable, obs_part, mean, total;
 };
 
 Layout layout_of(const rmp_params* p)
@@ -171,8 +171,10 @@ Layout layout_of(const rmp_params* p)
     L.bulk = take(2 * 8 * (size_t)s.ncell);
     L.tilemask = take(4 * (size_t)s.n_tiles_max);
     L.scanblk = take(4 * (size_t)s.n_scanblk);
-    L.chunk_cnt = take(4 * (size_t)s.n_chunks);
-    L.chunk_off = take(4 * (size_t)s.n_chunks);
+    const size_t n_close = std::max<size_t>(1, ((size_t)s.n_chunks + CLOSE_CH - 1) / CLOSE_CH);
+    L.chunk_cnt = take(2 * 4 * (size_t)s.n_chunks);
+    L.gpart = take(n_close * 4 * 8);
+    L.done = take(32 * 4 * (1 + (n_close + 63) / 64));
     L.cand_idx = take(4 * (size_t)s.cand_cap);
     L.order = take(2 * 4 * (size_t)s.ncell);
     L.partials = take(2 * ((size_t)s.G * ROWW + BCW) * 8);
@@ -192,8 +194,8 @@ size_t ctl_bytes_for(int32_t nslots)
 }
 
 const char* KNAMES[] = {"stream", "chain", "scan_blocks", "scan_final", "perm", "collide",
-                        "chunk_scan", "cand_write", "list", "analysis"};
-enum { KN_STREAM, KN_CHAIN, KN_SCANB, KN_SCANF, KN_PERM, KN_COLLIDE, KN_CHUNKSCAN, KN_CANDW, KN_LIST, KN_ANALYSIS,
+                        "close", "list", "analysis"};
+enum { KN_STREAM, KN_CHAIN, KN_SCANB, KN_SCANF, KN_PERM, KN_COLLIDE, KN_CLOSE, KN_LIST, KN_ANALYSIS,
        KN_COUNT };
 
 struct Replica {
@@ -273,7 +275,7 @@ constexpr size_t RMP_STATIC_SCRATCH_BYTES = RMP_NOALLOC_SCRATCH_BYTES;
 
 namespace {
 
-enum { PF_CHUNK, PF_TILE, PF_SCAN, PF_CHAIN, PF_REP, PF_IDENT };
+enum { PF_CHUNK, PF_TILE, PF_SCAN, PF_CHAIN, PF_REP, PF_CLOSE };
 
 thread_local char g_last_error[256] = "";
 
@@ -539,7 +541,8 @@ void fill_desc(rmp_batch* b, Replica& r)
     D.bulk = (double*)(w + L.bulk);
     D.tilemask = (uint32_t*)(w + L.tilemask);
     D.chunk_cnt = (uint32_t*)(w + L.chunk_cnt);
-    D.chunk_off = (uint32_t*)(w + L.chunk_off);
+    D.gpart = (double*)(w + L.gpart);
+    D.done = (uint32_t*)(w + L.done);
     D.cand_idx = (uint32_t*)(w + L.cand_idx);
     D.rank_of = (const uint32_t*)(w + L.order);
     D.cell_of = (const uint32_t*)(w + L.order) + s.ncell;
@@ -701,12 +704,13 @@ rmp_status sync_ctl(rmp_batch* b)
     b->n_total = 0;
     for (int r = 0; r < S; ++r) {
         Replica& R = b->reps[r];
-        int items[6] = {0, 0, 0, 0, 1, 1};
+        int items[6] = {0, 0, 0, 0, 1, 0};
         if (R.used) {
             fill_desc(b, R);
             items[PF_CHUNK] = R.desc.n_chunks;
             items[PF_TILE] = R.desc.n_tiles;
             items[PF_SCAN] = R.desc.n_scanblk;
+            items[PF_CLOSE] = std::max(1, (R.desc.n_chunks + CLOSE_CH - 1) / CLOSE_CH);
             items[PF_CHAIN] = R.desc.G;
             b->have_rule[R.p.rule][R.desc.dense ? 1 : R.desc.flow ? 2 : 0] = true;
             if (R.desc.n_scanblk > 1) b->multi_scan = true;
@@ -868,12 +872,8 @@ rmp_status launch_list(rmp_batch* b)
         hipLaunchKernelGGL((k_list<T>), dim3(b->totals[PF_CHUNK]), dim3(256), 0, s, work(b, PF_CHUNK));
     }
     {
-        Timer tm(b, KN_CHUNKSCAN, s);
-        hipLaunchKernelGGL(k_chunk_scan, dim3(b->nslots), dim3(1024), 0, s, work(b, PF_IDENT), 0);
-    }
-    {
-        Timer tm(b, KN_CANDW, s);
-        hipLaunchKernelGGL((k_cand_write<T>), dim3(b->totals[PF_CHUNK]), dim3(256), 0, s, work(b, PF_CHUNK));
+        Timer tm(b, KN_CLOSE, s);
+        hipLaunchKernelGGL((k_close<T>), dim3(b->totals[PF_CLOSE]), dim3(1024), 0, s, work(b, PF_CLOSE), 0);
     }
     return last_launch("list build");
 }
@@ -893,27 +893,19 @@ void launch_collide_rule(rmp_batch* b, hipStream_t s)
 #undef RMP_COLLIDE
 }
 
-// every collision launch is followed by the pass over the cells beyond a
-// group's capacity (tiles without any such cell cost one mask load each)
-template <class T>
-void launch_collide(rmp_batch* b, hipStream_t s, int rule)
+// the workgroup form is followed by the pass over the cells beyond a group's
+// capacity (tiles without any such cell cost one mask load each)
+template <class T, int RULE>
+void launch_collide(rmp_batch* b, hipStream_t s)
 {
-    const int items = b->totals[PF_TILE];
-    const dim3 gb((unsigned)((items + 63) / 64));
-    if (rule == 0) {
-        if (b->have_rule[0][0]) launch_collide_rule<T, 0, false>(b, s);
-        if (b->have_rule[0][2]) launch_collide_rule<T, 0, true>(b, s);
-        if (b->have_rule[0][1])
-            hipLaunchKernelGGL((k_collide_dense<T, 0, 256, 2>), dim3(items), dim3(256), 0, s, work(b, PF_TILE),
-                               b->tun.collide_xcd);
-        hipLaunchKernelGGL((k_collide_big<T, 0>), gb, dim3(256), 0, s, work(b, PF_TILE), items);
-    } else {
-        if (b->have_rule[1][0]) launch_collide_rule<T, 1, false>(b, s);
-        if (b->have_rule[1][2]) launch_collide_rule<T, 1, true>(b, s);
-        if (b->have_rule[1][1])
-            hipLaunchKernelGGL((k_collide_dense<T, 1, 256, 2>), dim3(items), dim3(256), 0, s, work(b, PF_TILE),
-                               b->tun.collide_xcd);
-        hipLaunchKernelGGL((k_collide_big<T, 1>), gb, dim3(256), 0, s, work(b, PF_TILE), items);
+    if (b->have_rule[RULE][0]) launch_collide_rule<T, RULE, false>(b, s);
+    if (b->have_rule[RULE][2]) launch_collide_rule<T, RULE, true>(b, s);
+    if (b->have_rule[RULE][1]) {
+        const int items = b->totals[PF_TILE];
+        hipLaunchKernelGGL((k_collide_dense<T, RULE, 256, 2>), dim3(items), dim3(256), 0, s, work(b, PF_TILE),
+                           b->tun.collide_xcd);
+        hipLaunchKernelGGL((k_collide_big<T, RULE>), dim3((unsigned)((items + 63) / 64)), dim3(256), 0, s,
+                           work(b, PF_TILE), items);
     }
 }
 
@@ -958,28 +950,27 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
         Timer tm(b, KN_SCANB, s);
         hipLaunchKernelGGL(k_scan_blocks, dim3(b->totals[PF_SCAN]), dim3(1024), 0, s, work(b, PF_SCAN));
     }
-    {
+    // (grids of one scan block each: k_perm scans them itself)
+    if (b->multi_scan) {
         Timer tm(b, KN_SCANF, s);
         hipLaunchKernelGGL(k_scan_final, dim3(b->totals[PF_SCAN]), dim3(1024), 0, s, work(b, PF_SCAN), direct);
     }
     {
         Timer tm(b, KN_PERM, s);
-        if (ppt == 4) hipLaunchKernelGGL((k_perm<4>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
-        else if (ppt == 2) hipLaunchKernelGGL((k_perm<2>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
-        else hipLaunchKernelGGL((k_perm<1>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        if (!b->multi_scan)
+            hipLaunchKernelGGL((k_perm<2, true>), dim3(nch * 2), dim3(256), 0, s, work(b, PF_CHUNK), 2);
+        else if (ppt == 4) hipLaunchKernelGGL((k_perm<4, false>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        else if (ppt == 2) hipLaunchKernelGGL((k_perm<2, false>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
+        else hipLaunchKernelGGL((k_perm<1, false>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
     }
     {
         Timer tm(b, KN_COLLIDE, s);
-        for (int rule = 0; rule < 2; ++rule)
-            if (b->have_rule[rule][0] || b->have_rule[rule][1] || b->have_rule[rule][2]) launch_collide<T>(b, s, rule);
+        launch_collide<T, 0>(b, s);
+        launch_collide<T, 1>(b, s);
     }
     {
-        Timer tm(b, KN_CHUNKSCAN, s);
-        hipLaunchKernelGGL(k_chunk_scan, dim3(b->nslots), dim3(1024), 0, s, work(b, PF_IDENT), 1);
-    }
-    {
-        Timer tm(b, KN_CANDW, s);
-        hipLaunchKernelGGL((k_cand_write<T>), dim3(nch), dim3(256), 0, s, work(b, PF_CHUNK));
+        Timer tm(b, KN_CLOSE, s);
+        hipLaunchKernelGGL((k_close<T>), dim3(b->totals[PF_CLOSE]), dim3(1024), 0, s, work(b, PF_CLOSE), 1);
     }
     if (b->any_analysis) {
         Timer tm(b, KN_ANALYSIS, s);

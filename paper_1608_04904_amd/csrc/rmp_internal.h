@@ -57,10 +57,11 @@ struct RepState {
     int64_t n_cat, n_bulk;
     int64_t list_nmd;          // n_md the current Verlet list was built for (-1: none)
     uint32_t flags;
-    uint32_t bar;              // inter-workgroup barrier counter of the MD chain
+    uint32_t pad;
+    int64_t coll_closing;      // coll_step of the interval under way (k_perm, for k_close)
     double U, e_rxn;
     double T_sum, T_cells;     // temperature estimator of the last collision
-    double shift[3];           // grid shift of the coming collision (k_chunk_scan)
+    double shift[3];           // grid shift of the coming collision (k_close)
     double Xw[MAXC][3];        // periodic images of the colloids at the coming collision (k_perm)
     double X[MAXC][3], V[MAXC][3], F[MAXC][3];
 };
@@ -131,8 +132,9 @@ struct RepDesc {
     uint32_t* scanblk;         // [n_scanblk]
     double* xchg;              // [n] one component of the state, for the exchange with the host
     uint64_t* lbits;           // [16 n_chunks] Verlet-list membership bits; zero outside chunks with members
-    uint32_t* chunk_cnt;       // [n_chunks]
-    uint32_t* chunk_off;       // [n_chunks]
+    uint32_t* chunk_cnt;       // [2][n_chunks] list members per chunk, buffer coll_step & 1 of the collision
+    double* gpart;             // [n_close][4] tile partials summed by workgroup of k_close
+    uint32_t* done;            // [32 (1 + groups of 64 n_close)] its arrivals; zero between launches
     uint32_t* cand_idx;        // [cand_cap]
     const uint32_t* rank_of;   // [ncell] sort rank of a cell (Hilbert order)
     const uint32_t* cell_of;   // [ncell] cell of a sort rank

@@ -23,8 +23,7 @@
 //                  axis (or Anderson thermostat), bulk B->A reaction,
 //                  Verlet-list flags for the next interval, contiguous write
 //                  of the cell-ordered records
-//   k_chunk_scan   list compaction offsets, per-interval bookkeeping
-//   k_cand_write   compacted Verlet list
+//   k_close        compacted Verlet list, per-interval bookkeeping
 //
 // Data layout in HBM: one record per particle (position, velocity, id, state
 // bits; 64 bytes in FP64, 32 in FP32), double-buffered across collisions, so
@@ -170,180 +169,221 @@ __global__ __launch_bounds__(256) void k_list(Work w)
         cnt += c ? 1u : 0u;
     }
     uint32_t tot = block_sum_u32<256>(cnt, sred);
-    if (t == 0) D.chunk_cnt[chunk] = tot;
+    if (t == 0) D.chunk_cnt[(int64_t)((rs->coll_step + 1) & 1) * D.n_chunks + chunk] = tot;
 }
 
-// Per replica (one workgroup each): exclusive scan of the chunk counts of
-// Verlet-list members, list length and capacity check, barrier reset.  When
-// `after_collision` is set it also closes the interval: collision-step
-// counter, temperature of the collision, reaction bookkeeping.
-__global__ __launch_bounds__(1024) void k_chunk_scan(Work w, int after_collision)
+// Closes an interval (after_collision), or a stand-alone list build: the
+// compacted Verlet list in array order, and per replica the list length and
+// capacity check and, after a collision, the collision-step counter, the
+// temperature, the reaction bookkeeping and the next grid shift.  One
+// workgroup takes CLOSE_CH chunks, a wave each, and sums the counts of the
+// chunks before them itself (where there are many chunks, only if its own have
+// members: few do, the list gathers around the colloids), so no scan goes
+// before.  Latency bounds it: what does not depend on the counts is loaded at
+// the start.  With up to CLOSE_DIRECT workgroups the first one does the
+// bookkeeping; with more, each sums its share of the tiles' partials and the
+// last to arrive combines the shares in order; what it and the others exchange
+// goes through atomics at device scope.  The counts are double-buffered by
+// collision, since workgroups read each other's: this launch clears the ones
+// the next collision adds to.  (A scan by one workgroup and a launch that
+// wrote the list after it: 60 + 9 us at 128^3, 10 + 6 at 32^3; now 40 and 12.)
+constexpr int CLOSE_CH = CHUNK / 64;         // chunks per workgroup
+constexpr int CLOSE_DIRECT = 64;             // (its chunks: one per thread of a workgroup)
+
+template <class T>
+__global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
 {
-    const int rep = blockIdx.x;
+    static_assert(CLOSE_CH == 16 && CHUNK == 1024, "a wave per chunk, 16 particles per lane");
+    const int rep = find_rep(w.prefix, w.nrep, blockIdx.x);
+    const int b = (int)blockIdx.x - w.prefix[rep];
     const RepDesc& D = w.desc[rep];
     if (!D.active) return;
     RepState* rs = D.rs;
     if (!after_collision && list_is_valid(D, rs)) return;
-    __shared__ uint32_t sbuf[16];
+    __shared__ uint32_t sbuf[16], s_sum[16][2], s_cnt[16];
     __shared__ double dbuf[17 * 6];
-    const int t = threadIdx.x;
+    __shared__ int s_last;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int nch = D.n_chunks;
-    const int per = (nch + 1023) / 1024;
-    const gptr<const uint32_t> cnt = G(D.chunk_cnt);
-    const gptr<uint32_t> off = G(D.chunk_off);
-    // a single workgroup walks all chunks: latency, not bandwidth, bounds
-    // this, so each thread's counts (up to CS_REG of them) are loaded at
-    // once and kept for the second pass; more are read in batches, twice
-    constexpr int CS_REG = 32, UB = 4;
-    const int q0 = t * per;
-    uint32_t c[CS_REG];
-    uint32_t local = 0;
-    if (per <= CS_REG) {
-#pragma unroll
-        for (int u = 0; u < CS_REG; ++u) c[u] = (u < per && q0 + u < nch) ? cnt[q0 + u] : 0u;
-#pragma unroll
-        for (int u = 0; u < CS_REG; ++u) local += c[u];
-    } else {
-        int kk = 0;
-        for (; kk + UB <= per; kk += UB) {
-            uint32_t b[UB];
-#pragma unroll
-            for (int u = 0; u < UB; ++u) b[u] = q0 + kk + u < nch ? cnt[q0 + kk + u] : 0u;
-#pragma unroll
-            for (int u = 0; u < UB; ++u) local += b[u];
-        }
-        for (; kk < per; ++kk)
-            if (q0 + kk < nch) local += cnt[q0 + kk];
+    const int nb = w.prefix[rep + 1] - w.prefix[rep];
+    const bool counted = !after_collision || nb > CLOSE_DIRECT;
+    // (coll_closing: the first workgroup may advance coll_step meanwhile)
+    const int64_t coll = after_collision ? rs->coll_closing + 1 : rs->coll_step;
+    const gptr<uint32_t> cnt = G(D.chunk_cnt) + (int64_t)((coll + 1) & 1) * nch;   // (the finished collision's parity)
+    const gptr<uint32_t> nxt = G(D.chunk_cnt) + (int64_t)(coll & 1) * nch;
+    const int c0 = b * CLOSE_CH;
+    const int chunk = c0 + wave;
+    const gptr<uint64_t> bits = G(D.lbits) + (int64_t)chunk * (CHUNK / 64);
+    const uint64_t word = chunk < nch ? bits[lane >> 2] : 0ull;
+    const uint32_t mine = chunk < nch ? cnt[chunk] : 0u;
+    uint32_t pre = 0, total = 0;
+    if (!counted) {
+        total = t < nch ? cnt[t] : 0u;
+        pre = t < c0 ? total : 0u;
     }
-    uint32_t total;
-    uint32_t pre = block_exscan_u32<1024>(local, sbuf, &total);
-    if (per <= CS_REG) {
+    // the tiles' partials: all of them, or this workgroup's share
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int64_t o_bulk = 0, o_cat = 0;
+    double o_rxn = 0.0;
+    if (after_collision && (counted || b == 0)) {
+        const gptr<const double> tp = G((const double*)D.tpart);
+        const int t0 = counted ? (int)((int64_t)D.n_tiles * b / nb) : 0;
+        const int t1 = counted ? (int)((int64_t)D.n_tiles * (b + 1) / nb) : D.n_tiles;
+        for (int k = t0 + t; k < t1; k += 1024)
 #pragma unroll
-        for (int u = 0; u < CS_REG; ++u) {
-            if (u < per && q0 + u < nch) off[q0 + u] = pre;
-            pre += c[u];
-        }
-    } else {
-        int kk = 0;
-        for (; kk + UB <= per; kk += UB) {
-            uint32_t b[UB];
-#pragma unroll
-            for (int u = 0; u < UB; ++u) b[u] = q0 + kk + u < nch ? cnt[q0 + kk + u] : 0u;
-#pragma unroll
-            for (int u = 0; u < UB; ++u) {
-                if (q0 + kk + u < nch) off[q0 + kk + u] = pre;
-                pre += b[u];
-            }
-        }
-        for (; kk < per; ++kk) {
-            const int q = q0 + kk;
-            if (q < nch) {
-                off[q] = pre;
-                pre += cnt[q];
-            }
-        }
-    }
-    if (after_collision) {
-        // tile partials (temperature sum and cells, reaction energy, bulk
-        // flips): eight 32-byte loads in flight per round into two
-        // accumulators; the order is fixed for a given tile count
-        double a[2][4] = {};
-        const gptr<const double> tp = G(D.tpart);
-        constexpr int TL = 8;
-        int k = t;
-        for (; k + (TL - 1) * 1024 < D.n_tiles; k += TL * 1024) {
-            double q[TL][4];
-#pragma unroll
-            for (int j = 0; j < TL; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) q[j][e] = tp[(int64_t)(k + j * 1024) * 4 + e];
-#pragma unroll
-            for (int j = 0; j < TL; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a[j & 1][e] += q[j][e];
-        }
-        for (; k < D.n_tiles; k += 1024)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[0][e] += tp[(int64_t)k * 4 + e];
-        double v[6];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = a[0][j] + a[1][j];
-        v[4] = 0.0;
-        v[5] = 0.0;
+            for (int e = 0; e < 4; ++e) v[e] += tp[(int64_t)k * 4 + e];
         for (int g = t; g < D.G; g += 1024) {
             v[4] += D.epart[(int64_t)g * 2 + 0];
             v[5] += D.epart[(int64_t)g * 2 + 1];
+        }
+        o_rxn = rs->e_rxn;
+        o_bulk = rs->n_bulk;
+        o_cat = rs->n_cat;
+    }
+    double shift[3];
+    if (t == 1023 && (counted || b == 0)) shift_of(D.seed, coll, shift);
+    if (lane == 0) {
+        s_cnt[wave] = mine;
+        if (chunk < nch) nxt[chunk] = 0u;
+    }
+    if (__syncthreads_or(mine != 0u || !counted)) {
+        if (counted) {
+            for (int k = t; k < c0; k += 4 * 1024) {
+                uint32_t q[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) q[u] = k + u * 1024 < c0 ? cnt[k + u * 1024] : 0u;
+                pre += (q[0] + q[1]) + (q[2] + q[3]);
+            }
+            pre = block_sum_u32<1024>(pre, sbuf);
+        } else {
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                pre += __shfl_xor(pre, m, 64);
+                total += __shfl_xor(total, m, 64);
+            }
+            if (lane == 0) {
+                s_sum[wave][0] = pre;
+                s_sum[wave][1] = total;
+            }
+            __syncthreads();
+            pre = total = 0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                pre += s_sum[k][0];
+                total += s_sum[k][1];
+            }
+        }
+        for (int k = 0; k < wave; ++k) pre += s_cnt[k];
+        if (mine != 0u) {
+            // lane l: particles [16 l, 16 l + 16) of the chunk
+            const int64_t i0 = (int64_t)chunk * CHUNK + lane * 16;
+            uint32_t f = (uint32_t)(word >> ((lane & 3) * 16)) & 0xffffu;
+            uint32_t x = (uint32_t)__popc(f);
+            const uint32_t own = x;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t y = __shfl_up(x, d, 64);
+                x += lane >= d ? y : 0u;
+            }
+            pre += x - own;
+            for (; f; f &= f - 1u) {
+                const int64_t i = i0 + __ffs(f) - 1;
+                if ((int64_t)pre < (int64_t)D.cand_cap) {
+                    D.cand_idx[pre] = (uint32_t)i;
+                } else if (i < D.n) {
+                    // beyond the list capacity (RMP_FLAG_LIST_OVERFLOW is set):
+                    // the particle is streamed freely so that every particle is
+                    // still binned exactly once
+                    Rec<T>* r = recs<T>(D, (int)(coll & 1)) + i;
+                    r->st = r->st & ST_PUBLIC;
+                }
+                pre++;
+            }
+            if (lane < CHUNK / 64) bits[lane] = 0ull;
+        }
+    }
+    if (counted && after_collision) {
+        const double e4 = v[4], e5 = v[5];          // (whole in every workgroup)
+        block_sum_n<1024, 6>(v, dbuf);
+        // the share to the exchange array; the returned old values are waited
+        // for, so that it is there before this workgroup is counted
+        if (t == 0) {
+            unsigned long long z = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                z |= __hip_atomic_exchange((unsigned long long*)D.gpart + (int64_t)b * 4 + e,
+                                           (unsigned long long)__double_as_longlong(v[e]), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            __asm__ __volatile__("" ::"v"((uint32_t)z), "v"((uint32_t)(z >> 32)) : "memory");
+        }
+        v[4] = e4;
+        v[5] = e5;
+    }
+    if (counted) {
+        if (t == 0) {
+            // counted in two levels: many arrivals at one address are serial
+            const int grp = b >> 6, ng = (nb + 63) >> 6;
+            const uint32_t members = (uint32_t)(nb - (grp << 6) < 64 ? nb - (grp << 6) : 64);
+            uint32_t* const done = D.done;
+            bool l = __hip_atomic_fetch_add(done + 32 * (1 + grp), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                     members - 1u;
+            if (l) {
+                __hip_atomic_store(done + 32 * (1 + grp), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                l = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)ng - 1u;
+                if (l) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            s_last = l ? 1 : 0;
+        }
+        __syncthreads();
+        if (s_last == 0) return;
+        for (int k = t; k < nch; k += 4 * 1024) {
+            uint32_t q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = k + u * 1024 < nch ? cnt[k + u * 1024] : 0u;
+            total += (q[0] + q[1]) + (q[2] + q[3]);
+        }
+        total = block_sum_u32<1024>(total, sbuf);
+    } else if (b != 0) {
+        return;
+    }
+    if (after_collision) {
+        if (counted) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = 0.0;
+            for (int k = t; k < nb; k += 1024)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[e] += __longlong_as_double((long long)__hip_atomic_load(
+                        (unsigned long long*)D.gpart + (int64_t)k * 4 + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
+        for (int g = t; g < D.G; g += 1024) {
             D.epart[(int64_t)g * 2 + 0] = 0.0;
             D.epart[(int64_t)g * 2 + 1] = 0.0;
         }
+        __syncthreads();
         block_sum_n<1024, 6>(v, dbuf);
         if (t == 0) {
             rs->T_sum = v[0];
             rs->T_cells = v[1];
-            rs->e_rxn += v[2] + v[4];
-            rs->n_bulk += (int64_t)v[3];
-            rs->n_cat += (int64_t)v[5];
+            rs->e_rxn = o_rxn + (v[2] + v[4]);
+            rs->n_bulk = o_bulk + (int64_t)v[3];
+            rs->n_cat = o_cat + (int64_t)v[5];
         }
-    }
-    if (!after_collision) {
+    } else {
         // a stand-alone list build follows init or set_state, where the step
         // counters may have moved backwards: clear the exchange words so no
         // stale epoch can match
         uint64_t* part = reinterpret_cast<uint64_t*>(D.partials);
         for (int64_t k = t; k < 2 * ((int64_t)D.G * ROWW + BCW); k += 1024) part[k] = 0ull;
     }
-    // (read before thread 0 advances the counter below)
-    const int64_t coll = rs->coll_step + (after_collision ? 1 : 0);
-    __syncthreads();
-    if (t == 64) shift_of(D.seed, coll, rs->shift);
+    if (t == 1023)
+        for (int d = 0; d < 3; ++d) rs->shift[d] = shift[d];
     if (t == 0) {
         rs->coll_step = coll;
         rs->n_cand = total;
         if ((int64_t)total > (int64_t)D.cand_cap) rs->flags |= RMP_FLAG_LIST_OVERFLOW;
-        rs->bar = 0;
         rs->list_nmd = D.n_md;
     }
-}
-
-// Compacted Verlet list in array order.
-template <class T>
-__global__ __launch_bounds__(256) void k_cand_write(Work w)
-{
-    const int item = blockIdx.x;
-    const int rep = find_rep(w.prefix, w.nrep, item);
-    const int chunk = item - w.prefix[rep];
-    const RepDesc& D = w.desc[rep];
-    if (!D.active) return;
-    // most chunks hold no list member (the list gathers around the
-    // colloids): their count is zero already, and so are their bits
-    if (D.chunk_cnt[chunk] == 0u) return;
-    __shared__ uint32_t sbuf[4];
-    const int64_t n = D.n;
-    const int64_t base = (int64_t)chunk * CHUNK;
-    constexpr int PER = CHUNK / 256;
-    static_assert(PER == 4, "sixteen threads share a word of membership bits");
-    const int t = threadIdx.x;
-    const uint32_t f = (uint32_t)(D.lbits[(base >> 6) + (t >> 4)] >> ((t & 15) * PER)) & 15u;
-    uint32_t total;
-    uint32_t pre = block_exscan_u32<256>((uint32_t)__popc(f), sbuf, &total) + D.chunk_off[chunk];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        if ((f >> k) & 1u) {
-            const int64_t i = base + (int64_t)t * PER + k;
-            if ((int64_t)pre < (int64_t)D.cand_cap) {
-                D.cand_idx[pre] = (uint32_t)i;
-            } else if (i < n) {
-                // beyond the list capacity (RMP_FLAG_LIST_OVERFLOW is set):
-                // the particle is streamed freely so that every particle is
-                // still binned exactly once
-                Rec<T>* r = recs<T>(D, (int)(D.rs->coll_step & 1)) + i;
-                r->st = r->st & ST_PUBLIC;
-            }
-            pre++;
-        }
-    }
-    if (t < CHUNK / 64) D.lbits[(base >> 6) + t] = 0ull;
-    if (t == 0) D.chunk_cnt[chunk] = 0;
 }
 
 // ------------------------------------------------------------- cell scan
@@ -495,7 +535,11 @@ __global__ __launch_bounds__(256) void k_stream(Work w, int wg_per_chunk)
 // start[key] + rank.  Thread t of a workgroup holds particles t, t +
 // blockDim.x, ... of its span (PPT of them).  The replica's workgroups share
 // its tiles (colloid masks).
-template <int PPT>
+// `scan` (every grid of the launch has at most SCAN_BLK cells): no scan went
+// before, and each workgroup sums the counts itself into LDS; the replica's
+// first writes the cell starts for the collision.  A launch takes 4.4 us even
+// when it does nothing (10^3 cells: scan and permutation 4.7 + 5.0, now 5.5).
+template <int PPT, bool SCAN>
 __global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
 {
     const int b = xcd_range(blockIdx.x, gridDim.x);
@@ -518,8 +562,37 @@ __global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
         const int64_t i = base + u * (int)blockDim.x + threadIdx.x;
         kr[u] = i < n ? keyrank[i] : 0ull;
     }
+    if constexpr (SCAN) {
+        __shared__ uint32_t s_start[SCAN_BLK];
+        __shared__ uint32_t sbuf[4];
+        const gptr<const uint32_t> count = G((const uint32_t*)D.count);
+        constexpr int PER = SCAN_BLK / 256;
+        const int nc = (int)D.ncell;
+        const int per = (nc + 255) / 256;                 // cells per thread
+        const int q0 = (int)threadIdx.x * per;
+        uint32_t c[PER], loc = 0;
 #pragma unroll
-    for (int u = 0; u < PPT; ++u) slot[u] = (int64_t)start[kr[u] >> 32] + (uint32_t)kr[u];
+        for (int k = 0; k < PER; ++k) c[k] = k < per && q0 + k < nc ? count[q0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) loc += c[k];
+        uint32_t total;
+        uint32_t p = block_exscan_u32<256>(loc, sbuf, &total);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (k < per && q0 + k < nc) {
+                s_start[q0 + k] = p;
+                if (chunk == 0 && sub == 0) D.start[q0 + k] = p;
+            }
+            p += c[k];
+        }
+        if (chunk == 0 && sub == 0 && threadIdx.x == 0) D.start[nc] = total;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) slot[u] = (int64_t)s_start[kr[u] >> 32] + (uint32_t)kr[u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < PPT; ++u) slot[u] = (int64_t)start[kr[u] >> 32] + (uint32_t)kr[u];
+    }
 #pragma unroll
     for (int u = 0; u < PPT; ++u) {
         const int64_t i = base + u * (int)blockDim.x + threadIdx.x;
@@ -527,6 +600,7 @@ __global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
     }
     const Share sh{(int64_t)chunk * wg_per_chunk + sub, (int64_t)D.n_chunks * wg_per_chunk};
     if (threadIdx.x < 64) tile_masks(D, sh.lo(D.n_tiles), sh.hi(D.n_tiles));
+    if (sh.me == 0 && threadIdx.x == 0) D.rs->coll_closing = D.rs->coll_step;
     if (sh.me == 0 && (int)threadIdx.x < D.nc) {
         RepState* rs = D.rs;
         for (int d = 0; d < 3; ++d) rs->Xw[threadIdx.x][d] = colloid_image(rs->X[threadIdx.x][d], D.Ld[d]);
@@ -539,7 +613,7 @@ __global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
 // uniform).  The bits go to their words (the wave's slots touch two at most)
 // and their number to their chunks' counts, one atomic each, only where some
 // slot is a member.  All 64 lanes must call it.
-__device__ __forceinline__ void list_flags(const RepDesc& D, int64_t o0, bool f)
+__device__ __forceinline__ void list_flags(const RepDesc& D, int64_t coll, int64_t o0, bool f)
 {
     const uint64_t m = __ballot(f);
     if (m == 0ull) return;
@@ -548,7 +622,7 @@ __device__ __forceinline__ void list_flags(const RepDesc& D, int64_t o0, bool f)
     if ((threadIdx.x & 63) == 0) {
         const int64_t w0 = o0 >> 6;
         const gptr<uint64_t> bits = G(D.lbits);
-        const gptr<uint32_t> cnt = G(D.chunk_cnt);
+        const gptr<uint32_t> cnt = G(D.chunk_cnt) + (int64_t)(coll & 1) * D.n_chunks;
         if (lo) {
             (void)__hip_atomic_fetch_or(bits + w0, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             g_add(cnt + w0 / (CHUNK / 64), (uint32_t)__popcll(lo));
@@ -700,7 +774,7 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
             for (int d = 0; d < 3; ++d) q->v[d] = vt[d];
             q->st = s | (cnd ? ST_LIST : 0u);
         }
-        list_flags(D, (int64_t)q0 + k0 + (t & ~63), cnd);
+        list_flags(D, coll, (int64_t)q0 + k0 + (t & ~63), cnd);
     }
     __syncthreads();
 }
@@ -769,7 +843,9 @@ __device__ __forceinline__ int cell_of_slot(const uint32_t* s_start, const uint8
 //   E  rotate about the cell's axis, apply the reaction, decide the
 //      Verlet-list membership, write the records (through LDS, four lanes a
 //      record, so that they leave as whole lines).
-// A cell beyond CAP is left to k_collide_big.
+// A cell beyond CAP is left to the end, when the workgroup collides it
+// (collide_big_cell; a launch of its own for these cost 4.4 us an interval
+// even where there are none).
 // Bound by memory: the records once in and once out, 2.8 GB in FP64 for 20.97 M
 // particles, 530 us at the rate of a copy, measured 664 (FP32 426).  Scattering
 // the records into cell order first and reading them back cost 557 + 714.
@@ -793,7 +869,7 @@ struct alignas(16) CollideWave {
 };
 
 template <class T, int RULE, int NT, int PPT, bool FLOW>
-__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 5 : 4) void k_collide(Work w, int xcd_map)
+__global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_collide(Work w, int xcd_map)
 {
     constexpr int CAP = 64 * PPT, NW = NT / 64;
     const int item = xcd_map ? xcd_range(blockIdx.x, gridDim.x) : (int)blockIdx.x;
@@ -842,7 +918,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 5 : 4) void k_collide(Work w, 
 
     double t_sum = 0.0;        // temperature terms of this lane's cells
     int t_cells = 0;           // (uniform)
-    uint64_t big = 0;          // cells left to k_collide_big (uniform)
+    uint64_t big = 0;          // cells beyond a run's capacity (the same in every wave)
     int ga = 0, nrun = 0;
     // this wave's next run: cells [a, a + nrc) of the tile, slots [q0, q0 + ns)
     int a = 0, nrc = 0, ns = 0;
@@ -1124,28 +1200,45 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 5 : 4) void k_collide(Work w, 
                                           (double)xr[u][2], (double)vr[u][0], (double)vr[u][1], (double)vr[u][2]);
                 so[u] |= cnd ? ST_LIST : 0u;
             }
-            list_flags(D, (int64_t)q1 + u * 64, cnd);
+            list_flags(D, coll, (int64_t)q1 + u * 64, cnd);
         }
         records_out<T, PPT>(reinterpret_cast<char*>(&S), dst + (int64_t)q1, n1, xr, vr, idr, so);
     }
     const int lane = lane0;
     // the wave's sums, then the waves in order
     const double red = wave_tree_sum(t_sum);
-    if (t == 0) G(D.bigmask)[tile] = big;
-    if constexpr (NW == 1) {
-        if (lane < 4)
-            G(D.tpart)[(int64_t)tile * 4 + lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
-    } else {
-        __shared__ double s_red[NW][4];
-        if (lane < 4) s_red[wave][lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
-        __syncthreads();
-        if (t < 4) {
-            double s = 0.0;
+    __shared__ double s_red[NW][4];
+    if (lane < 4) s_red[wave][lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
+    if constexpr (NW > 1) __syncthreads();
+    else wave_sync();
+    double part = 0.0;
+    if (t < 4)
 #pragma unroll
-            for (int q = 0; q < NW; ++q) s = s + s_red[q][t];
-            G(D.tpart)[(int64_t)tile * 4 + t] = s;
+        for (int q = 0; q < NW; ++q) part = part + s_red[q][t];
+    if (big != 0ull) {
+        // cells beyond a run's capacity, one after the other, by the workgroup
+        // (their temperature, reaction energy and flips after the others')
+        __shared__ double s_bu[3], s_bn[3], s_bred[(NT / 64 + 1) * 4];
+        __shared__ int32_t s_bflip;
+        double b_sum = 0.0, b_cells = 0.0, b_du = 0.0, b_flip = 0.0;
+        for (uint64_t m = big; m; m &= m - 1) {
+            const int k = __ffsll((long long)m) - 1;
+            const int64_t cell = D.hbits == KEY_ROW ? c0 + k : D.cell_of[c0 + k];
+            const uint32_t q0b = D.start[c0 + k];
+            const int nn = (int)(D.start[c0 + k + 1] - q0b);
+            if (RULE == 0 && t == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_bn);
+            __syncthreads();
+            collide_big_cell<T, RULE, NT>(D, cp, nc, Xw, coll, cell, q0b, nn, s_bu, s_bn, &s_bflip, b_sum, b_cells,
+                                          b_du, b_flip);
         }
+        double br[4] = {b_sum, b_cells, b_du, b_flip};
+        block_sum_n<NT, 4>(br, s_bred);
+        if (t == 0)
+            for (int j = 0; j < 4; ++j) s_red[0][j] = br[j];
+        __syncthreads();
+        if (t < 4) part = part + s_red[0][t];
     }
+    if (t < 4) G(D.tpart)[(int64_t)tile * 4 + t] = part;
 }
 
 // The same collision for dense systems (more than DENSE_RHO particles per
@@ -1433,7 +1526,7 @@ __global__ __launch_bounds__(NT, RULE ? 3 : 4) void k_collide_dense(Work w, int 
                                           (double)vo[0], (double)vo[1], (double)vo[2]);
                 rec_store<T, RecWords<T>::W>(dst + ((int64_t)q0 + sl), xo, vo, s_id[sl], s | (cnd ? ST_LIST : 0u));
             }
-            list_flags(D, (int64_t)q0 + u * NT + (t & ~63), cnd);
+            list_flags(D, coll, (int64_t)q0 + u * NT + (t & ~63), cnd);
         }
         // the potential change of a flipped particle, in the same order per
         // thread, after the writes: inside their loop its colloid loop
@@ -1501,7 +1594,7 @@ __global__ __launch_bounds__(256) void k_collide_big(Work w, int n_items)
         if (item < n_items) {
             const int rep = find_rep(w.prefix, w.nrep, item);
             const RepDesc& D = w.desc[rep];
-            if (D.active && D.rule == RULE) m = D.bigmask[item - w.prefix[rep]];
+            if (D.active && D.rule == RULE && D.dense) m = D.bigmask[item - w.prefix[rep]];
         }
         s_mask[t] = m;
         any = m != 0;
@@ -1802,7 +1895,7 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_init<T>(const RepDesc*);                          \
     template __global__ void k_init_sub<T>(const RepDesc*, const double*);       \
     template __global__ void k_list<T>(Work);                                    \
-    template __global__ void k_cand_write<T>(Work);                              \
+    template __global__ void k_close<T>(Work, int);                              \
     template __global__ void k_stream<T, 1, false>(Work, int);                   \
     template __global__ void k_stream<T, 2, false>(Work, int);                   \
     template __global__ void k_stream<T, 4, false>(Work, int);                   \
@@ -1840,9 +1933,10 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_observe<T>(Work, double*);                     \
     template __global__ void k_analysis<T>(Work);
 
-template __global__ void k_perm<1>(Work, int);
-template __global__ void k_perm<2>(Work, int);
-template __global__ void k_perm<4>(Work, int);
+template __global__ void k_perm<2, true>(Work, int);
+template __global__ void k_perm<1, false>(Work, int);
+template __global__ void k_perm<2, false>(Work, int);
+template __global__ void k_perm<4, false>(Work, int);
 RMP_INST(double)
 RMP_INST(float)
 

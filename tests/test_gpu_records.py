@@ -47,6 +47,8 @@ def _same(p, state, n_md, n_coll, tuning=None):
     ((33, 9, 5), 0.3),    # runs bounded by their cells
     ((65, 3, 3), 2),
     ((3, 5, 67), 5),
+    ((16, 16, 16), 3),    # the largest grid that the permutation scans itself
+    ((17, 16, 16), 3),
 ])
 def test_densities_and_ragged_boxes(L, rho):
     p = W.base_params(L=L, rho=rho, dt=0.02, n_md=6)
