@@ -219,6 +219,8 @@ struct Replica {
 
 }  // namespace
 
+constexpr int OBS_HOST_CHUNKS = 1024;    // observations of up to this many chunks go to pinned memory
+
 struct rmp_batch {
     int32_t nslots = 0;
     int32_t precision = 64;
@@ -230,6 +232,8 @@ struct rmp_batch {
     RepDesc* d_desc = nullptr;
     int32_t* d_prefix[6] = {};
     uint32_t* d_tick = nullptr;     // chain work-list tickets (two counters)
+    int n_obs = 0;                  // observations without it so far
+    char* hobs = nullptr;           // pinned: observation partials of OBS_HOST_CHUNKS chunks, then a state
     int32_t chain_resident[2][5] = {}; // chain workgroups the device holds at once, per shape:
                                        // generic variant, one- or two-colloid variant
     int32_t nc_common = -1;         // colloid count shared by every occupied slot, -1 if mixed
@@ -1167,6 +1171,8 @@ void batch_release(rmp_batch* b)
     for (auto e : b->ev) (void)hipEventDestroy(e);
     if (b->fork) (void)hipEventDestroy(b->fork);
     if (b->join) (void)hipEventDestroy(b->join);
+    if (b->hobs) (void)hipHostFree(b->hobs);
+    b->hobs = nullptr;
     if (b->side) (void)hipStreamDestroy(b->side);
     if (b->capture) (void)hipStreamDestroy(b->capture);
     b->gexec = nullptr; b->graph = nullptr; b->fork = b->join = nullptr; b->side = nullptr; 
@@ -1200,8 +1206,22 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
     w.nrep = 1;
     w.flags = 0;
     w.budget = barrier_budget(b);
-    double* part = scr ? (double*)scr : nullptr;
-    hipLaunchKernelGGL((k_observe<T>), dim3(cnt), dim3(256), 0, s, w, part);
+    // small systems: the kernel writes the partials and the state to pinned
+    // host memory, and the call waits for it alone (two copies to pageable
+    // memory after it: 40 us a call at 10^3, now 18)
+    bool direct = !scr && cnt <= OBS_HOST_CHUNKS;
+    if (direct && !b->hobs) {
+        // from the second observation on (allocating it takes longer than one)
+        direct = b->n_obs++ > 0 && hipHostMalloc((void**)&b->hobs, OBS_HOST_CHUNKS * 64 + sizeof(RepState),
+                                                 hipHostMallocDefault) == hipSuccess;
+        if (!direct) {
+            (void)hipGetLastError();
+            b->hobs = nullptr;
+        }
+    }
+    double* part = scr ? (double*)scr : direct ? (double*)b->hobs : nullptr;
+    RepState* state = direct ? (RepState*)(b->hobs + OBS_HOST_CHUNKS * 64) : nullptr;
+    hipLaunchKernelGGL((k_observe<T>), dim3(cnt), dim3(256), 0, s, w, part, state);
     st = last_launch("k_observe");
     if (st != RMP_OK) return st;
     double P[3] = {0, 0, 0}, ke = 0, nb = 0;
@@ -1216,6 +1236,14 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
         HIPCHK(hipMemcpyAsync(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         P[0] = t[0]; P[1] = t[1]; P[2] = t[2]; ke = t[3]; nb = t[4];
+    } else if (direct) {
+        HIPCHK(hipStreamSynchronize(s));
+        for (int k = 0; k < cnt; ++k) {
+            for (int d = 0; d < 3; ++d) P[d] += part[(size_t)k * 8 + d];
+            ke += part[(size_t)k * 8 + 3];
+            nb += part[(size_t)k * 8 + 4];
+        }
+        std::memcpy(&rs, state, sizeof(rs));
     } else {
         std::vector<double> hpart((size_t)cnt * 8);
         HIPCHK(hipMemcpyAsync(hpart.data(), R.ws + R.lay.obs_part, part_bytes, hipMemcpyDeviceToHost, s));
@@ -1258,9 +1286,13 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
     return rs.flags ? RMP_EDEVICE : RMP_OK;
 }
 
-// The state is exchanged field by field: a kernel splits one field off the
-// records into the workspace's exchange array (or merges it in), a plain copy
-// moves it from or to the caller's buffer.
+// The state is exchanged as contiguous arrays: a kernel splits them off the
+// records into the record buffer that holds no state (or merges them in), plain
+// copies move them from or to the caller's buffers.  An FP32 record has room
+// for three doubles at a time.
+template <class T> constexpr int exchange_passes() { return sizeof(T) == 8 ? 1 : 2; }
+template <class T> constexpr int exchange_pass(int pass) { return sizeof(T) == 8 ? 7 : pass == 0 ? 5 : 2; }
+
 template <class T>
 rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
 {
@@ -1273,16 +1305,19 @@ rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));
     const int cur = (int)(rs.coll_step & 1);
     const int64_t n = R.sz.n;
-    for (int f = 0; f < 8 && n > 0; ++f) {
-        char* to = f < 3 ? (char*)dst->x : f < 6 ? (char*)dst->v : f == 6 ? (char*)dst->id : (char*)dst->state;
-        if (!to) continue;
-        const size_t w = f < 6 ? 8 : f == 6 ? 4 : 1;
-        hipLaunchKernelGGL((k_field_out<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (const RepDesc*)(b->d_desc + slot), cur, f);
-        st = last_launch("k_field_out");
+    for (int pass = 0; pass < exchange_passes<T>() && n > 0; ++pass) {
+        const int what = exchange_pass<T>(pass);
+        hipLaunchKernelGGL((k_fields_out<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const RepDesc*)(b->d_desc + slot), cur, what);
+        st = last_launch("k_fields_out");
         if (st != RMP_OK) return st;
-        HIPCHK(hipMemcpyAsync(to + (f < 6 ? (size_t)(f % 3) * n * 8 : 0), R.ws + R.lay.xchg, w * n,
-                              hipMemcpyDeviceToHost, s));
+        const char* from = (const char*)R.desc.rec[cur ^ 1];
+        if ((what & 1) && dst->x) HIPCHK(hipMemcpyAsync(dst->x, from, 24 * n, hipMemcpyDeviceToHost, s));
+        if (what & 1) from += 24 * n;
+        if ((what & 2) && dst->v) HIPCHK(hipMemcpyAsync(dst->v, from, 24 * n, hipMemcpyDeviceToHost, s));
+        const char* ids = R.ws + R.lay.xchg;
+        if ((what & 4) && dst->id) HIPCHK(hipMemcpyAsync(dst->id, ids, 4 * n, hipMemcpyDeviceToHost, s));
+        if ((what & 4) && dst->state) HIPCHK(hipMemcpyAsync(dst->state, ids + 4 * n, n, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
     }
     for (int c = 0; c < R.p.n_colloids; ++c)
@@ -1365,15 +1400,21 @@ rmp_status set_state_t(rmp_batch* b, int slot, const rmp_host_state* src)
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));
     const int64_t n = R.sz.n;
     const int cur = (int)(src->coll_step & 1);
-    for (int f = 0; f < 8 && n > 0; ++f) {
-        const char* from = f < 3 ? (const char*)src->x : f < 6 ? (const char*)src->v
-                         : f == 6 ? (const char*)src->id : (const char*)src->state;
-        const size_t w = f < 6 ? 8 : f == 6 ? 4 : 1;
-        HIPCHK(hipMemcpyAsync(R.ws + R.lay.xchg, from + (f < 6 ? (size_t)(f % 3) * n * 8 : 0), w * n,
-                              hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL((k_field_in<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (const RepDesc*)(b->d_desc + slot), cur, f);
-        cst = last_launch("k_field_in");
+    for (int pass = 0; pass < exchange_passes<T>() && n > 0; ++pass) {
+        const int what = exchange_pass<T>(pass);
+        char* to = (char*)R.desc.rec[cur ^ 1];
+        if (what & 1) {
+            HIPCHK(hipMemcpyAsync(to, src->x, 24 * n, hipMemcpyHostToDevice, s));
+            to += 24 * n;
+        }
+        if (what & 2) HIPCHK(hipMemcpyAsync(to, src->v, 24 * n, hipMemcpyHostToDevice, s));
+        if (what & 4) {
+            HIPCHK(hipMemcpyAsync(R.ws + R.lay.xchg, src->id, 4 * n, hipMemcpyHostToDevice, s));
+            HIPCHK(hipMemcpyAsync(R.ws + R.lay.xchg + 4 * n, src->state, n, hipMemcpyHostToDevice, s));
+        }
+        hipLaunchKernelGGL((k_fields_in<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           (const RepDesc*)(b->d_desc + slot), cur, what);
+        cst = last_launch("k_fields_in");
         if (cst != RMP_OK) return cst;
         HIPCHK(hipStreamSynchronize(s));
     }

@@ -130,7 +130,7 @@ struct RepDesc {
     uint32_t* count;           // [ncell] particles per cell of the coming collision; zero between intervals
     uint32_t* start;           // [ncell + 1]
     uint32_t* scanblk;         // [n_scanblk]
-    double* xchg;              // [n] one component of the state, for the exchange with the host
+    double* xchg;              // [n] ids and state bytes for the exchange with the host
     uint64_t* lbits;           // [16 n_chunks] Verlet-list membership bits; zero outside chunks with members
     uint32_t* chunk_cnt;       // [2][n_chunks] list members per chunk, buffer coll_step & 1 of the collision
     double* gpart;             // [n_close][4] tile partials summed by workgroup of k_close

@@ -1637,8 +1637,10 @@ __global__ __launch_bounds__(256) void k_collide_big(Work w, int n_items)
 
 // part: where the per-chunk partials go (nullptr: the replica's own
 // workspace region)
+// state: where a copy of the replica's state goes (nullptr: nowhere); part and
+// state may be host memory.
 template <class T>
-__global__ __launch_bounds__(256) void k_observe(Work w, double* part)
+__global__ __launch_bounds__(256) void k_observe(Work w, double* part, RepState* state)
 {
     const int item = blockIdx.x;
     const int rep = find_rep(w.prefix, w.nrep, item);
@@ -1649,6 +1651,11 @@ __global__ __launch_bounds__(256) void k_observe(Work w, double* part)
     const int cur = (int)(D.rs->coll_step & 1);
     const int64_t n = D.n;
     const int64_t base = (int64_t)chunk * CHUNK;
+    if (state && chunk == 0) {
+        static_assert(sizeof(RepState) % 8 == 0, "copied as 64-bit words");
+        for (int k = threadIdx.x; k < (int)(sizeof(RepState) / 8); k += 256)
+            ((uint64_t*)state)[k] = ((const uint64_t*)D.rs)[k];
+    }
     double P0 = 0.0, P1 = 0.0, P2 = 0.0, ke = 0.0, nb = 0.0;
     for (int j = threadIdx.x; j < CHUNK; j += 256) {
         int64_t i = base + j;
@@ -1680,36 +1687,48 @@ __global__ __launch_bounds__(64) void k_observe_total(const double* part, int cn
 }
 
 // --------------------------------------------------- exchange with the host
-// One field of the records of buffer b as a contiguous array: 0..2 position,
-// 3..5 velocity (double, exact from FP32, rounded to it), 6 id, 7 state byte.
+// Fields of the records of buffer b as contiguous arrays, by the bits of
+// `what`: 1 positions, 2 velocities (three arrays of doubles each, exact from
+// FP32, rounded to it), one after the other in the other record buffer, whose
+// contents are spent between intervals; 4 ids, then state bytes, in xchg.
 template <class T>
-__global__ __launch_bounds__(256) void k_field_out(const RepDesc* Dp, int b, int field)
+__global__ __launch_bounds__(256) void k_fields_out(const RepDesc* Dp, int b, int what)
 {
     const RepDesc& D = *Dp;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= D.n) return;
-    const Rec<T>* r = recs<T>(D, b) + i;
-    if (field < 6) D.xchg[i] = (double)(field < 3 ? r->x[field] : r->v[field - 3]);
-    else if (field == 6) reinterpret_cast<uint32_t*>(D.xchg)[i] = r->id;
-    else reinterpret_cast<uint8_t*>(D.xchg)[i] = (uint8_t)(r->st & ST_PUBLIC);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n = D.n;
+    if (i >= n) return;
+    T x[3], v[3];
+    uint32_t id, st;
+    rec_load<T>((gptr<const Rec<T>>)(recs<T>(D, b) + i), x, v, id, st);
+    double* o = reinterpret_cast<double*>(recs<T>(D, b ^ 1)) + i;
+    if (what & 1)
+        for (int d = 0; d < 3; ++d, o += n) *o = (double)x[d];
+    if (what & 2)
+        for (int d = 0; d < 3; ++d, o += n) *o = (double)v[d];
+    if (what & 4) {
+        reinterpret_cast<uint32_t*>(D.xchg)[i] = id;
+        (reinterpret_cast<uint8_t*>(D.xchg) + 4 * n)[i] = (uint8_t)(st & ST_PUBLIC);
+    }
 }
 
 template <class T>
-__global__ __launch_bounds__(256) void k_field_in(const RepDesc* Dp, int b, int field)
+__global__ __launch_bounds__(256) void k_fields_in(const RepDesc* Dp, int b, int what)
 {
     const RepDesc& D = *Dp;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= D.n) return;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, n = D.n;
+    if (i >= n) return;
     Rec<T>* r = recs<T>(D, b) + i;
-    if (field < 3) {
-        const T xt = (T)D.xchg[i];
-        r->x[field] = (double)xt >= D.Ld[field] ? (T)0 : xt;    // FP32 rounding up to L
-    } else if (field < 6) {
-        r->v[field - 3] = (T)D.xchg[i];
-    } else if (field == 6) {
+    const double* o = reinterpret_cast<const double*>(recs<T>(D, b ^ 1)) + i;
+    if (what & 1)
+        for (int d = 0; d < 3; ++d, o += n) {
+            const T xt = (T)*o;
+            r->x[d] = (double)xt >= D.Ld[d] ? (T)0 : xt;    // FP32 rounding up to L
+        }
+    if (what & 2)
+        for (int d = 0; d < 3; ++d, o += n) r->v[d] = (T)*o;
+    if (what & 4) {
         r->id = reinterpret_cast<const uint32_t*>(D.xchg)[i];
-    } else {
-        r->st = reinterpret_cast<const uint8_t*>(D.xchg)[i];
+        r->st = (reinterpret_cast<const uint8_t*>(D.xchg) + 4 * n)[i];
     }
 }
 
@@ -1900,8 +1919,8 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_stream<T, 2, false>(Work, int);                   \
     template __global__ void k_stream<T, 4, false>(Work, int);                   \
     template __global__ void k_stream<T, 1, true>(Work, int);                    \
-    template __global__ void k_field_out<T>(const RepDesc*, int, int);           \
-    template __global__ void k_field_in<T>(const RepDesc*, int, int);            \
+    template __global__ void k_fields_out<T>(const RepDesc*, int, int);          \
+    template __global__ void k_fields_in<T>(const RepDesc*, int, int);           \
     template __global__ void k_collide_big<T, 0>(Work, int);                     \
     template __global__ void k_collide_big<T, 1>(Work, int);                     \
     template __global__ void k_collide<T, 0, 64, 2, false>(Work, int); \
@@ -1930,7 +1949,7 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_collide<T, 1, 512, 1, true>(Work, int); \
     template __global__ void k_collide_dense<T, 0, 256, 2>(Work, int);           \
     template __global__ void k_collide_dense<T, 1, 256, 2>(Work, int);           \
-    template __global__ void k_observe<T>(Work, double*);                     \
+    template __global__ void k_observe<T>(Work, double*, RepState*);                     \
     template __global__ void k_analysis<T>(Work);
 
 template __global__ void k_perm<2, true>(Work, int);
