@@ -383,13 +383,15 @@ struct ChainCtx {
 };
 
 // species_dU for an A -> B flip inside the MD chain, with the colloid
-// constants from LDS (same arithmetic)
+// constants from LDS (same arithmetic); mask: the colloids that the wave's
+// entries can be within cut-off of, so that the others add nothing
 template <class Ctx>
-__device__ __forceinline__ double species_dU_lds(const Ctx& S, const double (*Xw)[3], const ChainConst& cc, int nc,
+__device__ __forceinline__ double species_dU_lds(const Ctx& S, const double (*Xw)[3], const ChainConst& cc, uint32_t mask,
                                                  double x0, double x1, double x2)
 {
     double du = 0.0;
-    for (int c = 0; c < nc; ++c) {
+    for (; mask; mask &= mask - 1u) {
+        const int c = __ffs(mask) - 1;
         double dx = min_image(x0 - Xw[c][0], cc.L(0), cc.h(0));
         double dy = min_image(x1 - Xw[c][1], cc.L(1), cc.h(1));
         double dz = min_image(x2 - Xw[c][2], cc.L(2), cc.h(2));
@@ -476,7 +478,15 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const double 
     // the last pair, of the potential) side by side
     constexpr int CB = 2;
     bool hit_any = false;        // some entry of this wave hit some colloid so far
-    for (int c0 = 0; c0 < nc; c0 += CB) {
+    // pairs with a colloid in reach (bit 2 p: pair p); the others' values are
+    // zero (128^3 with 8 dimers: walking all 16 colloids in every wave, with the
+    // positions awaited behind their flag, 805 us a launch alone, now 633)
+    uint32_t pairs = nc > 2 ? (reach_mask | (reach_mask >> 1)) & 0x55555555u : (nc > 0 ? 1u : 0u);
+    if (nc > 2)
+        for (int k = lane; k < 3 * nc + 1; k += 64) S.sRed[wave][k] = 0.0;
+    while (pairs) {
+        const int c0 = __ffs(pairs) - 1;
+        pairs &= pairs - 1u;
         double tv[8];
         bool hit_chunk = false;  // ... one of this pair of colloids
 #pragma unroll
@@ -535,7 +545,7 @@ __device__ __forceinline__ void chain_compute(ChainCtx<NT, NB>& S, const double 
                 }
             tv[3 * cb + 0] = gx[0]; tv[3 * cb + 1] = gy[0]; tv[3 * cb + 2] = gz[0];
         }
-        const bool last = c0 + CB >= nc;
+        const bool last = pairs == 0u;
         tv[3 * CB] = tv[7] = 0.0;
         if (last) {
             double a[K];
@@ -839,51 +849,54 @@ __device__ __forceinline__ void broadcast_images(ChainCtx<NT, NB>& S, const doub
 }
 
 // Other workgroups: wait (bounded) for the master's positions of the coming
-// MD step into sXw and sFull.  Wave 0: lane 0 polls the flag word, then the
-// wave reads the positions (read again if a word is not yet current).
+// MD step into Xw, and its flag word into sFull.  Wave 0; every lane polls the
+// words it needs.
 template <int NT, int NB>
-__device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, double (*Xw)[3], const ChainConst& cc, int nc, uint32_t nbar,
-                                             uint32_t epoch0)
+__device__ __forceinline__ void await_images(ChainCtx<NT, NB>& S, double (*Xw)[3], const ChainConst& cc, int nc,
+                                             uint32_t nbar, uint32_t epoch0)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t epoch = epoch0 + nbar;
     const gptr<const uint64_t> B = cc.part() + (int64_t)(nbar & 1) * cc.stride() + cc.G() * (int64_t)ROWW;
     const uint64_t t_start = wall_clock64();
     int nap = 0;
-    uint64_t fw = 0;
-    bool gave_up = (__hip_atomic_load(&S.sflags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) &
-                    RMP_FLAG_BARRIER) != 0;
-    while (!gave_up) {
-        __asm__ __volatile__("" ::: "memory");
-        uint64_t f = 0;
-        if (lane == 0) f = __hip_atomic_load(&B[6 * nc], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        fw = __shfl(f, 0, 64);
-        if ((uint32_t)fw == epoch) break;
-        if (wall_clock64() - t_start > cc.budget()) {
-            if (lane == 0) atomicOr(&S.sflags, RMP_FLAG_BARRIER);
-            gave_up = true;
-            break;
-        }
-        if (++nap > 16) __builtin_amdgcn_s_sleep(2);
-    }
-    while (!gave_up) {
+    // value k of the 3 nc: its two words; k = 3 nc: the flag word
+    const int nk = 3 * nc + 1;
+    while (true) {
         // every round loads anew (no load of the words may be carried over
         // from an earlier round)
         __asm__ __volatile__("" ::: "memory");
-        bool good = true;
-        for (int k = lane; k < 3 * nc; k += 64) {
-            const uint64_t lo = __hip_atomic_load(&B[2 * k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t hi = __hip_atomic_load(&B[2 * k + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            good = good && (uint32_t)lo == epoch && (uint32_t)hi == epoch;
-            Xw[k / 3][k % 3] = __hiloint2double((int)(hi >> 32), (int)(lo >> 32));
+        constexpr int KL = (3 * MAXC + 1 + 63) / 64;
+        uint64_t lo[KL], hi[KL];
+#pragma unroll
+        for (int q = 0; q < KL; ++q) {
+            const int k = lane + 64 * q;
+            lo[q] = hi[q] = epoch;
+            if (k < nk) {
+                lo[q] = __hip_atomic_load(&B[2 * k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (k < 3 * nc) hi[q] = __hip_atomic_load(&B[2 * k + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
-        if (__ballot(!good) == 0) break;
-        if (wall_clock64() - t_start > cc.budget()) {
-            if (lane == 0) atomicOr(&S.sflags, RMP_FLAG_BARRIER);
+        bool good = true;
+#pragma unroll
+        for (int q = 0; q < KL; ++q) good = good && (uint32_t)lo[q] == epoch && (uint32_t)hi[q] == epoch;
+        const bool all = __ballot(!good) == 0;
+        const bool late = !all && wall_clock64() - t_start > cc.budget();
+        const bool gave_up = (__hip_atomic_load(&S.sflags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) &
+                              RMP_FLAG_BARRIER) != 0;
+        if (all) {
+#pragma unroll
+            for (int q = 0; q < KL; ++q) {
+                const int k = lane + 64 * q;
+                if (k < 3 * nc) Xw[k / 3][k % 3] = __hiloint2double((int)(hi[q] >> 32), (int)(lo[q] >> 32));
+                else if (k == 3 * nc && (lo[q] >> 32) != 0) S.sFull = 1u;
+            }
             break;
         }
+        if (late && lane == 0) atomicOr(&S.sflags, RMP_FLAG_BARRIER);
+        if (late || gave_up) break;
+        if (++nap > 16) __builtin_amdgcn_s_sleep(2);
     }
-    if (lane == 0 && (fw >> 32) != 0) S.sFull = 1u;
 }
 
 // Wait (bounded) for the exchange words of values v = v0 + vb*vs (vb < VB,
@@ -1337,7 +1350,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
                 if (flip) {
                     st[j] = 1;
                     ef += 1.0;
-                    eu += species_dU_lds(S, Xw, cc, nc, (double)x[j][0], (double)x[j][1], (double)x[j][2]);
+                    eu += species_dU_lds(S, Xw, cc, wmask, (double)x[j][0], (double)x[j][1], (double)x[j][2]);
                 } else {
                     st[j] = 0;
                 }
