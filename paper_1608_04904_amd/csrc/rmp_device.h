@@ -123,11 +123,14 @@ __device__ __forceinline__ void wca(double r2, double sig2, double eps, double& 
     pot = (4.0 * eps) * (((s6 * s6) - s6) + 0.25);
 }
 
-// Marsaglia point on the unit sphere, two tries per Philox block.
+// Marsaglia point on the unit sphere, two tries per Philox block, from the
+// blocks [first, end); false if none of them holds one (the last is then the
+// z axis).
 template <bool ROLL = false>
-__device__ __forceinline__ void marsaglia_axis(uint64_t seed, uint64_t coll, uint64_t cell, double n[3])
+__device__ __forceinline__ bool marsaglia_axis(uint64_t seed, uint64_t coll, uint64_t cell, double n[3],
+                                               uint64_t first = 0, uint64_t end = 64)
 {
-    for (uint64_t sub = 0; sub < 64; ++sub) {
+    for (uint64_t sub = first; sub < end; ++sub) {
         uint64_t w[4];
         philox<ROLL>(coll, cell, sub, seed, TAG_ROT, w);
 #pragma unroll
@@ -140,11 +143,12 @@ __device__ __forceinline__ void marsaglia_axis(uint64_t seed, uint64_t coll, uin
                 n[0] = (2.0 * a) * q;
                 n[1] = (2.0 * b) * q;
                 n[2] = 1.0 - (2.0 * ss);
-                return;
+                return true;
             }
         }
     }
     n[0] = 0.0; n[1] = 0.0; n[2] = 1.0;
+    return false;
 }
 
 // Rodrigues rotation of w by alpha about the unit axis n.

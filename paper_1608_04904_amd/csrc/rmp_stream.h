@@ -82,34 +82,55 @@ __device__ __forceinline__ void rec_store(gptr<Rec<T>> r, const T (&x)[3], const
     for (int k = 0; k < WORDS; ++k) p[k] = q.w[k];
 }
 
-// Per-cell random numbers of the coming collision (sort ranks [lo, hi)):
-// rotation axes (role 0) and bulk-reaction uniforms (role 1), one cell per
-// lane.  Made by k_stream, with every lane at work, because a wave's run of
-// cells in the collision has a dozen only; k_stream waits for its atomics
-// anyway.
-__device__ __forceinline__ void collision_draws(const RepDesc& D, int role, int64_t lo, int64_t hi)
+// Per-cell random numbers of the coming collision, for the block of DRAW_CELLS
+// sort ranks from lo: rotation axes and bulk-reaction uniforms.  Made by
+// k_stream, which waits for its atomics anyway, because a wave's run of cells
+// in the collision has a dozen only.  A Philox block takes 2000 cycles of a
+// wave (64-bit products), so all lanes are kept at work: a workgroup does a
+// whole block of cells, and the 5 % of the axes that both tries of their first
+// Philox block miss are collected and tried again together.  (A share of the
+// cells, 26 or 51, for each workgroup and waves repeating until their last
+// lane had its axis: 128^3 FP64, 689 us for the streaming, now 633; FP32 451,
+// now 410.)
+constexpr int DRAW_CELLS = 256;
+
+__device__ __forceinline__ void collision_draws(const RepDesc& D, int64_t lo)
 {
-    const int lane = threadIdx.x & 63;
-    const RepState* rs = D.rs;
-    const uint64_t coll = (uint64_t)rs->coll_step;
-    if (role == 0 && D.rule == 0) {
-        const gptr<double> axes = G(D.axes);
-        for (int64_t r = lo + lane; r < hi; r += 64) {
-            const uint64_t cell = D.hbits == KEY_ROW ? (uint64_t)r : (uint64_t)G(D.cell_of)[r];
+    __shared__ uint32_t s_nq;
+    __shared__ uint16_t s_q[DRAW_CELLS];
+    const int t = threadIdx.x, bd = (int)blockDim.x;
+    const uint64_t coll = (uint64_t)D.rs->coll_step;
+    const int n = (int)(D.ncell - lo < DRAW_CELLS ? D.ncell - lo : DRAW_CELLS);
+    if (t == 0) s_nq = 0u;
+    __syncthreads();
+    const gptr<double> axes = G(D.axes) + 3 * lo;
+    const gptr<double> bulk = G(D.bulk) + 2 * lo;
+    for (int k = t; k < n; k += bd) {
+        const uint64_t cell = D.hbits == KEY_ROW ? (uint64_t)(lo + k) : (uint64_t)G(D.cell_of)[lo + k];
+        if (D.rule == 0) {
             double a[3];
-            marsaglia_axis<true>(D.seed, coll, cell, a);
-            axes[3 * r] = a[0]; axes[3 * r + 1] = a[1]; axes[3 * r + 2] = a[2];
+            if (marsaglia_axis<true>(D.seed, coll, cell, a, 0, 1)) {
+                axes[3 * k] = a[0]; axes[3 * k + 1] = a[1]; axes[3 * k + 2] = a[2];
+            } else {
+                s_q[atomicAdd(&s_nq, 1u)] = (uint16_t)k;
+            }
         }
-    }
-    if (role == 1 && D.bulk_on) {
-        const gptr<double> bulk = G(D.bulk);
-        for (int64_t r = lo + lane; r < hi; r += 64) {
-            const uint64_t cell = D.hbits == KEY_ROW ? (uint64_t)r : (uint64_t)G(D.cell_of)[r];
+        if (D.bulk_on) {
             uint64_t wv[4];
             philox<true>(coll, cell, 0, D.seed, TAG_BULK, wv);
-            bulk[2 * r] = u01(wv[0]); bulk[2 * r + 1] = u01(wv[1]);
+            bulk[2 * k] = u01(wv[0]); bulk[2 * k + 1] = u01(wv[1]);
         }
     }
+    __syncthreads();
+    const int nq = (int)s_nq;
+    for (int q = t; q < nq; q += bd) {
+        const int k = s_q[q];
+        const uint64_t cell = D.hbits == KEY_ROW ? (uint64_t)(lo + k) : (uint64_t)G(D.cell_of)[lo + k];
+        double a[3];
+        marsaglia_axis<true>(D.seed, coll, cell, a, 1);
+        axes[3 * k] = a[0]; axes[3 * k + 1] = a[1]; axes[3 * k + 2] = a[2];
+    }
+    __syncthreads();
 }
 
 // Share of a replica's work list, cut over its particle workgroups
@@ -121,20 +142,21 @@ struct Share {
 
 // Streaming of the particles outside the Verlet list (flows: of all) over the
 // interval, their cells in the coming collision and their ranks in them (any
-// order: the collision restores the stable one), with one returning atomic per
-// run of equal keys in a wave.  Workgroup `sub` of a chunk covers particles
-// [sub*span, (sub+1)*span) of it, span = blockDim.x * PPT; thread t holds
-// particles t, t + blockDim.x, ... of its span: every load is issued before
-// the drifts, every rank atomic before the first of them is waited for.  The
-// atomics all go to memory, so this kernel keeps many waves (in the
-// collision, at four waves per SIMD, their latency and the drifts showed in
-// full).  A list member's record, which the MD chain on the side stream may be
-// writing meanwhile, is loaded and not used but for the list bit, which stays
-// set.  The replica's workgroups share its cells for the collision's draws.
+// order: the collision restores the stable one).  Workgroup `sub` of a chunk
+// covers particles [sub*span, (sub+1)*span) of it, span = blockDim.x * PPT;
+// thread t holds particles t, t + blockDim.x, ... of its span, and every load
+// is issued before the drifts.  The ranks are counted in LDS first, in a hash
+// table of the workgroup's cell pairs (neighbours in the array go to a few rows
+// of cells), and each pair takes one 64-bit atomic of both its counters: the
+// atomics all go to memory, 0.2 a particle where one per run of equal keys in
+// a wave made 0.5.  A list member's record, which the MD chain may be writing
+// meanwhile, is loaded and not used but for the list bit, which stays set.
 // A wave reads and writes its 64 records through LDS so that each instruction
-// covers a contiguous kilobyte (one lane a record: 783 us where this takes
-// 706, 20.97 M particles in FP64; FP32 489).  Those 2.2 GB need 414 us at the
-// rate of a copy; the rest is the rank atomics (a trial without them 450).
+// covers a contiguous kilobyte (one lane a record: 80 us more).
+// 20.97 M particles, 50 drifts: FP64 633 us, FP32 410.  The records, read whole
+// and half written, are 2.0 and 1.0 GB, 380 and 190 us at the rate of a copy;
+// with one drift instead of 50 it takes 540, and the draws for the cells cost
+// about 30.
 // b: the workgroup's place in the list of particle workgroups.
 template <class T, int PPT, bool FLOW, int NT>
 __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* prefix, int nrep, int b,
@@ -182,12 +204,50 @@ __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* 
     }
     const double s[3] = {uniform_d(G(rs)->shift[0]), uniform_d(G(rs)->shift[1]), uniform_d(G(rs)->shift[2])};
     advance<T, PPT, FLOW>(D, x, v, go);
-    uint32_t key[PPT];
-    RankIssue ri[PPT];
+    // ranks among the workgroup's particles of each cell, by cell pair
+    constexpr int SLOTS = 2 * NT * PPT;              // at most half filled
+    constexpr uint32_t NONE = 0xffffffffu;
+    __shared__ uint32_t s_pair[SLOTS], s_cnt[SLOTS][2];
+    const int nslots = 2 * (int)blockDim.x * PPT;    // of this launch's workgroup size (a power of two)
+    for (int k = threadIdx.x; k < nslots; k += (int)blockDim.x) {
+        s_pair[k] = NONE;
+        s_cnt[k][0] = s_cnt[k][1] = 0u;
+    }
+    __syncthreads();
+    uint32_t key[PPT], rank[PPT];
+    int slot[PPT];
 #pragma unroll
     for (int u = 0; u < PPT; ++u) {
-        key[u] = go[u] ? cell_key<FLOW>(D, (double)x[u][0], (double)x[u][1], (double)x[u][2], s) : 0u;
-        ri[u] = wave_rank_issue(G(D.count), key[u], go[u]);
+        key[u] = rank[u] = 0u;
+        slot[u] = 0;
+        if (go[u]) {
+            key[u] = cell_key<FLOW>(D, (double)x[u][0], (double)x[u][1], (double)x[u][2], s);
+            const uint32_t pair = key[u] >> 1;
+            int q = (int)((pair * 0x9E3779B1u) >> 12) & (nslots - 1);
+            while (true) {
+                const uint32_t old = atomicCAS(&s_pair[q], NONE, pair);
+                if (old == NONE || old == pair) break;
+                q = (q + 1) & (nslots - 1);
+            }
+            slot[u] = q;
+            rank[u] = atomicAdd(&s_cnt[q][key[u] & 1u], 1u);
+        }
+    }
+    __syncthreads();
+    // one 64-bit atomic per cell pair: both cells' counts
+    constexpr int SPT = 2 * PPT;
+    uint64_t got[SPT];
+    bool have[SPT];
+#pragma unroll
+    for (int k = 0; k < SPT; ++k) {
+        const int q = (int)threadIdx.x + k * (int)blockDim.x;
+        const uint32_t pair = s_pair[q];
+        have[k] = pair != NONE;
+        got[k] = 0;
+        if (have[k])
+            got[k] = __hip_atomic_fetch_add((gptr<uint64_t>)G(D.count) + pair,
+                                            (uint64_t)s_cnt[q][0] | ((uint64_t)s_cnt[q][1] << 32), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
     }
 #pragma unroll
     for (int u = 0; u < PPT; ++u) {
@@ -207,14 +267,26 @@ __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* 
             if ((m >> r) & 1ull) p[r * W + part] = buf[lds_word<W>(r, part)];
         }
     }
-    const Share sh{(int64_t)chunk * wg_per_chunk + sub, (int64_t)D.n_chunks * wg_per_chunk};
-    for (int role = threadIdx.x >> 6; role < 2; role += (int)(blockDim.x >> 6))
-        collision_draws(D, role, sh.lo(D.ncell), sh.hi(D.ncell));
+    // the blocks of cells that fall to this workgroup
+    {
+        const int64_t nblk = (D.ncell + DRAW_CELLS - 1) / DRAW_CELLS;
+        const int64_t me = (int64_t)chunk * wg_per_chunk + sub, all = (int64_t)D.n_chunks * wg_per_chunk;
+        for (int64_t j = (me * nblk + all - 1) / all; j < ((me + 1) * nblk + all - 1) / all; ++j)
+            collision_draws(D, j * DRAW_CELLS);
+    }
+    // (a thread rewrites only the counts of its own slots, read above)
+#pragma unroll
+    for (int k = 0; k < SPT; ++k)
+        if (have[k]) {
+            const int q = (int)threadIdx.x + k * (int)blockDim.x;
+            s_cnt[q][0] = (uint32_t)got[k];
+            s_cnt[q][1] = (uint32_t)(got[k] >> 32);
+        }
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < PPT; ++u) {
         const int64_t i = base + u * (int)blockDim.x + threadIdx.x;
-        const uint32_t rank = wave_rank_finish(ri[u]);
-        if (go[u]) G(D.keyrank)[i] = ((uint64_t)key[u] << 32) | rank;
+        if (go[u]) G(D.keyrank)[i] = ((uint64_t)key[u] << 32) | (s_cnt[slot[u]][key[u] & 1u] + rank[u]);
     }
 }
 

@@ -395,40 +395,7 @@ __device__ __forceinline__ Rec<T>* recs(const RepDesc& D, int b)
     return reinterpret_cast<Rec<T>*>(D.rec[b]);
 }
 
-// ------------------------------------------------- free streaming + binning
-
-// Rank of this lane's particle within its cell, with one atomic per run of
-// equal keys in consecutive lanes (particles arrive sorted by the previous
-// collision's cells, so runs are common).  All 64 lanes must call it.
-struct RankIssue {
-    uint32_t base;             // the run head's atomic result (head lanes only)
-    int h;                     // lane of this lane's run head
-};
-
-__device__ __forceinline__ RankIssue wave_rank_issue(gptr<uint32_t> count, uint32_t key, bool valid)
-{
-    const int lane = threadIdx.x & 63;
-    const uint32_t k = valid ? key : 0xffffffffu;
-    const uint32_t prev = __shfl_up(k, 1, 64);
-    const bool head = (lane == 0) || (k != prev);
-    const uint64_t H = __ballot(head);
-    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-    const int h = 63 - __clzll(H & upto);
-    const uint64_t above = (h == 63) ? 0ull : (H & (~0ull << (h + 1)));
-    const int nexth = above ? (__ffsll((long long)above) - 1) : 64;
-    RankIssue r;
-    r.base = 0;
-    r.h = h;
-    if (head && valid)
-        r.base = __hip_atomic_fetch_add(count + key, (uint32_t)(nexth - h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return r;
-}
-
-__device__ __forceinline__ uint32_t wave_rank_finish(const RankIssue& r)
-{
-    const int lane = threadIdx.x & 63;
-    return __shfl(r.base, r.h, 64) + (uint32_t)(lane - r.h);
-}
+// ------------------------------------------------------- free streaming
 
 // One streaming step under the constant acceleration g, with the plates at
 // z = 0 and z = L_z when present: half kick, drift, half kick; a drift that
