@@ -1690,7 +1690,8 @@ __global__ __launch_bounds__(64) void k_observe_total(const double* part, int cn
 // Fields of the records of buffer b as contiguous arrays, by the bits of
 // `what`: 1 positions, 2 velocities (three arrays of doubles each, exact from
 // FP32, rounded to it), one after the other in the other record buffer, whose
-// contents are spent between intervals; 4 ids, then state bytes, in xchg.
+// contents are spent between intervals; 4 ids, then state bytes, in xchg; 8
+// positions and velocities as stored instead of doubles.
 template <class T>
 __global__ __launch_bounds__(256) void k_fields_out(const RepDesc* Dp, int b, int what)
 {
@@ -1700,6 +1701,11 @@ __global__ __launch_bounds__(256) void k_fields_out(const RepDesc* Dp, int b, in
     T x[3], v[3];
     uint32_t id, st;
     rec_load<T>((gptr<const Rec<T>>)(recs<T>(D, b) + i), x, v, id, st);
+    if (what & 8) {
+        T* q = reinterpret_cast<T*>(recs<T>(D, b ^ 1)) + i;
+        for (int d = 0; d < 3; ++d, q += n) *q = x[d];
+        for (int d = 0; d < 3; ++d, q += n) *q = v[d];
+    }
     double* o = reinterpret_cast<double*>(recs<T>(D, b ^ 1)) + i;
     if (what & 1)
         for (int d = 0; d < 3; ++d, o += n) *o = (double)x[d];
