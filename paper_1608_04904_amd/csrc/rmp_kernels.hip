@@ -698,7 +698,23 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
             S1 = S1 + (double)q->v[1];
             S2 = S2 + (double)q->v[2];
         }
-        const double u0 = S0 / (double)nn, u1 = S1 / (double)nn, u2 = S2 / (double)nn;
+        // a cell cut by a plate and under-filled has virtual particles, as in
+        // k_collide, and no temperature
+        bool virt = false;
+        if (D.walls && nn < D.wall_n0) {
+            const int64_t cz = cell / ((int64_t)D.L[0] * D.L[1]);
+            virt = cz == 0 || cz == D.L[2] - 1;
+        }
+        double u0 = S0 / (double)nn, u1 = S1 / (double)nn, u2 = S2 / (double)nn;
+        if (virt) {
+            uint64_t wv[4]; double z[3];
+            philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
+            normals3(wv, z);
+            const double sd = sqrt((double)(D.wall_n0 - nn)) * D.vscale, n0 = (double)D.wall_n0;
+            u0 = (S0 + (sd * z[0])) / n0;
+            u1 = (S1 + (sd * z[1])) / n0;
+            u2 = (S2 + (sd * z[2])) / n0;
+        }
         double tsum = 0.0, G0 = 0.0, G1 = 0.0, G2 = 0.0;
         int nB = 0;
         for (int k = 0; k < nn; ++k) {
@@ -715,8 +731,10 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
                 G2 = G2 + (D.vscale * z[2]);
             }
         }
-        t_sum += (D.mass * tsum) / (double)(nn - 1);
-        t_cells += 1.0;
+        if (!virt) {
+            t_sum += (D.mass * tsum) / (double)(nn - 1);
+            t_cells += 1.0;
+        }
         if (!(isfinite(u0) && isfinite(u1) && isfinite(u2))) atomicOr(&rs->flags, RMP_FLAG_NONFINITE);
         s_u[0] = u0; s_u[1] = u1; s_u[2] = u2;
         if constexpr (RULE == 1) {
