@@ -18,6 +18,10 @@
  *     owned by the library and released by the matching destroy call.
  *   - `stream` is a hipStream_t passed as void*; all device work of a handle
  *     is ordered on that stream.  Calls are asynchronous unless stated.
+ *   - Several host threads may read one handle at once (observables of its
+ *     slots).  A call that changes a handle (step, set_state, slots,
+ *     tuning, profiling, analysis, destroy) runs beside no other call on it.
+ *     Different handles are independent.
  *   - Every call returns an rmp_status and never aborts or throws.  Device
  *     side faults (list overflow, unsound Verlet list, barrier time-out,
  *     non-finite force) are latched in a per-replica flag word and reported

@@ -232,6 +232,9 @@ struct rmp_batch {
     RepDesc* d_desc = nullptr;
     int32_t* d_prefix[6] = {};
     uint32_t* d_tick = nullptr;     // chain work-list tickets (two counters)
+    // several host threads may read a handle at once; what they share on it:
+    std::mutex ctl_mu;              // descriptors and work lists (sync_ctl), event timings
+    std::mutex obs_mu;              // hobs and n_obs: the call that has it uses hobs, the others do without
     int n_obs = 0;                  // observations without it so far
     char* hobs = nullptr;           // pinned: observation partials of OBS_HOST_CHUNKS chunks, then a state
     int32_t chain_resident[2][5] = {}; // chain workgroups the device holds at once, per shape:
@@ -696,6 +699,7 @@ void make_ptable(Replica& r)
 // recompute the work-list prefixes and upload descriptors
 rmp_status sync_ctl(rmp_batch* b)
 {
+    std::lock_guard<std::mutex> guard(b->ctl_mu);
     if (!b->dirty) return RMP_OK;
     const int S = b->nslots;
     for (int k = 0; k < 6; ++k) b->hprefix[k].assign(S + 1, 0);
@@ -1208,8 +1212,10 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
     w.budget = barrier_budget(b);
     // small systems: the kernel writes the partials and the state to pinned
     // host memory, and the call waits for it alone (two copies to pageable
-    // memory after it: 40 us a call at 10^3, now 18)
-    bool direct = !scr && cnt <= OBS_HOST_CHUNKS;
+    // memory after it: 40 us a call at 10^3, now 18); one call at a time, the
+    // other host threads' take the copies
+    std::unique_lock<std::mutex> pinned(b->obs_mu, std::defer_lock);
+    bool direct = !scr && cnt <= OBS_HOST_CHUNKS && pinned.try_lock();
     if (direct && !b->hobs) {
         // from the second observation on (allocating it takes longer than one)
         direct = b->n_obs++ > 0 && hipHostMalloc((void**)&b->hobs, OBS_HOST_CHUNKS * 64 + sizeof(RepState),
@@ -1255,7 +1261,11 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
             nb += hpart[(size_t)k * 8 + 4];
         }
     }
-    if (b->prof) flush_profile(b);
+    if (pinned.owns_lock()) pinned.unlock();
+    if (b->prof) {
+        std::lock_guard<std::mutex> guard(b->ctl_mu);
+        flush_profile(b);
+    }
     std::memset(o, 0, sizeof(*o));
     double kec = 0.0;
     for (int d = 0; d < 3; ++d) o->momentum[d] = R.p.mass * P[d];

@@ -1,0 +1,97 @@
+"""Reads of one handle from several host threads, and observations of every
+size: the partial sums that pass through pinned host memory, those that are
+copied from the workspace, and the allocation-free ones are the same."""
+import threading
+
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _rm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1608_04904_amd as rm
+    return rm
+
+
+def _solvent(L, precision=64, **kw):
+    return W.base_params(L=L, rho=10, dt=0.01, n_md=3, precision=precision, **kw)
+
+
+def _in_threads(fs):
+    err = []
+
+    def run(f):
+        try:
+            f()
+        except BaseException as e:            # noqa: BLE001 (reported below)
+            err.append(e)
+    ts = [threading.Thread(target=run, args=(f,)) for f in fs]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    if err:
+        raise err[0]
+
+
+def test_slots_of_a_batch_observed_by_two_threads():
+    rm = _rm()
+    b = rm.Batch(2, 64)
+    for k, L in enumerate([(20, 20, 20), (23, 20, 20)]):
+        b.set_slot(k, _solvent(L), 5 + k, 3)
+    b.step(1)
+    want = [b.observables(k) for k in range(2)]
+    assert want[0] != want[1]
+    wrong = []
+
+    def read(k):
+        for _ in range(400):
+            if b.observables(k) != want[k]:
+                wrong.append(k)
+    print("[shared] two slots, two threads", flush=True)
+    _in_threads([lambda: read(0), lambda: read(1)])
+    assert not wrong, f"{len(wrong)} of 800 observations were not their slot's"
+    b.close()
+
+
+# 1, 1024 and 1025 chunks of 1024 particles, and the chunks of two slots of
+# very different size
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("n", [1, 1024, 1025, 1 << 20, (1 << 20) + 1, 3 << 20])
+def test_every_way_of_an_observation_agrees(n, precision):
+    rm = _rm()
+    p = _solvent((64, 64, 64), precision)
+    p["n_solvent"] = n
+    g = rm.System(p, 3)
+    g.step(3, 1)
+    print(f"[shared] observations of {n} particles FP{precision}", flush=True)
+    first, second, third = g.observables(), g.observables(), g.observables()
+    assert first == second == third == g.observables_noalloc()
+    g.step(3, 1)
+    assert g.observables() == g.observables_noalloc() != first
+    g.close()
+
+
+def test_slots_of_different_size_observed_in_turn():
+    rm = _rm()
+    b = rm.Batch(3, 64)
+    sizes = [2000, (1 << 20) + 5000, 300_000]
+    alone = []
+    for k, n in enumerate(sizes):
+        p = _solvent((48, 48, 48))
+        p["n_solvent"] = n
+        b.set_slot(k, p, 9 + k, 3)
+        g = rm.System(p, 9 + k)
+        g.step(3, 2)
+        alone.append(g.observables())
+        g.close()
+    b.step(2)
+    for _ in range(3):
+        for k in (0, 1, 2, 1, 0):
+            assert b.observables(k) == alone[k], k
+    b.close()
