@@ -19,7 +19,7 @@
  *   - `stream` is a hipStream_t passed as void*; all device work of a handle
  *     is ordered on that stream.  Calls are asynchronous unless stated.
  *   - Several host threads may read one handle at once (observables of its
- *     slots).  A call that changes a handle (step, set_state, slots,
+ *     slots, get_state).  A call that changes a handle (step, set_state, slots,
  *     tuning, profiling, analysis, destroy) runs beside no other call on it.
  *     Different handles are independent.
  *   - Every call returns an rmp_status and never aborts or throws.  Device

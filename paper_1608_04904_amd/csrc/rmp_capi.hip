@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -235,6 +236,7 @@ struct rmp_batch {
     // several host threads may read a handle at once; what they share on it:
     std::mutex ctl_mu;              // descriptors and work lists (sync_ctl), event timings
     std::mutex obs_mu;              // hobs and n_obs: the call that has it uses hobs, the others do without
+    std::unique_ptr<std::mutex[]> xchg_mu;  // per slot: the scratch of the state exchange
     int n_obs = 0;                  // observations without it so far
     char* hobs = nullptr;           // pinned: observation partials of OBS_HOST_CHUNKS chunks, then a state
     int32_t chain_resident[2][5] = {}; // chain workgroups the device holds at once, per shape:
@@ -1162,6 +1164,8 @@ rmp_status batch_init(rmp_batch* b, int32_t nslots, int32_t precision, void* ctl
         for (int v = 0; v < 2; ++v)
             for (int q = 0; q < 5; ++q) b->chain_resident[v][q] = std::max(1, per[v][q]) * std::max(1, ncu);
     }
+    b->xchg_mu.reset(new (std::nothrow) std::mutex[nslots]);
+    if (!b->xchg_mu) return RMP_ENOMEM;
     b->reps.assign(nslots, Replica{});
     b->hdesc.assign(nslots, RepDesc{});
     b->dirty = true;
@@ -1299,7 +1303,7 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
 // The state is exchanged as contiguous arrays: a kernel splits them off the
 // records into the record buffer that holds no state (or merges them in), plain
 // copies move them from or to the caller's buffers.  An FP32 record has room
-// for three doubles at a time.
+// for three doubles at a time.  One exchange at a time per slot (xchg_mu).
 constexpr int64_t NARROW_EXCHANGE_N = (int64_t)1 << 19;
 template <class T> constexpr int exchange_passes() { return sizeof(T) == 8 ? 1 : 2; }
 template <class T> constexpr int exchange_pass(int pass) { return sizeof(T) == 8 ? 7 : pass == 0 ? 5 : 2; }
@@ -1311,6 +1315,7 @@ rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
     rmp_status st = sync_ctl(b);
     if (st != RMP_OK) return st;
     hipStream_t s = b->stream;
+    std::lock_guard<std::mutex> guard(b->xchg_mu[slot]);
     HIPCHK(hipStreamSynchronize(s));
     RepState rs;
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));
@@ -1427,6 +1432,7 @@ rmp_status set_state_t(rmp_batch* b, int slot, const rmp_host_state* src)
     cst = sync_ctl(b);
     if (cst != RMP_OK) return cst;
     hipStream_t s = b->stream;
+    std::lock_guard<std::mutex> guard(b->xchg_mu[slot]);
     HIPCHK(hipStreamSynchronize(s));
     RepState rs;
     HIPCHK(hipMemcpy(&rs, R.ws + R.lay.rs, sizeof(rs), hipMemcpyDeviceToHost));

@@ -1,8 +1,10 @@
 """Reads of one handle from several host threads, and observations of every
 size: the partial sums that pass through pinned host memory, those that are
 copied from the workspace, and the allocation-free ones are the same."""
+import ctypes as C
 import threading
 
+import numpy as np
 import pytest
 
 import workloads as W
@@ -57,6 +59,57 @@ def test_slots_of_a_batch_observed_by_two_threads():
     _in_threads([lambda: read(0), lambda: read(1)])
     assert not wrong, f"{len(wrong)} of 800 observations were not their slot's"
     b.close()
+
+
+@pytest.mark.parametrize("L,precision", [((20, 20, 20), 64), ((20, 20, 20), 32), ((38, 38, 37), 32)])
+def test_state_read_by_several_threads(L, precision):
+    """Each thread with host buffers of its own (an FP32 state of more than 2^19
+    particles is exchanged in two passes)."""
+    rm = _rm()
+    p = _solvent(L, precision)
+    g = rm.System(p, 7)
+    g.step(3, 1)
+    want = g.get_state()
+    from paper_1608_04904_amd import _StateBuffers, _capi
+    wrong = []
+
+    def read():
+        buf = _StateBuffers(p["n_solvent"], 0)
+        for _ in range(30):
+            h = buf.host_state()
+            assert _capi.lib().rmp_get_state(g.h, C.byref(h)) == _capi.OK
+            for f in ("x", "v", "id", "state"):
+                if not np.array_equal(getattr(buf, f)[..., ::499], want[f][..., ::499]):
+                    wrong.append(f)
+                    getattr(buf, f)[:] = 0
+    print(f"[shared] state of {p['n_solvent']} particles, FP{precision}, six threads", flush=True)
+    _in_threads([read] * 6)
+    assert not wrong, wrong
+    g.close()
+
+
+@pytest.mark.parametrize("fields", [("x",), ("v",), ("id",), ("state",), ("x", "state"), ()])
+@pytest.mark.parametrize("L,precision", [((9, 8, 7), 64), ((9, 8, 7), 32), ((40, 40, 40), 32)])
+def test_reading_some_fields(L, precision, fields):
+    rm = _rm()
+    p = _solvent(L, precision)
+    g = rm.System(p, 7)
+    g.step(3, 1)
+    want = g.get_state()
+    from paper_1608_04904_amd import _StateBuffers, _capi
+    buf = _StateBuffers(p["n_solvent"], 0)
+    buf.x[:] = buf.v[:] = -1.0
+    buf.id[:] = 7
+    buf.state[:] = 9
+    h = buf.host_state()
+    for f in ("x", "v", "id", "state"):
+        if f not in fields:
+            setattr(h, f, None)
+    assert _capi.lib().rmp_get_state(g.h, C.byref(h)) == _capi.OK
+    for f, untouched in (("x", -1.0), ("v", -1.0), ("id", 7), ("state", 9)):
+        got = getattr(buf, f)
+        assert np.array_equal(got, want[f]) if f in fields else (got == untouched).all(), f
+    g.close()
 
 
 # 1, 1024 and 1025 chunks of 1024 particles, and the chunks of two slots of
