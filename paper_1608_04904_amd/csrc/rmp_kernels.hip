@@ -661,14 +661,45 @@ __device__ __forceinline__ bool is_candidate_masked(const RepDesc& D, const Coll
 
 constexpr int COLL_TCMAX = 64;       // cells per tile at most
 
-// One cell of the tile holding more particles than a collision group (rare:
-// hundreds of particles in one cell).  Its particles go to their output slots
-// in the stable order, found by counting ranks of the old indices; then the
-// per-cell quantities by one thread in that order, then every particle in
-// place.
-template <class T, int RULE, int NT>
+// Sums over k = 0 .. nn - 1, one term after the other, of the M values that
+// fill(k, o) gives: the workgroup puts the terms of `cap` k at a time into buf
+// (M cap doubles of LDS), thread d < M adds those of value d and returns the sum.
+template <int NT, int M, class F>
+__device__ __forceinline__ double ordered_sums(double* buf, int cap, int nn, F fill)
+{
+    const int t = threadIdx.x;
+    double sum = 0.0;
+    for (int k0 = 0; k0 < nn; k0 += cap) {
+        const int n = nn - k0 < cap ? nn - k0 : cap;
+        __syncthreads();                             // (buf is free)
+        for (int k = t; k < n; k += NT) {
+            double o[M];
+            fill(k0 + k, o);
+#pragma unroll
+            for (int d = 0; d < M; ++d) buf[d * cap + k] = o[d];
+        }
+        __syncthreads();
+        if (t < M) {
+            const double* p = buf + t * cap;
+#pragma unroll 8
+            for (int k = 0; k < n; ++k) sum = sum + p[k];
+        }
+    }
+    return sum;
+}
+
+// One cell of the tile holding more particles than a collision group (beyond a
+// wave's 128, in the workgroup form 512).  Its particles go to their output
+// slots in the stable order, found by counting ranks of the old indices; then
+// the sequential sums over them in that order, their terms staged in LDS; then
+// every particle in place.  buf: LDS of 3 cap doubles, cap a multiple of 4.
+// Bound by the comparisons of the ranks and the chains of additions.  (One
+// thread reading the records for the sums, the indices read from memory: 512
+// cells of 200 in 32^3 cells, 711 us an interval, under the thermostat 5920; now
+// 163 and 208.)
+template <class T, int RULE, int NT, bool FLOW>
 __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int nc, const double (*s_Xw)[3],
-                                 int64_t coll, int64_t cell, uint32_t q0, int nn,
+                                 int64_t coll, int64_t cell, uint32_t q0, int nn, double* buf, int cap,
                                  double* s_u, double* s_n, int32_t* s_flip,
                                  double& t_sum, double& t_cells, double& du_sum, double& n_flip)
 {
@@ -681,81 +712,110 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
     const Rec<T>* src = recs<T>(D, cur);
     Rec<T>* rec = recs<T>(D, nxt) + q0;
     const uint32_t* perm = D.perm + q0;
-    for (int j = t; j < nn; j += NT) {
-        const uint32_t pj = perm[j];
-        int r = 0;
-        for (int q = 0; q < nn; ++q) r += perm[q] < pj ? 1 : 0;
-        Rec<T> a = src[pj];
-        a.st &= ST_PUBLIC;
-        rec[r] = a;
+    constexpr int JP = 2;                            // particles a thread ranks at a time
+    uint32_t* ix = reinterpret_cast<uint32_t*>(buf);
+    for (int j0 = 0; j0 < nn; j0 += JP * NT) {
+        uint32_t pj[JP];
+        int r[JP];
+#pragma unroll
+        for (int u = 0; u < JP; ++u) {
+            const int j = j0 + u * NT + t;
+            pj[u] = j < nn ? perm[j] : 0u;
+            r[u] = 0;
+        }
+        for (int k0 = 0; k0 < nn; k0 += 6 * cap) {
+            const int n = nn - k0 < 6 * cap ? nn - k0 : 6 * cap;
+            __syncthreads();                         // (buf is free)
+            for (int k = t; k < ((n + 3) & ~3); k += NT) ix[k] = k < n ? perm[k0 + k] : 0xffffffffu;
+            __syncthreads();
+            for (int k = 0; k < n; k += 4) {
+                const u32x4 q = *reinterpret_cast<const u32x4*>(ix + k);
+#pragma unroll
+                for (int u = 0; u < JP; ++u)
+                    r[u] += (q.x < pj[u] ? 1 : 0) + (q.y < pj[u] ? 1 : 0) + (q.z < pj[u] ? 1 : 0) +
+                            (q.w < pj[u] ? 1 : 0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < JP; ++u)
+            if (j0 + u * NT + t < nn) {
+                Rec<T> a = src[pj[u]];
+                a.st &= ST_PUBLIC;
+                rec[r[u]] = a;
+            }
     }
-    __syncthreads();
-    if (t == 0) {
-        double S0 = 0.0, S1 = 0.0, S2 = 0.0;
-        for (int k = 0; k < nn; ++k) {
-            const Rec<T>* q = &rec[k];
-            S0 = S0 + (double)q->v[0];
-            S1 = S1 + (double)q->v[1];
-            S2 = S2 + (double)q->v[2];
-        }
-        // a cell cut by a plate and under-filled has virtual particles, as in
-        // k_collide, and no temperature
-        bool virt = false;
-        if (D.walls && nn < D.wall_n0) {
-            const int64_t cz = cell / ((int64_t)D.L[0] * D.L[1]);
-            virt = cz == 0 || cz == D.L[2] - 1;
-        }
-        double u0 = S0 / (double)nn, u1 = S1 / (double)nn, u2 = S2 / (double)nn;
-        if (virt) {
+    // a cell cut by a plate and under-filled has virtual particles, as in
+    // k_collide, and no temperature
+    bool virt = false;
+    if (FLOW && D.walls && nn < D.wall_n0) {
+        const int64_t cz = cell / ((int64_t)D.L[0] * D.L[1]);
+        virt = cz == 0 || cz == D.L[2] - 1;
+    }
+    const double S = ordered_sums<NT, 3>(buf, cap, nn, [&](int k, double (&o)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) o[d] = (double)rec[k].v[d];
+    });
+    if (t < 3) {
+        double um = S / (double)nn;
+        if (FLOW && virt) {
             uint64_t wv[4]; double z[3];
             philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
             normals3(wv, z);
-            const double sd = sqrt((double)(D.wall_n0 - nn)) * D.vscale, n0 = (double)D.wall_n0;
-            u0 = (S0 + (sd * z[0])) / n0;
-            u1 = (S1 + (sd * z[1])) / n0;
-            u2 = (S2 + (sd * z[2])) / n0;
+            const double sd = sqrt((double)(D.wall_n0 - nn)) * D.vscale;
+            um = (S + (sd * (t == 0 ? z[0] : t == 1 ? z[1] : z[2]))) / (double)D.wall_n0;
         }
-        double tsum = 0.0, G0 = 0.0, G1 = 0.0, G2 = 0.0;
-        int nB = 0;
-        for (int k = 0; k < nn; ++k) {
-            const Rec<T>* q = &rec[k];
-            double w0 = (double)q->v[0] - u0, w1 = (double)q->v[1] - u1, w2 = (double)q->v[2] - u2;
-            tsum = tsum + dot3(w0, w1, w2, w0, w1, w2);
-            nB += (int)(q->st & 1u);
-            if constexpr (RULE == 1) {
-                uint64_t wv[4]; double z[3];
-                philox<true>((uint64_t)coll, q->id, 0, D.seed, TAG_THERMO, wv);
-                normals3(wv, z);
-                G0 = G0 + (D.vscale * z[0]);
-                G1 = G1 + (D.vscale * z[1]);
-                G2 = G2 + (D.vscale * z[2]);
-            }
-        }
-        if (!virt) {
+        if (!isfinite(um)) atomicOr(&rs->flags, RMP_FLAG_NONFINITE);
+        s_u[t] = um;
+    }
+    __syncthreads();
+    if (!virt) {
+        const double tsum = ordered_sums<NT, 1>(buf, cap, nn, [&](int k, double (&o)[1]) {
+            const double w0 = (double)rec[k].v[0] - s_u[0], w1 = (double)rec[k].v[1] - s_u[1],
+                         w2 = (double)rec[k].v[2] - s_u[2];
+            o[0] = dot3(w0, w1, w2, w0, w1, w2);
+        });
+        if (t == 0) {
             t_sum += (D.mass * tsum) / (double)(nn - 1);
             t_cells += 1.0;
         }
-        if (!(isfinite(u0) && isfinite(u1) && isfinite(u2))) atomicOr(&rs->flags, RMP_FLAG_NONFINITE);
-        s_u[0] = u0; s_u[1] = u1; s_u[2] = u2;
-        if constexpr (RULE == 1) {
-            s_n[0] = G0 / (double)nn; s_n[1] = G1 / (double)nn; s_n[2] = G2 / (double)nn;
-        }
+    }
+    if constexpr (RULE == 1) {
+        const double G = ordered_sums<NT, 3>(buf, cap, nn, [&](int k, double (&o)[3]) {
+            uint64_t wv[4]; double z[3];
+            philox<true>((uint64_t)coll, rec[k].id, 0, D.seed, TAG_THERMO, wv);
+            normals3(wv, z);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) o[d] = D.vscale * z[d];
+        });
+        if (t < 3) s_n[t] = G / (double)nn;
+    }
+    if (t < 64) {
+        // bulk reaction: the jb-th of the nB B particles, 64 particles at a time
         int flipk = -1;
-        if (D.bulk_on && nB > 0) {
-            uint64_t wv[4];
-            philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_BULK, wv);
-            double P = D.ptable[nB < RMP_PTABLE ? nB : RMP_PTABLE - 1];
-            if (u01(wv[0]) < P) {
-                int jb = (int)(u01(wv[1]) * (double)nB);
-                if (jb >= nB) jb = nB - 1;
-                for (int k = 0; k < nn; ++k)
-                    if (rec[k].st & 1u) {
-                        if (jb == 0) { flipk = k; break; }
-                        jb--;
+        if (D.bulk_on) {
+            auto species = [&](int k0) { return __ballot(k0 + t < nn && (rec[k0 + t < nn ? k0 + t : 0].st & 1u) != 0u); };
+            int nB = 0;
+            for (int k0 = 0; k0 < nn; k0 += 64) nB += __popcll(species(k0));
+            if (nB > 0) {
+                uint64_t wv[4];
+                philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_BULK, wv);
+                const double P = D.ptable[nB < RMP_PTABLE ? nB : RMP_PTABLE - 1];
+                if (u01(wv[0]) < P) {
+                    int jb = (int)(u01(wv[1]) * (double)nB);
+                    if (jb >= nB) jb = nB - 1;
+                    for (int k0 = 0; k0 < nn && flipk < 0; k0 += 64) {
+                        uint64_t m = species(k0);
+                        const int c = __popcll(m);
+                        if (jb < c) {
+                            for (; jb > 0; --jb) m &= m - 1ull;
+                            flipk = k0 + __ffsll((long long)m) - 1;
+                        }
+                        jb -= c;
                     }
+                }
             }
         }
-        *s_flip = flipk;
+        if (t == 0) *s_flip = flipk;
     }
     __syncthreads();
     const double u0 = s_u[0], u1 = s_u[1], u2 = s_u[2];
@@ -1238,6 +1298,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
         // (their temperature, reaction energy and flips after the others')
         __shared__ double s_bu[3], s_bn[3], s_bred[(NT / 64 + 1) * 4];
         __shared__ int32_t s_bflip;
+        // (the waves' runs are done: their LDS holds the terms)
+        double* buf = reinterpret_cast<double*>(s_w);
+        constexpr int BIG_CAP = (int)(sizeof(s_w) / 24) & ~3;
         double b_sum = 0.0, b_cells = 0.0, b_du = 0.0, b_flip = 0.0;
         for (uint64_t m = big; m; m &= m - 1) {
             const int k = __ffsll((long long)m) - 1;
@@ -1246,8 +1309,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
             const int nn = (int)(D.start[c0 + k + 1] - q0b);
             if (RULE == 0 && t == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_bn);
             __syncthreads();
-            collide_big_cell<T, RULE, NT>(D, cp, nc, Xw, coll, cell, q0b, nn, s_bu, s_bn, &s_bflip, b_sum, b_cells,
-                                          b_du, b_flip);
+            collide_big_cell<T, RULE, NT, FLOW>(D, cp, nc, Xw, coll, cell, q0b, nn, buf, BIG_CAP, s_bu, s_bn, &s_bflip, b_sum,
+                                          b_cells, b_du, b_flip);
         }
         double br[4] = {b_sum, b_cells, b_du, b_flip};
         block_sum_n<NT, 4>(br, s_bred);
@@ -1604,6 +1667,8 @@ __global__ __launch_bounds__(256) void k_collide_big(Work w, int n_items)
     __shared__ int32_t s_flip;
     __shared__ double s_Xw[MAXC][3];
     __shared__ double sred[(NT / 64 + 1) * 4];
+    constexpr int BIG_CAP = 512;
+    __shared__ __attribute__((aligned(16))) double s_buf[3 * BIG_CAP];
     const int item0 = blockIdx.x * 64;
     bool any = false;
     if (t < 64) {
@@ -1640,7 +1705,7 @@ __global__ __launch_bounds__(256) void k_collide_big(Work w, int n_items)
             const int nn = (int)(D.start[c0 + ga + 1] - q0);
             if (RULE == 0 && t == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_n);
             __syncthreads();
-            collide_big_cell<T, RULE, NT>(D, cp, nc, s_Xw, coll, cell, q0, nn, s_u, s_n, &s_flip,
+            collide_big_cell<T, RULE, NT, true>(D, cp, nc, s_Xw, coll, cell, q0, nn, s_buf, BIG_CAP, s_u, s_n, &s_flip,
                                           t_sum, t_cells, du_sum, n_flip);
         }
         double red[4] = {t_sum, t_cells, du_sum, n_flip};
