@@ -6,8 +6,8 @@
 // launches, for all occupied replicas at once:
 //
 //   [ k_chain  ||  k_stream ]  (in large launches on a side stream, in small
-//   ones in one launch), k_scan_blocks, k_scan_final, k_perm, k_collide,
-//   k_close
+//   ones in one launch), k_scan_blocks, k_scan_final, k_cells (sparse
+//   boxes), k_perm, k_collide, k_close
 //
 // optionally replayed from a captured hipGraph.
 #include "rmp_kernels.hip"
@@ -189,9 +189,11 @@ Layout layout_of(const rmp_params* p)
     return L;
 }
 
+constexpr int N_PREFIX = 7;    // work lists
+
 size_t ctl_bytes_for(int32_t nslots)
 {
-    return aup(sizeof(RepDesc) * (size_t)nslots) + 6 * aup(4 * (size_t)(nslots + 1)) + aup(16);
+    return aup(sizeof(RepDesc) * (size_t)nslots) + N_PREFIX * aup(4 * (size_t)(nslots + 1)) + aup(16);
 }
 
 const char* KNAMES[] = {"stream", "chain", "scan_blocks", "scan_final", "perm", "collide",
@@ -231,7 +233,7 @@ struct rmp_batch {
     hipEvent_t fork = nullptr, join = nullptr;
     char* ctl = nullptr;
     RepDesc* d_desc = nullptr;
-    int32_t* d_prefix[6] = {};
+    int32_t* d_prefix[N_PREFIX] = {};
     uint32_t* d_tick = nullptr;     // chain work-list tickets (two counters)
     // several host threads may read a handle at once; what they share on it:
     std::mutex ctl_mu;              // descriptors and work lists (sync_ctl), event timings
@@ -244,8 +246,8 @@ struct rmp_batch {
     int32_t nc_common = -1;         // colloid count shared by every occupied slot, -1 if mixed
     std::vector<Replica> reps;
     std::vector<RepDesc> hdesc;
-    std::vector<int32_t> hprefix[6];
-    int32_t totals[6] = {};
+    std::vector<int32_t> hprefix[N_PREFIX];
+    int32_t totals[N_PREFIX] = {};
     bool dirty = true;
     bool have_rule[2][3] = {};      // [rule][wave form, dense, flow] among the occupied slots
     bool multi_scan = false;
@@ -284,7 +286,7 @@ constexpr size_t RMP_STATIC_SCRATCH_BYTES = RMP_NOALLOC_SCRATCH_BYTES;
 
 namespace {
 
-enum { PF_CHUNK, PF_TILE, PF_SCAN, PF_CHAIN, PF_REP, PF_CLOSE };
+enum { PF_CHUNK, PF_TILE, PF_SCAN, PF_CHAIN, PF_REP, PF_CLOSE, PF_CELLS };
 
 thread_local char g_last_error[256] = "";
 
@@ -451,6 +453,15 @@ constexpr double DENSE_RHO = 32.0;
 
 bool dense_of(int64_t ncell, int64_t n) { return ncell > 0 && (double)n > DENSE_RHO * (double)ncell; }
 
+// Cells per particle chunk (of 1024) beyond which the per-cell work before a
+// collision (draws, tile masks) is a launch of its own, all cells side by side,
+// and not the particle workgroups': below half a particle per cell these are too
+// few (an interval in us, their work and k_cells: 64^3 cells FP64, 0.02
+// particles per cell 387 and 74, 0.2 110 and 82, 0.4 95 and 85, 1.0 92 and 92, 2.0
+// 95 and 99; 128^3 with a sphere 901 and 312, 424 and 375, 425 and 388, 386 and
+// 391, 495 and 510; 16^3 and 32^3 and FP32 alike)
+constexpr int64_t SPARSE_CELLS = 2048;
+
 // Cells per collision tile: the slot's override, else the batch tuning, else
 // sized so that the mean tile fills TILE_FILL of the workgroup's slots (runs
 // end at whole cells; a tile beyond one run per wave takes another round), in
@@ -499,6 +510,7 @@ void fill_desc(rmp_batch* b, Replica& r)
     D.n_scanblk = s.n_scanblk;
     D.nc = p->n_colloids;
     D.dense = dense_of(s.ncell, s.n) ? 1 : 0;
+    D.sparse = s.ncell > SPARSE_CELLS * s.n_chunks ? 1 : 0;
     D.cand_cap = s.cand_cap;
     const ChainShape cs = chain_shape_of(b);
     const int K = cs.k;
@@ -704,7 +716,7 @@ rmp_status sync_ctl(rmp_batch* b)
     std::lock_guard<std::mutex> guard(b->ctl_mu);
     if (!b->dirty) return RMP_OK;
     const int S = b->nslots;
-    for (int k = 0; k < 6; ++k) b->hprefix[k].assign(S + 1, 0);
+    for (int k = 0; k < N_PREFIX; ++k) b->hprefix[k].assign(S + 1, 0);
     std::memset(b->have_rule, 0, sizeof(b->have_rule));
     b->multi_scan = false;
     b->max_scanblk = 0;
@@ -714,7 +726,7 @@ rmp_status sync_ctl(rmp_batch* b)
     b->n_total = 0;
     for (int r = 0; r < S; ++r) {
         Replica& R = b->reps[r];
-        int items[6] = {0, 0, 0, 0, 1, 0};
+        int items[N_PREFIX] = {0, 0, 0, 0, 1, 0, 0};
         if (R.used) {
             fill_desc(b, R);
             items[PF_CHUNK] = R.desc.n_chunks;
@@ -722,6 +734,7 @@ rmp_status sync_ctl(rmp_batch* b)
             items[PF_SCAN] = R.desc.n_scanblk;
             items[PF_CLOSE] = std::max(1, (R.desc.n_chunks + CLOSE_CH - 1) / CLOSE_CH);
             items[PF_CHAIN] = R.desc.G;
+            if (R.desc.sparse) items[PF_CELLS] = (int)((R.desc.ncell + DRAW_CELLS - 1) / DRAW_CELLS);
             b->have_rule[R.p.rule][R.desc.dense ? 1 : R.desc.flow ? 2 : 0] = true;
             if (R.desc.n_scanblk > 1) b->multi_scan = true;
             b->max_scanblk = std::max(b->max_scanblk, R.desc.n_scanblk);
@@ -735,9 +748,9 @@ rmp_status sync_ctl(rmp_batch* b)
             b->hdesc[r] = RepDesc{};
             b->hdesc[r].active = 0;
         }
-        for (int k = 0; k < 6; ++k) b->hprefix[k][r + 1] = b->hprefix[k][r] + items[k];
+        for (int k = 0; k < N_PREFIX; ++k) b->hprefix[k][r + 1] = b->hprefix[k][r] + items[k];
     }
-    for (int k = 0; k < 6; ++k) b->totals[k] = b->hprefix[k][S];
+    for (int k = 0; k < N_PREFIX; ++k) b->totals[k] = b->hprefix[k][S];
     b->nc_common = -1;
     bool first = true;
     for (int r = 0; r < S; ++r) {
@@ -748,7 +761,7 @@ rmp_status sync_ctl(rmp_batch* b)
         first = false;
     }
     HIPCHK(hipMemcpyAsync(b->d_desc, b->hdesc.data(), sizeof(RepDesc) * S, hipMemcpyHostToDevice, b->stream));
-    for (int k = 0; k < 6; ++k)
+    for (int k = 0; k < N_PREFIX; ++k)
         HIPCHK(hipMemcpyAsync(b->d_prefix[k], b->hprefix[k].data(), 4 * (S + 1), hipMemcpyHostToDevice, b->stream));
     HIPCHK(hipStreamSynchronize(b->stream));
     b->dirty = false;
@@ -967,6 +980,8 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
     }
     {
         Timer tm(b, KN_PERM, s);
+        if (b->totals[PF_CELLS] > 0)
+            hipLaunchKernelGGL(k_cells, dim3(b->totals[PF_CELLS]), dim3(256), 0, s, work(b, PF_CELLS));
         if (!b->multi_scan)
             hipLaunchKernelGGL((k_perm<2, true>), dim3(nch * 2), dim3(256), 0, s, work(b, PF_CHUNK), 2);
         else if (ppt == 4) hipLaunchKernelGGL((k_perm<4, false>), gp, dim3(bs), 0, s, work(b, PF_CHUNK), wpc);
@@ -1138,7 +1153,7 @@ rmp_status batch_init(rmp_batch* b, int32_t nslots, int32_t precision, void* ctl
     size_t o = 0;
     b->d_desc = (RepDesc*)(b->ctl + o);
     o += aup(sizeof(RepDesc) * (size_t)nslots);
-    for (int k = 0; k < 6; ++k) {
+    for (int k = 0; k < N_PREFIX; ++k) {
         b->d_prefix[k] = (int32_t*)(b->ctl + o);
         o += aup(4 * (size_t)(nslots + 1));
     }

@@ -117,7 +117,8 @@ struct RepDesc {
     double dt, h, tau, vscale, mass, ca, sa, cat_prob, skin_half2;
     double vcap;               // speed up to which tilemask holds
     double cull_me, cull_margin; // MD chain cull: entry displacement allowed per interval; + skin/2
-    int32_t bulk_on, pad1;
+    int32_t bulk_on;
+    int32_t sparse;            // per-cell work by k_cells, not by the particle workgroups
     int32_t flow;              // constant acceleration and/or walls: every particle streams
     int32_t walls;             // plates at z = 0 and z = Ld[2]
     int32_t wall_n0;           // particles of a full cell (virtual fill of cut cells)
@@ -140,7 +141,7 @@ struct RepDesc {
     const uint32_t* cell_of;   // [ncell] cell of a sort rank
     double* partials;          // [2][G * ROWW + BCW] 64-bit exchange words of the MD chain
     double* epart;             // [G][2] reaction energy / flips of the interval
-    double* axes;              // [ncell][3] rotation axes of the coming collision, by sort rank (k_perm)
+    double* axes;              // [ncell][3] rotation axes of the coming collision, by sort rank (collision_draws)
     double* bulk;              // [ncell][2] its bulk-reaction uniforms
     uint32_t* tilemask;        // [n_tiles] colloids whose list reach meets the tile at speeds up to vcap
     double* tpart;             // [n_tiles][4] collision partials: temperature sum, cells, reaction energy, flips

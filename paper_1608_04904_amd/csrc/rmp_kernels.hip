@@ -15,6 +15,7 @@
 //                  per step when the list spans several workgroups; then the
 //                  list particles' cells and ranks
 //   k_scan_*       exclusive scan of the cell counts -> cell_start
+//   k_cells        sparse boxes: the random numbers per cell
 //   k_perm         array position of each particle to slot
 //                  cell_start[key] + rank of the sort permutation
 //   k_collide      per tile of cells: gather the records through the
@@ -531,6 +532,19 @@ __global__ __launch_bounds__(256) void k_stream(Work w, int wg_per_chunk)
     stream_body<T, PPT, FLOW, 256>(w.desc, w.prefix, w.nrep, xcd_range(blockIdx.x, gridDim.x), wg_per_chunk);
 }
 
+// Sparse boxes: the coming collision's draws, a block of DRAW_CELLS cells per
+// workgroup, and its tile masks, shared out over the replica's waves.
+__global__ __launch_bounds__(256) void k_cells(Work w)
+{
+    const int rep = find_rep(w.prefix, w.nrep, blockIdx.x);
+    const int blk = (int)blockIdx.x - w.prefix[rep];
+    const RepDesc& D = w.desc[rep];
+    if (!D.active) return;
+    collision_draws(D, (int64_t)blk * DRAW_CELLS);
+    const Share sh{(int64_t)blk * 4 + (threadIdx.x >> 6), (int64_t)(w.prefix[rep + 1] - w.prefix[rep]) * 4};
+    tile_masks(D, sh.lo(D.n_tiles), sh.hi(D.n_tiles));
+}
+
 // Sort permutation of the coming collision: particle i goes to slot
 // start[key] + rank.  Thread t of a workgroup holds particles t, t +
 // blockDim.x, ... of its span (PPT of them).  The replica's workgroups share
@@ -599,7 +613,7 @@ __global__ __launch_bounds__(256) void k_perm(Work w, int wg_per_chunk)
         if (i < n && slot[u] < n) perm[slot[u]] = (uint32_t)i;
     }
     const Share sh{(int64_t)chunk * wg_per_chunk + sub, (int64_t)D.n_chunks * wg_per_chunk};
-    if (threadIdx.x < 64) tile_masks(D, sh.lo(D.n_tiles), sh.hi(D.n_tiles));
+    if (threadIdx.x < 64 && !D.sparse) tile_masks(D, sh.lo(D.n_tiles), sh.hi(D.n_tiles));
     if (sh.me == 0 && threadIdx.x == 0) D.rs->coll_closing = D.rs->coll_step;
     if (sh.me == 0 && (int)threadIdx.x < D.nc) {
         RepState* rs = D.rs;

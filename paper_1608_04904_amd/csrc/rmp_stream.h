@@ -85,7 +85,8 @@ __device__ __forceinline__ void rec_store(gptr<Rec<T>> r, const T (&x)[3], const
 // Per-cell random numbers of the coming collision, for the block of DRAW_CELLS
 // sort ranks from lo: rotation axes and bulk-reaction uniforms.  Made by
 // k_stream, which waits for its atomics anyway, because a wave's run of cells
-// in the collision has a dozen only.  A Philox block takes 2000 cycles of a
+// in the collision has a dozen only; in a sparse box, where that would leave
+// many cells to few workgroups, by k_cells.  A Philox block takes 2000 cycles of a
 // wave (64-bit products), so all lanes are kept at work: a workgroup does a
 // whole block of cells, and the 5 % of the axes that both tries of their first
 // Philox block miss are collected and tried again together.  (A share of the
@@ -268,7 +269,7 @@ __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* 
         }
     }
     // the blocks of cells that fall to this workgroup
-    {
+    if (!D.sparse) {
         const int64_t nblk = (D.ncell + DRAW_CELLS - 1) / DRAW_CELLS;
         const int64_t me = (int64_t)chunk * wg_per_chunk + sub, all = (int64_t)D.n_chunks * wg_per_chunk;
         for (int64_t j = (me * nblk + all - 1) / all; j < ((me + 1) * nblk + all - 1) / all; ++j)

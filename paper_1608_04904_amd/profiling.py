@@ -43,7 +43,7 @@ def kernel_source_hash() -> str:
 # library kernel (rocprof name without namespace and template arguments) ->
 # the name of the timed phase that brackets it in the library's own events
 PHASE = {"k_stream": "stream", "k_chain": "chain", "k_scan_blocks": "scan_blocks",
-         "k_scan_final": "scan_final", "k_perm": "perm", "k_collide": "collide",
+         "k_scan_final": "scan_final", "k_perm": "perm", "k_cells": "perm", "k_collide": "collide",
          "k_collide_dense": "collide", "k_collide_big": "collide", "k_close": "close",
          "k_list": "list", "k_analysis": "analysis"}
 
