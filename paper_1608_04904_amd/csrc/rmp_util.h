@@ -453,13 +453,14 @@ __device__ __forceinline__ void flow_step(T (&x)[3], T (&v)[3], const T (&g)[3],
 // moving up at m >= L, moving down at -m < 0, that is m >= the smallest
 // positive number; either way the wrap is then m - L (and -L, where y + L
 // rounded to L and the wrap subtracts L again, becomes zero).  If no lane's m
-// is outside after all n_md drifts, none wrapped; otherwise the drifts are
-// done again in runs of DRIFT_RUN, and a run in which a coordinate of some
-// lane left the box once more for that coordinate with the wrap after each
-// drift, without branches.  (Doing all n_md drifts again with branches, one
-// coordinate after the other, held up whole collision tiles behind one wave.)  A coordinate that
-// starts outside the box, or a step longer than it, takes the drifts as they
-// are defined (drift_wrapped).
+// is outside after all n_md drifts, none wrapped (a coordinate moving down that
+// ends exactly on zero counts as outside there, since -m would be -0); otherwise
+// the drifts are done again in runs of DRIFT_RUN, and a run in which a
+// coordinate of some lane left the box once more for that coordinate with the
+// wrap after each drift, without branches.  (Doing all n_md drifts again with
+// branches, one coordinate after the other, held up whole collision tiles behind
+// one wave.)  A coordinate that starts outside the box, or a step longer than it,
+// takes the drifts as they are defined (drift_wrapped).
 constexpr int DRIFT_RUN = 10;
 
 template <class T> __device__ __forceinline__ T tiny();
@@ -525,7 +526,7 @@ __device__ __forceinline__ void advance(const RepDesc& D, T (&x)[P][3], T (&v)[P
         for (int u = 0; u < P; ++u)
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                out = out || (go[u] && z[u][d] >= (v[u][d] < (T)0 ? tiny<T>() : Lt[d]));
+                out = out || (go[u] && z[u][d] >= (v[u][d] < (T)0 ? (T)0 : Lt[d]));
                 odd = odd || (go[u] && !(m[u][d] > (v[u][d] < (T)0 ? -Lt[d] : -tiny<T>())));
             }
         if (__ballot(out || odd) == 0ull) {
