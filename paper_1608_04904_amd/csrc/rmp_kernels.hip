@@ -943,7 +943,11 @@ __device__ __forceinline__ int cell_of_slot(const uint32_t* s_start, const uint8
 // the records into cell order first and reading them back cost 557 + 714.
 constexpr int RUN_CELLS = 24;        // cells per run at most
 
-template <class T, int PPT, int RULE>
+// VW: the partial sums of reaction energy and flips, one for each wave of a
+// workgroup; a lone wave keeps four, by run, as four waves would, and the
+// temperature terms are summed by cell, so that a tile's sums are the same
+// whichever of the two forms its launch takes
+template <class T, int PPT, int RULE, int VW>
 struct alignas(16) CollideWave {
     static constexpr int CAP = 64 * PPT;
     T x[3][CAP], v[3][CAP];                  // by slot
@@ -955,7 +959,7 @@ struct alignas(16) CollideWave {
     uint8_t st[CAP];
     double u[RUN_CELLS][3];                  // centre-of-mass velocity
     double n[RUN_CELLS][3];                  // rotation axis; under the thermostat the mean draw
-    double du[2];                            // reaction energy and flips
+    double du[VW][2];                        // reaction energy and flips
     int16_t flip[RUN_CELLS];
     uint8_t go[RUN_CELLS];
 };
@@ -969,16 +973,18 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
     const int tile = w.nrep == 1 ? item : item - w.prefix[rep];
     const RepDesc& D = w.desc[rep];
     if (!D.active || D.rule != RULE || D.dense || (D.flow != 0) != FLOW) return;
-    __shared__ CollideWave<T, PPT, RULE> s_w[NW];
-    using Ctx = CollideWave<T, PPT, RULE>;
-    static_assert(sizeof(Ctx) - 128 >= 64 * sizeof(Rec<T>), "room for 64 records before du");
+    constexpr int VW = NW == 1 ? 4 : 1;
+    using Ctx = CollideWave<T, PPT, RULE, VW>;
+    __shared__ Ctx s_w[NW];
+    static_assert(sizeof(Ctx) - 176 >= 64 * sizeof(Rec<T>), "room for 64 records before du");
+    __shared__ double s_ct[COLL_TCMAX];        // the cells' temperature terms
     __shared__ uint32_t s_start[COLL_TCMAX + 1];
     RepState* rs = D.rs;
     const ColloidParams* cp = D.cp;
     const int nc = D.nc;
     const int t = threadIdx.x, lane0 = t & 63;
     const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(t >> 6);
-    CollideWave<T, PPT, RULE>& S = s_w[wave];
+    Ctx& S = s_w[wave];
     const int TC = D.tile_cells;
     const int64_t c0 = (int64_t)tile * TC;
     const int ncl = (int)((c0 + TC < D.ncell ? c0 + TC : D.ncell) - c0);
@@ -999,7 +1005,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
     if (lane0 < ncl) s_start[lane0] = sl0;
     if (lane0 == 0) {
         s_start[ncl] = tend;
-        S.du[0] = S.du[1] = 0.0;
+#pragma unroll
+        for (int q = 0; q < VW; ++q) S.du[q][0] = S.du[q][1] = 0.0;
     }
 
     const gptr<const Rec<T>> src = G((const Rec<T>*)recs<T>(D, cur));
@@ -1008,8 +1015,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
     const gptr<const double> axes = G((const double*)D.axes);
     const double ca = D.ca, sa = D.sa, oma = 1.0 - D.ca;
 
-    double t_sum = 0.0;        // temperature terms of this lane's cells
-    int t_cells = 0;           // (uniform)
+    int t_cells = 0;           // cells with a temperature term (uniform)
     uint64_t big = 0;          // cells beyond a run's capacity (the same in every wave)
     int ga = 0, nrun = 0;
     // this wave's next run: cells [a, a + nrc) of the tile, slots [q0, q0 + ns)
@@ -1055,7 +1061,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
         T xq[PPT][3], vq[PPT][3];
         uint32_t idq[PPT], stq[PPT], pc[PPT];
         int lc[PPT];                                             // cell of the slot, from a
-        const int a0 = a, nr = nrc, n1 = ns;
+        const int a0 = a, nr = nrc, n1 = ns, dq = (nrun - 1) & (VW - 1);
         const uint32_t q1 = q0;
 #pragma unroll
         for (int u = 0; u < PPT; ++u) rec_load<T>(src + (int64_t)pj[u], xq[u], vq[u], idq[u], stq[u]);
@@ -1174,12 +1180,14 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
             bool tc = false, flips = false;
             if (lane < nr) {
                 const int cb = (int)(s_start[a0 + lane] - q1), ce = (int)(s_start[a0 + lane + 1] - q1);
+                double term = 0.0;
                 if (S.go[lane] == 1) {
                     double tsum = 0.0;
                     for (int i = cb; i < ce; ++i) tsum = tsum + S.sq[i];
-                    t_sum += (D.mass * tsum) / (double)(ce - cb - 1);
+                    term = (D.mass * tsum) / (double)(ce - cb - 1);
                     tc = true;
                 }
+                s_ct[a0 + lane] = term;
                 if (D.bulk_on) {
                     // the cell's B particles: bits [cb, ce) of the species masks
                     int nB = 0;
@@ -1219,8 +1227,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
                 du = wave_tree_sum(du);
                 nf = wave_tree_sum(nf);
                 if (lane == 0) {
-                    S.du[0] += du;
-                    S.du[1] += nf;
+                    S.du[dq][0] += du;
+                    S.du[dq][1] += nf;
                 }
             }
         }
@@ -1297,20 +1305,29 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
         records_out<T, PPT>(reinterpret_cast<char*>(&S), dst + (int64_t)q1, n1, xr, vr, idr, so);
     }
     const int lane = lane0;
-    // the wave's sums, then the waves in order
-    const double red = wave_tree_sum(t_sum);
-    __shared__ double s_red[NW][4];
-    if (lane < 4) s_red[wave][lane] = lane == 0 ? red : lane == 1 ? (double)t_cells : S.du[lane - 2];
+    // the tile's sums: the temperature terms over its cells (those of a run; the
+    // others have none), the rest over the waves in order
+    __shared__ double s_red[NW * VW][3];
+    if (lane < VW) {
+        s_red[wave * VW + lane][0] = lane == 0 ? (double)t_cells : 0.0;
+        s_red[wave * VW + lane][1] = S.du[lane][0];
+        s_red[wave * VW + lane][2] = S.du[lane][1];
+    }
     if constexpr (NW > 1) __syncthreads();
     else wave_sync();
     double part = 0.0;
-    if (t < 4)
+    if (wave == 0) {
+        const uint32_t nn = sl1 - sl0;
+        const double tsum = wave_tree_sum(lane < ncl && nn >= 2u && nn <= (uint32_t)CAP ? s_ct[lane] : 0.0);
+        if (t == 0) part = tsum;
+        else if (t < 4)
 #pragma unroll
-        for (int q = 0; q < NW; ++q) part = part + s_red[q][t];
+            for (int q = 0; q < NW * VW; ++q) part = part + s_red[q][t - 1];
+    }
     if (big != 0ull) {
         // cells beyond a run's capacity, one after the other, by the workgroup
         // (their temperature, reaction energy and flips after the others')
-        __shared__ double s_bu[3], s_bn[3], s_bred[(NT / 64 + 1) * 4];
+        __shared__ double s_bu[3], s_bn[3], s_bred[(NT / 64 + 1) * 4], s_bsum[4];
         __shared__ int32_t s_bflip;
         // (the waves' runs are done: their LDS holds the terms)
         double* buf = reinterpret_cast<double*>(s_w);
@@ -1329,9 +1346,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
         double br[4] = {b_sum, b_cells, b_du, b_flip};
         block_sum_n<NT, 4>(br, s_bred);
         if (t == 0)
-            for (int j = 0; j < 4; ++j) s_red[0][j] = br[j];
+            for (int j = 0; j < 4; ++j) s_bsum[j] = br[j];
         __syncthreads();
-        if (t < 4) part = part + s_red[0][t];
+        if (t < 4) part = part + s_bsum[t];
     }
     if (t < 4) G(D.tpart)[(int64_t)tile * 4 + t] = part;
 }

@@ -50,3 +50,29 @@ def test_a_coordinate_that_lands_on_zero_is_plus_zero(precision, place, way):
         o.run(4, 1)
         assert x.tobytes() == np.asarray(o.get_state()["x"]).tobytes()
     g.close()
+
+
+def test_observables_of_a_slot_do_not_depend_on_the_others():
+    """A slot alone and beside one of 4.3 million particles, which takes
+    another form of the collision: the same bits."""
+    rm = _rm()
+    p = W.dimer_system(L=20, rho=10, n_md=4, seed=3, bulk_rate=0.5)
+    big = W.base_params(L=(76, 75, 76), rho=10, dt=0.01, n_md=4)
+    s = W.random_state(p, 9, species_B_fraction=0.5)
+    out = []
+    for beside in (False, True):
+        b = rm.Batch(2, 64)
+        b.set_slot(0, p, 21, 4)
+        b.set_state(0, s)
+        if beside:
+            b.set_slot(1, big, 22, 4)
+        print(f"[bits] beside={beside}", flush=True)
+        seen = []
+        for _ in range(3):
+            b.step(1)
+            seen.append(b.observables(0))
+        out.append(seen)
+        b.close()
+    for a, c in zip(*out):
+        assert a == c, [(k, a[k], c[k]) for k in a if a[k] != c[k]]
+    assert out[0][-1]["n_bulk_flips"] > 10 and out[0][-1]["e_rxn"] != 0.0
