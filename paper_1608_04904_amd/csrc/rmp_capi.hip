@@ -165,7 +165,7 @@ Layout layout_of(const rmp_params* p)
     L.keyrank = take(8 * s.n);
     L.perm = take(4 * s.n);
     L.xchg = take(8 * s.n);
-    L.lbits = take(8 * (size_t)(CHUNK / 64) * s.n_chunks);
+    L.lbits = take(2 * 8 * (size_t)(CHUNK / 64) * s.n_chunks);
     L.count = take(4 * (s.ncell + 1));      // (counted in pairs)
     L.start = take(4 * (s.ncell + 1));
     L.axes = take(3 * 8 * (size_t)s.ncell);

@@ -1226,7 +1226,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             x[j][d] = valid[j] ? rb[idx[j]].x[d] : (T)0;
             v[j][d] = valid[j] ? rb[idx[j]].v[d] : (T)0;
         }
-        st[j] = valid[j] ? (uint8_t)(rb[idx[j]].st & ST_PUBLIC) : (uint8_t)0;
+        st[j] = valid[j] ? (uint8_t)(rb[idx[j]].st & 3u) : (uint8_t)0;
         pid[j] = valid[j] ? rb[idx[j]].id : 0;
         for (int d = 0; d < 3; ++d) x0[j][d] = x[j][d];
     }
@@ -1409,7 +1409,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             rb[i].x[d] = x[j][d];
             rb[i].v[d] = v[j][d];
         }
-        rb[i].st = (uint32_t)st[j] | ST_LIST;
+        rb[i].st = (uint32_t)st[j];
         uint32_t key = cell_key(D, (double)x[j][0], (double)x[j][1], (double)x[j][2], s3);
         const uint32_t rank = __hip_atomic_fetch_add(G(D.count) + key, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         G(D.keyrank)[i] = ((uint64_t)key << 32) | rank;

@@ -84,7 +84,7 @@ struct Analysis {
 // memory: one aligned 64-byte record in FP64, 32 bytes in FP32, so that the
 // collision gathers each particle through the sort permutation with whole
 // sectors and writes whole sectors back.  st: bit 0 species, bit 1 catalysis
-// flag, bit 2 Verlet-list member for the coming interval (library internal).
+// flag.
 // The position and the first velocity component fill the record's first 32
 // (16) bytes, so that streaming rewrites whole sectors.
 template <class T> struct Rec;
@@ -98,8 +98,6 @@ template <> struct alignas(32) Rec<float> {
     uint32_t id, st;
 };
 static_assert(sizeof(Rec<double>) == 64 && sizeof(Rec<float>) == 32, "record sizes");
-constexpr uint32_t ST_PUBLIC = 3u;   // species and catalysis flag
-constexpr uint32_t ST_LIST = 4u;     // Verlet-list member
 
 // Per-replica descriptor, written by the host.
 struct RepDesc {
@@ -132,7 +130,8 @@ struct RepDesc {
     uint32_t* start;           // [ncell + 1]
     uint32_t* scanblk;         // [n_scanblk]
     double* xchg;              // [n] ids and state bytes for the exchange with the host
-    uint64_t* lbits;           // [16 n_chunks] Verlet-list membership bits; zero outside chunks with members
+    uint64_t* lbits;           // [2][16 n_chunks] Verlet-list membership by array position: buffer coll_step & 1
+                               // holds the coming interval's, which streaming and chain only read; the other is zero
     uint32_t* chunk_cnt;       // [2][n_chunks] list members per chunk, buffer coll_step & 1 of the collision
     double* gpart;             // [n_close][4] tile partials summed by workgroup of k_close
     uint32_t* done;            // [32 (1 + groups of 64 n_close)] its arrivals; zero between launches

@@ -152,7 +152,8 @@ __global__ __launch_bounds__(256) void k_list(Work w)
     if (t < nc)
         for (int d = 0; d < 3; ++d) sXw[t][d] = colloid_image(rs->X[t][d], D.Ld[d]);
     __syncthreads();
-    Rec<T>* rec = recs<T>(D, (int)(rs->coll_step & 1));
+    const Rec<T>* rec = recs<T>(D, (int)(rs->coll_step & 1));
+    uint64_t* lbits = list_bits(D, rs->coll_step);
     const int64_t n = D.n;
     const int64_t base = (int64_t)chunk * CHUNK;
     uint32_t cnt = 0;
@@ -160,13 +161,11 @@ __global__ __launch_bounds__(256) void k_list(Work w)
         const int64_t i = base + j;
         bool c = false;
         if (i < n) {
-            Rec<T>* r = rec + i;
-            const uint32_t st = r->st & ST_PUBLIC;
-            c = is_candidate(D, cp, nc, sXw, (uint8_t)st, r->x[0], r->x[1], r->x[2], r->v[0], r->v[1], r->v[2]);
-            r->st = st | (c ? ST_LIST : 0u);
+            const Rec<T>* r = rec + i;
+            c = is_candidate(D, cp, nc, sXw, (uint8_t)r->st, r->x[0], r->x[1], r->x[2], r->v[0], r->v[1], r->v[2]);
         }
         const uint64_t m = __ballot(c);
-        if ((t & 63) == 0) D.lbits[i >> 6] = m;
+        if ((t & 63) == 0) lbits[i >> 6] = m;
         cnt += c ? 1u : 0u;
     }
     uint32_t tot = block_sum_u32<256>(cnt, sred);
@@ -185,8 +184,9 @@ __global__ __launch_bounds__(256) void k_list(Work w)
 // bookkeeping; with more, each sums its share of the tiles' partials and the
 // last to arrive combines the shares in order; what it and the others exchange
 // goes through atomics at device scope.  The counts are double-buffered by
-// collision, since workgroups read each other's: this launch clears the ones
-// the next collision adds to.  (A scan by one workgroup and a launch that
+// collision, since workgroups read each other's, and the list bits, since the
+// streaming reads them after this launch: it clears the ones the next collision
+// adds to.  (A scan by one workgroup and a launch that
 // wrote the list after it: 60 + 9 us at 128^3, 10 + 6 at 32^3; now 40 and 12.)
 constexpr int CLOSE_CH = CHUNK / 64;         // chunks per workgroup
 constexpr int CLOSE_DIRECT = 64;             // (its chunks: one per thread of a workgroup)
@@ -214,8 +214,10 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
     const gptr<uint32_t> nxt = G(D.chunk_cnt) + (int64_t)(coll & 1) * nch;
     const int c0 = b * CLOSE_CH;
     const int chunk = c0 + wave;
-    const gptr<uint64_t> bits = G(D.lbits) + (int64_t)chunk * (CHUNK / 64);
+    const gptr<uint64_t> bits = G(list_bits(D, coll)) + (int64_t)chunk * (CHUNK / 64);
+    const gptr<uint64_t> spent = G(list_bits(D, coll + 1)) + (int64_t)chunk * (CHUNK / 64);
     const uint64_t word = chunk < nch ? bits[lane >> 2] : 0ull;
+    const bool clear = chunk < nch && lane < CHUNK / 64 && spent[lane] != 0ull;
     const uint32_t mine = chunk < nch ? cnt[chunk] : 0u;
     uint32_t pre = 0, total = 0;
     if (!counted) {
@@ -247,6 +249,7 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
         s_cnt[wave] = mine;
         if (chunk < nch) nxt[chunk] = 0u;
     }
+    if (clear) spent[lane] = 0ull;
     if (__syncthreads_or(mine != 0u || !counted)) {
         if (counted) {
             for (int k = t; k < c0; k += 4 * 1024) {
@@ -278,7 +281,8 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
         if (mine != 0u) {
             // lane l: particles [16 l, 16 l + 16) of the chunk
             const int64_t i0 = (int64_t)chunk * CHUNK + lane * 16;
-            uint32_t f = (uint32_t)(word >> ((lane & 3) * 16)) & 0xffffu;
+            const uint32_t all = (uint32_t)(word >> ((lane & 3) * 16)) & 0xffffu;
+            uint32_t f = all;
             uint32_t x = (uint32_t)__popc(f);
             const uint32_t own = x;
 #pragma unroll
@@ -288,19 +292,17 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
             }
             pre += x - own;
             for (; f; f &= f - 1u) {
-                const int64_t i = i0 + __ffs(f) - 1;
-                if ((int64_t)pre < (int64_t)D.cand_cap) {
-                    D.cand_idx[pre] = (uint32_t)i;
-                } else if (i < D.n) {
-                    // beyond the list capacity (RMP_FLAG_LIST_OVERFLOW is set):
-                    // the particle is streamed freely so that every particle is
-                    // still binned exactly once
-                    Rec<T>* r = recs<T>(D, (int)(coll & 1)) + i;
-                    r->st = r->st & ST_PUBLIC;
+                // beyond the list capacity (RMP_FLAG_LIST_OVERFLOW is set) the
+                // particles are streamed freely so that every particle is still
+                // binned exactly once
+                if ((int64_t)pre >= (int64_t)D.cand_cap) {
+                    typedef uint16_t __attribute__((may_alias)) bits16;
+                    ((gptr<bits16>)bits)[lane] = (uint16_t)(all & ~f);
+                    break;
                 }
+                D.cand_idx[pre] = (uint32_t)(i0 + __ffs(f) - 1);
                 pre++;
             }
-            if (lane < CHUNK / 64) bits[lane] = 0ull;
         }
     }
     if (counted && after_collision) {
@@ -635,7 +637,7 @@ __device__ __forceinline__ void list_flags(const RepDesc& D, int64_t coll, int64
     const uint64_t lo = m << sh, hi = sh ? m >> (64 - sh) : 0ull;
     if ((threadIdx.x & 63) == 0) {
         const int64_t w0 = o0 >> 6;
-        const gptr<uint64_t> bits = G(D.lbits);
+        const gptr<uint64_t> bits = G(list_bits(D, coll + 1));
         const gptr<uint32_t> cnt = G(D.chunk_cnt) + (int64_t)(coll & 1) * D.n_chunks;
         if (lo) {
             (void)__hip_atomic_fetch_or(bits + w0, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -753,9 +755,7 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
 #pragma unroll
         for (int u = 0; u < JP; ++u)
             if (j0 + u * NT + t < nn) {
-                Rec<T> a = src[pj[u]];
-                a.st &= ST_PUBLIC;
-                rec[r[u]] = a;
+                rec[r[u]] = src[pj[u]];
             }
     }
     // a cell cut by a plate and under-filled has virtual particles, as in
@@ -864,7 +864,7 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
             const T vt[3] = {(T)v3[0], (T)v3[1], (T)v3[2]};
             cnd = is_candidate(D, cp, nc, s_Xw, (uint8_t)s, x0, x1, x2, (double)vt[0], (double)vt[1], (double)vt[2]);
             for (int d = 0; d < 3; ++d) q->v[d] = vt[d];
-            q->st = s | (cnd ? ST_LIST : 0u);
+            q->st = s;
         }
         list_flags(D, coll, (int64_t)q0 + k0 + (t & ~63), cnd);
     }
@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
 #pragma unroll
                 for (int d = 0; d < 3; ++d) { S.x[d][sl] = xr[d]; S.v[d][sl] = vr[d]; }
                 S.id[sl] = idq[u];
-                S.st[sl] = (uint8_t)(stq[u] & ST_PUBLIC);
+                S.st[sl] = (uint8_t)stq[u];
                 if (cull) {
                     // largest |v|^2 rounded up in FP32, for the tile mask (inf
                     // or NaN: no cull)
@@ -1298,7 +1298,6 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
                 if (S.flip[k] == sl) so[u] = 0u;
                 cnd = !FLOW && is_candidate_masked(D, cp, cmask, Xw, (uint8_t)so[u], (double)xr[u][0], (double)xr[u][1],
                                           (double)xr[u][2], (double)vr[u][0], (double)vr[u][1], (double)vr[u][2]);
-                so[u] |= cnd ? ST_LIST : 0u;
             }
             list_flags(D, coll, (int64_t)q1 + u * 64, cnd);
         }
@@ -1498,7 +1497,7 @@ __global__ __launch_bounds__(NT, RULE ? 3 : 4) void k_collide_dense(Work w, int 
 #pragma unroll
                 for (int d = 0; d < 3; ++d) { s_x[d][sl] = xr[u][d]; s_v[d][sl] = vr[u][d]; }
                 s_id[sl] = idr[u];
-                s_st[sl] = (uint8_t)(sr[u] & ST_PUBLIC);
+                s_st[sl] = (uint8_t)sr[u];
                 if constexpr (RULE == 1) {
                     uint64_t wv[4]; double z[3];
                     philox<true>((uint64_t)coll, idr[u], 0, D.seed, TAG_THERMO, wv);
@@ -1636,7 +1635,7 @@ __global__ __launch_bounds__(NT, RULE ? 3 : 4) void k_collide_dense(Work w, int 
                 const T vo[3] = {(T)v3[0], (T)v3[1], (T)v3[2]};
                 cnd = is_candidate_masked(D, cp, cmask, s_Xw, (uint8_t)s, (double)xo[0], (double)xo[1], (double)xo[2],
                                           (double)vo[0], (double)vo[1], (double)vo[2]);
-                rec_store<T, RecWords<T>::W>(dst + ((int64_t)q0 + sl), xo, vo, s_id[sl], s | (cnd ? ST_LIST : 0u));
+                rec_store<T, RecWords<T>::W>(dst + ((int64_t)q0 + sl), xo, vo, s_id[sl], s);
             }
             list_flags(D, coll, (int64_t)q0 + u * NT + (t & ~63), cnd);
         }
@@ -1827,7 +1826,7 @@ __global__ __launch_bounds__(256) void k_fields_out(const RepDesc* Dp, int b, in
         for (int d = 0; d < 3; ++d, o += n) *o = (double)v[d];
     if (what & 4) {
         reinterpret_cast<uint32_t*>(D.xchg)[i] = id;
-        (reinterpret_cast<uint8_t*>(D.xchg) + 4 * n)[i] = (uint8_t)(st & ST_PUBLIC);
+        (reinterpret_cast<uint8_t*>(D.xchg) + 4 * n)[i] = (uint8_t)st;
     }
 }
 

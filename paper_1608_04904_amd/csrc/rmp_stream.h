@@ -151,7 +151,8 @@ struct Share {
 // of cells), and each pair takes one 64-bit atomic of both its counters: the
 // atomics all go to memory, 0.2 a particle where one per run of equal keys in
 // a wave made 0.5.  A list member's record, which the MD chain may be writing
-// meanwhile, is loaded and not used but for the list bit, which stays set.
+// meanwhile, is loaded and not used: who is a member is read from the list bits,
+// a word per wave.
 // A wave reads and writes its 64 records through LDS so that each instruction
 // covers a contiguous kilobyte (one lane a record: 80 us more).
 // 20.97 M particles, 50 drifts: FP64 633 us, FP32 410.  The records, read whole
@@ -182,9 +183,12 @@ __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* 
     bool go[PPT];
     uint32_t id[PPT], st[PPT];
     u32x4 in[PPT][W];
+    uint64_t members[PPT];
+    const gptr<const uint64_t> lbits = G((const uint64_t*)list_bits(D, rs->coll_step));
 #pragma unroll
     for (int u = 0; u < PPT; ++u) {
         const int64_t i0 = base + u * (int)blockDim.x + (threadIdx.x & ~63u);
+        members[u] = FLOW ? 0ull : lbits[i0 >> 6];
         const int64_t left = (n - i0) * W;
         const gptr<const u32x4> p = (gptr<const u32x4>)rec + i0 * W;
 #pragma unroll
@@ -201,7 +205,7 @@ __device__ __forceinline__ void stream_body(const RepDesc* desc, const int32_t* 
 #pragma unroll
         for (int k = 0; k < W; ++k) q.w[k] = buf[lds_word<W>(lane, k)];
         q.unpack(x[u], v[u], id[u], st[u]);
-        go[u] = i < n && (st[u] & ST_LIST) == 0u;
+        go[u] = i < n && ((members[u] >> lane) & 1ull) == 0ull;
     }
     const double s[3] = {uniform_d(G(rs)->shift[0]), uniform_d(G(rs)->shift[1]), uniform_d(G(rs)->shift[2])};
     advance<T, PPT, FLOW>(D, x, v, go);

@@ -388,6 +388,12 @@ __device__ __forceinline__ double species_dU(const RepDesc& D, const ColloidPara
     return du;
 }
 
+// list bits of the interval that ends in collision `coll`
+__device__ __forceinline__ uint64_t* list_bits(const RepDesc& D, int64_t coll)
+{
+    return D.lbits + (coll & 1) * (int64_t)(CHUNK / 64) * D.n_chunks;
+}
+
 // the records of buffer b
 template <class T>
 __device__ __forceinline__ Rec<T>* recs(const RepDesc& D, int b)
