@@ -1168,7 +1168,8 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             cX[d] = rs->X[t][d];
             cV[d] = rs->V[t][d];
             cX0[d] = cX[d];
-            S.sXw[0][t][d] = colloid_image(cX[d], cc.L(d));
+            // (both buffers: a wait that is given up leaves one as it was)
+            S.sXw[0][t][d] = S.sXw[1][t][d] = colloid_image(cX[d], cc.L(d));
         }
         S.cRc2[t] = cp->rc2[t];
         {

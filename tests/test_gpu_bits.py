@@ -76,3 +76,25 @@ def test_observables_of_a_slot_do_not_depend_on_the_others():
     for a, c in zip(*out):
         assert a == c, [(k, a[k], c[k]) for k in a if a[k] != c[k]]
     assert out[0][-1]["n_bulk_flips"] > 10 and out[0][-1]["e_rxn"] != 0.0
+
+
+def test_waits_given_up_leave_finite_positions():
+    """Three colloids take the exchange with a master workgroup; with a wait
+    budget of 1 us its waits expire, and the workgroups then go on with the last
+    positions they have."""
+    rm = _rm()
+    p = W.base_params(L=(40, 24, 24), rho=10, dt=0.01, n_md=10)
+    for k in range(3):
+        W.add_colloid(p, (7.0 + 13.0 * k, 12.0, 12.0), sigma=4.0)
+    s = W.random_state(p, 12)
+    g = rm.System(p, 3)
+    g.set_tuning(barrier_budget_us=1, use_graph=0)
+    g.set_state(s)
+    print("[bits] waits given up", flush=True)
+    g.step(10, 1)
+    o = g.observables(raise_on_flags=False)
+    assert o["flags"] & 32
+    a = g.get_state()
+    assert np.isfinite(a["x"]).all() and np.isfinite(a["v"]).all()
+    assert o["flags"] & 4 == 0
+    g.close()
