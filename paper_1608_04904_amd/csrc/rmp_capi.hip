@@ -222,7 +222,9 @@ struct Replica {
 
 }  // namespace
 
-constexpr int OBS_HOST_CHUNKS = 1024;    // observations of up to this many chunks go to pinned memory
+// Observations of up to this many chunks (33.5 million particles, 2 MB) go to
+// pinned memory, in a buffer as large as the handle's observations so far needed
+constexpr int OBS_HOST_CHUNKS = 32768;
 
 struct rmp_batch {
     int32_t nslots = 0;
@@ -240,7 +242,8 @@ struct rmp_batch {
     std::mutex obs_mu;              // hobs and n_obs: the call that has it uses hobs, the others do without
     std::unique_ptr<std::mutex[]> xchg_mu;  // per slot: the scratch of the state exchange
     int n_obs = 0;                  // observations without it so far
-    char* hobs = nullptr;           // pinned: observation partials of OBS_HOST_CHUNKS chunks, then a state
+    char* hobs = nullptr;           // pinned: a state, then observation partials of hobs_chunks chunks
+    int hobs_chunks = 0;
     int32_t chain_resident[2][5] = {}; // chain workgroups the device holds at once, per shape:
                                        // generic variant, one- or two-colloid variant
     int32_t nc_common = -1;         // colloid count shared by every occupied slot, -1 if mixed
@@ -303,6 +306,8 @@ void note_error(const char* what, hipError_t e)
             return RMP_EHIP;                            \
         }                                               \
     } while (0)
+
+constexpr size_t OBS_STATE_BYTES = (sizeof(RepState) + ALIGN - 1) / ALIGN * ALIGN;
 
 // Address of `scratch` on each device (nullptr until taken) and a lock per
 // device that keeps the allocation-free calls on one device from
@@ -1229,23 +1234,31 @@ rmp_status observe(rmp_batch* b, int slot, rmp_obs* o, char* scr = nullptr)
     w.nrep = 1;
     w.flags = 0;
     w.budget = barrier_budget(b);
-    // small systems: the kernel writes the partials and the state to pinned
-    // host memory, and the call waits for it alone (two copies to pageable
-    // memory after it: 40 us a call at 10^3, now 18); one call at a time, the
-    // other host threads' take the copies
+    // the kernel writes the partials and the state to pinned host memory, and
+    // the call waits for it alone (two copies to pageable memory after it, us a
+    // call at 10, 64 and 128 cells cubed: FP64 40, 75, 362, now 18, 44, 261; FP32
+    // 38, 64, 253, now 18, 34, 152); one call at a time, the other host threads'
+    // take the copies
     std::unique_lock<std::mutex> pinned(b->obs_mu, std::defer_lock);
     bool direct = !scr && cnt <= OBS_HOST_CHUNKS && pinned.try_lock();
-    if (direct && !b->hobs) {
-        // from the second observation on (allocating it takes longer than one)
-        direct = b->n_obs++ > 0 && hipHostMalloc((void**)&b->hobs, OBS_HOST_CHUNKS * 64 + sizeof(RepState),
-                                                 hipHostMallocDefault) == hipSuccess;
+    if (direct && b->hobs_chunks < cnt) {
+        // once the calls without it have cost about as much as allocating it
+        // does (50 us up to 64 KB, beyond 350 to 500)
+        direct = b->n_obs++ >= (cnt <= 1024 ? 1 : 8);
+        if (direct) {
+            if (b->hobs) (void)hipHostFree(b->hobs);
+            b->hobs_chunks = std::max(cnt, 1024);
+            direct = hipHostMalloc((void**)&b->hobs, OBS_STATE_BYTES + 64 * (size_t)b->hobs_chunks,
+                                   hipHostMallocDefault) == hipSuccess;
+        }
         if (!direct) {
             (void)hipGetLastError();
             b->hobs = nullptr;
+            b->hobs_chunks = 0;
         }
     }
-    double* part = scr ? (double*)scr : direct ? (double*)b->hobs : nullptr;
-    RepState* state = direct ? (RepState*)(b->hobs + OBS_HOST_CHUNKS * 64) : nullptr;
+    RepState* state = direct ? (RepState*)b->hobs : nullptr;
+    double* part = scr ? (double*)scr : direct ? (double*)(b->hobs + OBS_STATE_BYTES) : nullptr;
     hipLaunchKernelGGL((k_observe<T>), dim3(cnt), dim3(256), 0, s, w, part, state);
     st = last_launch("k_observe");
     if (st != RMP_OK) return st;

@@ -112,8 +112,7 @@ def test_reading_some_fields(L, precision, fields):
     g.close()
 
 
-# 1, 1024 and 1025 chunks of 1024 particles, and the chunks of two slots of
-# very different size
+# up to 1, and 1024 and 1025, and 3072 chunks of 1024 particles
 @pytest.mark.parametrize("precision", [64, 32])
 @pytest.mark.parametrize("n", [1, 1024, 1025, 1 << 20, (1 << 20) + 1, 3 << 20])
 def test_every_way_of_an_observation_agrees(n, precision):
@@ -123,8 +122,9 @@ def test_every_way_of_an_observation_agrees(n, precision):
     g = rm.System(p, 3)
     g.step(3, 1)
     print(f"[shared] observations of {n} particles FP{precision}", flush=True)
-    first, second, third = g.observables(), g.observables(), g.observables()
-    assert first == second == third == g.observables_noalloc()
+    first = g.observables()
+    assert all(g.observables() == first for _ in range(10))
+    assert first == g.observables_noalloc()
     g.step(3, 1)
     assert g.observables() == g.observables_noalloc() != first
     g.close()
@@ -144,7 +144,32 @@ def test_slots_of_different_size_observed_in_turn():
         alone.append(g.observables())
         g.close()
     b.step(2)
-    for _ in range(3):
+    for _ in range(4):
         for k in (0, 1, 2, 1, 0):
             assert b.observables(k) == alone[k], k
     b.close()
+
+
+def _us(f, reps=15):
+    import time
+    ts = []
+    for _ in range(reps):
+        t = time.perf_counter()
+        f()
+        ts.append(time.perf_counter() - t)
+    return 1e6 * sorted(ts)[reps // 2]
+
+
+def test_observation_time_does_not_jump_with_the_size():
+    """48^3 cells of 10 particles (1080 chunks) beside 47^3 (1014)."""
+    rm = _rm()
+    t = {}
+    for L in (47, 48):
+        g = rm.System(_solvent((L, L, L)), 3)
+        g.step(3, 1)
+        for _ in range(12):
+            g.observables()
+        t[L] = _us(g.observables)
+        g.close()
+    print(f"[shared] observation us {t}", flush=True)
+    assert t[48] <= 1.6 * t[47]
