@@ -1350,20 +1350,33 @@ rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
     const int cur = (int)(rs.coll_step & 1);
     const int64_t n = R.sz.n;
     // small FP32 states leave as floats, half the bytes over the link, and are
-    // widened here (327,680 particles 1.24 ms, by the kernel 2.20); larger ones
-    // are faster widened by the kernel (1,310,720: 8.2 ms, here 9.4)
+    // widened here (in us, by the kernel and here: 80,000 particles 272 and 194,
+    // 506,530 1530 and 1305, 851,840 2550 and 2490, 2,621,440 7790 and 8130)
     const bool narrow = sizeof(T) == 4 && n <= NARROW_EXCHANGE_N;
-    std::vector<T> tmp;
     if (narrow && n > 0) {
-        hipLaunchKernelGGL((k_fields_out<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (const RepDesc*)(b->d_desc + slot), cur, 4 | 8);
-        st = last_launch("k_fields_out");
-        if (st != RMP_OK) return st;
-        tmp.resize(6 * (size_t)n);
         const char* ids = R.ws + R.lay.xchg;
-        HIPCHK(hipMemcpyAsync(tmp.data(), R.desc.rec[cur ^ 1], sizeof(T) * tmp.size(), hipMemcpyDeviceToHost, s));
+        double* const fields[2] = {dst->x, dst->v};
+        const int what = (dst->x || dst->v ? 8 : 0) | (dst->id || dst->state ? 4 : 0);
+        std::unique_ptr<T[]> tmp;
+        if (what & 8) {
+            tmp.reset(new (std::nothrow) T[3 * (size_t)n]);
+            if (!tmp) return RMP_ENOMEM;
+        }
+        if (what) {
+            hipLaunchKernelGGL((k_fields_out<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                               (const RepDesc*)(b->d_desc + slot), cur, what);
+            st = last_launch("k_fields_out");
+            if (st != RMP_OK) return st;
+        }
         if (dst->id) HIPCHK(hipMemcpyAsync(dst->id, ids, 4 * n, hipMemcpyDeviceToHost, s));
         if (dst->state) HIPCHK(hipMemcpyAsync(dst->state, ids + 4 * n, n, hipMemcpyDeviceToHost, s));
+        for (int f = 0; f < 2; ++f) {
+            if (!fields[f]) continue;
+            HIPCHK(hipMemcpyAsync(tmp.get(), (const T*)R.desc.rec[cur ^ 1] + f * 3 * n, sizeof(T) * 3 * n,
+                                  hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            for (int64_t k = 0; k < 3 * n; ++k) fields[f][k] = (double)tmp[k];
+        }
     }
     for (int pass = 0; !narrow && pass < exchange_passes<T>() && n > 0; ++pass) {
         const int what = exchange_pass<T>(pass);
@@ -1380,11 +1393,6 @@ rmp_status get_state_t(rmp_batch* b, int slot, rmp_host_state* dst)
         if ((what & 4) && dst->state) HIPCHK(hipMemcpyAsync(dst->state, ids + 4 * n, n, hipMemcpyDeviceToHost, s));
     }
     if (n > 0) HIPCHK(hipStreamSynchronize(s));
-    const size_t half = tmp.size() / 2;
-    if (dst->x)
-        for (size_t k = 0; k < half; ++k) dst->x[k] = (double)tmp[k];
-    if (dst->v)
-        for (size_t k = 0; k < half; ++k) dst->v[k] = (double)tmp[half + k];
     for (int c = 0; c < R.p.n_colloids; ++c)
         for (int d = 0; d < 3; ++d) {
             if (dst->X) dst->X[3 * c + d] = rs.X[c][d];

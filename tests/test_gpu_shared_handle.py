@@ -173,3 +173,21 @@ def test_observation_time_does_not_jump_with_the_size():
         g.close()
     print(f"[shared] observation us {t}", flush=True)
     assert t[48] <= 1.6 * t[47]
+
+
+def test_small_fp32_read_of_ids_copies_ids_alone():
+    rm = _rm()
+    from paper_1608_04904_amd import _StateBuffers, _capi
+    p = _solvent((36, 36, 36), 32)
+    g = rm.System(p, 3)
+    g.step(3, 1)
+    buf = _StateBuffers(p["n_solvent"], 0)
+    t = {}
+    for name in ("all", "ids"):
+        h = buf.host_state()
+        if name == "ids":
+            h.x = h.v = None
+        t[name] = _us(lambda: _capi.lib().rmp_get_state(g.h, C.byref(h)))
+    print(f"[shared] FP32 read us {t}", flush=True)
+    assert t["ids"] <= 0.5 * t["all"]
+    g.close()
