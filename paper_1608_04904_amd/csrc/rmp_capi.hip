@@ -437,8 +437,12 @@ ChainShape chain_shape_of(const rmp_batch* b)
 // cells holds at most 64 times the latter).  With many tiles a workgroup is
 // one wave, which takes the runs of its tile one after the other and so has
 // the next run's index loads and the last run's ranks in flight; with few,
-// four waves share a tile.
-constexpr int64_t COLLIDE_ONE_WAVE_N = (int64_t)1 << 21;
+// four waves share a tile, since one wave's tile would be the launch's tail.
+// The collision alone in us, four waves and one (10 particles per cell): FP64
+// 2.6 million particles 87 and 99, 5.1 171 and 177, 7.8 254 and 257, 10 321 and
+// 319, 21 652 and 630; FP32 57 and 65, 112 and 114, 172 and 168, 220 and 210,
+// 446 and 408; batches of 64 dimers (10 million): no difference.
+constexpr int64_t COLLIDE_ONE_WAVE_N = (int64_t)1 << 23;
 
 int collide_nt(const rmp_batch* b)
 {
@@ -450,10 +454,13 @@ int collide_nt(const rmp_batch* b)
 }
 int collide_ppt(const rmp_batch* b) { return b->tun.collide_ppt == 1 ? 1 : 2; }
 
-// Particles per cell beyond which the collision takes the workgroup form: at
-// 32 a run of 128 slots holds three whole cells or four, so a wave has a
-// quarter of its lanes idle, and a cell beyond 128 particles would take the
-// one-by-one path
+// Particles per cell beyond which the collision takes the workgroup form, where
+// a wave's 128 slots would hold few whole cells and a denser one would be
+// collided alone.  One line for every type and rule, between what suits the FP32
+// thermostat and what suits the rest (an interval of 48^3 cells in us, wave and
+// workgroup form: FP64 16 particles per cell 150 and 169, 32 289 and 317, 64 594
+// and 682, thermostat 32 390 and 426; FP32 32 197 and 213, 64 440 and 500,
+// thermostat 16 170 and 166, 32 330 and 291, 64 811 and 732)
 constexpr double DENSE_RHO = 32.0;
 
 bool dense_of(int64_t ncell, int64_t n) { return ncell > 0 && (double)n > DENSE_RHO * (double)ncell; }

@@ -53,11 +53,11 @@ def test_a_coordinate_that_lands_on_zero_is_plus_zero(precision, place, way):
 
 
 def test_observables_of_a_slot_do_not_depend_on_the_others():
-    """A slot alone and beside one of 4.3 million particles, which takes
+    """A slot alone and beside one of 8.7 million particles, which takes
     another form of the collision: the same bits."""
     rm = _rm()
     p = W.dimer_system(L=20, rho=10, n_md=4, seed=3, bulk_rate=0.5)
-    big = W.base_params(L=(76, 75, 76), rho=10, dt=0.01, n_md=4)
+    big = W.base_params(L=(96, 95, 96), rho=10, dt=0.01, n_md=4)
     s = W.random_state(p, 9, species_B_fraction=0.5)
     out = []
     for beside in (False, True):

@@ -58,3 +58,36 @@ def test_list_closed_by_many_workgroups(n):
     p["bulk_rate"] = 0.2
     W.add_colloid(p, (20.0, 21.0, 22.0), sigma=3.0, eps_B=0.5, catalytic=1)
     _both(p, 4, 4)
+
+
+# one wave per tile: from 2^23 particles
+BIG = (96, 96, 92)
+
+
+def _pile(s, at, count, seed):
+    rng = np.random.default_rng(seed)
+    k = rng.permutation(s["x"].shape[1])[:count]
+    s["x"][:, k] = np.asarray(at)[:, None] + 1e-3 * rng.random((3, count))
+    s["v"][:, k] = 0.0
+
+
+@pytest.mark.parametrize("kind", ["dimer", "accelerated", "plates", "thermostat"])
+@pytest.mark.parametrize("ppt", [1, 2])
+def test_collision_of_one_wave_per_tile(kind, ppt):
+    p = W.base_params(L=BIG, rho=10, dt=0.004, n_md=2, rule="at" if kind == "thermostat" else "srd")
+    p["bulk_rate"] = 0.5
+    if kind == "dimer":
+        W.add_dimer(p, (40.0, 41.0, 42.0), (0.6, 0.0, 0.8))
+    if kind == "accelerated":
+        p["accel"] = (0.2, -0.1, 0.3)
+    if kind == "plates":
+        p["walls"], p["wall_density"], p["accel"] = 1, 250, (0.1, 0.0, 0.0)
+
+    def change(s):
+        rng = np.random.default_rng(4)
+        s["state"][:] = rng.random(s["state"].size) < 0.5
+        # oversized cells, the last in the lowest layer, one beside the dimer
+        for i, c in enumerate([66, 90, 127, 140, 300, 900]):
+            _pile(s, (46.3 + 0.01 * i if i == 0 else 10.6 + 7.2 * i, 41.3, 44.7 if i == 0 else 0.003), c, 80 + i)
+    exact = kind in ("dimer", "accelerated")
+    _both(p, 2, 2 if exact else 1, dict(collide_ppt=ppt), exact, change)
