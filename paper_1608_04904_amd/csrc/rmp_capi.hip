@@ -970,10 +970,15 @@ rmp_status launch_interval(rmp_batch* b, hipStream_t s)
     if (!fused) {
         Timer tm(b, KN_STREAM, s);
         const Work w = work(b, PF_CHUNK);
-        if (b->any_free && ppt == 4) hipLaunchKernelGGL((k_stream<T, 4, false>), gp, dim3(bs), 0, s, w, wpc);
-        else if (b->any_free && ppt == 2) hipLaunchKernelGGL((k_stream<T, 2, false>), gp, dim3(bs), 0, s, w, wpc);
-        else if (b->any_free) hipLaunchKernelGGL((k_stream<T, 1, false>), gp, dim3(bs), 0, s, w, wpc);
-        if (b->any_flow) hipLaunchKernelGGL((k_stream<T, 1, true>), dim3(nch * wpc1), dim3(bs), 0, s, w, wpc1);
+#define RMP_STREAM(NT)                                                                                              \
+    if (bs == NT) {                                                                                                 \
+        if (b->any_free && ppt == 4) hipLaunchKernelGGL((k_stream<T, 4, false, NT>), gp, dim3(NT), 0, s, w, wpc);     \
+        else if (b->any_free && ppt == 2) hipLaunchKernelGGL((k_stream<T, 2, false, NT>), gp, dim3(NT), 0, s, w, wpc); \
+        else if (b->any_free) hipLaunchKernelGGL((k_stream<T, 1, false, NT>), gp, dim3(NT), 0, s, w, wpc);            \
+        if (b->any_flow) hipLaunchKernelGGL((k_stream<T, 1, true, NT>), dim3(nch * wpc1), dim3(NT), 0, s, w, wpc1);   \
+    }
+        RMP_STREAM(64) RMP_STREAM(128) RMP_STREAM(256)
+#undef RMP_STREAM
     }
     if (!serial) {
         HIPCHK(hipEventRecord(b->join, b->side));

@@ -528,10 +528,13 @@ __device__ __forceinline__ void tile_masks(const RepDesc& D, int64_t tlo, int64_
     }
 }
 
-template <class T, int PPT, bool FLOW>
-__global__ __launch_bounds__(256) void k_stream(Work w, int wg_per_chunk)
+// (the workgroup size is a parameter of the instance: LDS for 256 threads left a
+// compute unit five workgroups of 64, 128^3 with 8 dimers 2504 us an interval,
+// now 1836)
+template <class T, int PPT, bool FLOW, int NT>
+__global__ __launch_bounds__(NT) void k_stream(Work w, int wg_per_chunk)
 {
-    stream_body<T, PPT, FLOW, 256>(w.desc, w.prefix, w.nrep, xcd_range(blockIdx.x, gridDim.x), wg_per_chunk);
+    stream_body<T, PPT, FLOW, NT>(w.desc, w.prefix, w.nrep, xcd_range(blockIdx.x, gridDim.x), wg_per_chunk);
 }
 
 // Sparse boxes: the coming collision's draws, a block of DRAW_CELLS cells per
@@ -2034,10 +2037,6 @@ __global__ __launch_bounds__(256) void k_msd(Analysis* A, int32_t max_lag)
     template __global__ void k_init_sub<T>(const RepDesc*, const double*);       \
     template __global__ void k_list<T>(Work);                                    \
     template __global__ void k_close<T>(Work, int);                              \
-    template __global__ void k_stream<T, 1, false>(Work, int);                   \
-    template __global__ void k_stream<T, 2, false>(Work, int);                   \
-    template __global__ void k_stream<T, 4, false>(Work, int);                   \
-    template __global__ void k_stream<T, 1, true>(Work, int);                    \
     template __global__ void k_fields_out<T>(const RepDesc*, int, int);          \
     template __global__ void k_fields_in<T>(const RepDesc*, int, int);           \
     template __global__ void k_collide_big<T, 0>(Work, int);                     \
