@@ -501,13 +501,7 @@ __device__ __forceinline__ void advance(const RepDesc& D, T (&x)[P][3], T (&v)[P
 #pragma unroll
         for (int u = 0; u < P; ++u)
             if (go[u])
-                for (int k = 0; k < nmd; ++k) {
-                    // v is opaque at the head of each step: without this hipcc 7.2 lost the
-                    // copy of v[1] that starts a step (its registers then held other data)
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) asm volatile("" : "+v"(v[u][d]));
-                    flow_step<T>(x[u], v[u], g, dt, hdt, Lt, D.walls != 0);
-                }
+                for (int k = 0; k < nmd; ++k) flow_step<T>(x[u], v[u], g, dt, hdt, Lt, D.walls != 0);
         return;
     }
     T m[P][3];
