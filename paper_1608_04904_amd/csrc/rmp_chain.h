@@ -1265,7 +1265,14 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
         }
 
     double eu = 0.0, ef = 0.0;
+    // The loop's code starts on a 64-byte line, in the one- and two-colloid
+    // variants 16 bytes into it: where its branch targets fall in a line of the
+    // instruction fetch changes a step's time by up to 3 % (32^3 with one dimer
+    // FP64 289 us an interval, 286 so; iterative RATTLE 6890 and with the 16 bytes
+    // 7120), and would otherwise follow from the length of the code before it.
+    [[clang::code_align(64)]]
     for (int step = 0; step < nmd; ++step) {
+        if constexpr (NC > 0) __asm__ __volatile__(".rept 4\n s_nop 0\n .endr");
         double (*Xw)[3] = S.sXw[(step + 1) & 1];
         const int64_t md = md0 + step;
         // colloids (wave 0, in registers): half kick, drift, RATTLE
