@@ -1185,8 +1185,9 @@ rmp_status batch_init(rmp_batch* b, int32_t nslots, int32_t precision, void* ctl
         rmp_status sst = take_scratch_address(dev);
         if (sst != RMP_OK) return sst;
         HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-        // per shape, for the generic and the one- or two-colloid variants
-        // (the ticketed instantiations use the same resources)
+        // per shape, for the generic and the one- or two-colloid variants: up to
+        // these the launch is not ticketed (the ticketed instances, which need
+        // not all be resident, have registers for more waves)
         int per[2][5] = {};
         if (precision == 64) {
             HIPCHK(occupancy_of<double>(per));

@@ -178,7 +178,6 @@ __device__ __forceinline__ void normals3(const uint64_t w[4], double z[3])
     z[2] = r1 * cos(t1);
 }
 
-// replica owning work item `item`: largest r with prefix[r] <= item
 // Position of cell (x, y, z) along the Hilbert curve of the 2^bits cube
 // (J. Skilling, "Programming the Hilbert curve", AIP Conf. Proc. 707 (2004)
 // 381): undo the excess work level by level from the top (invert the low
@@ -210,6 +209,7 @@ __device__ __forceinline__ uint32_t hilbert_index(uint32_t x, uint32_t y, uint32
     return h;
 }
 
+// replica owning work item `item`: largest r with prefix[r] <= item
 __device__ __forceinline__ int find_rep(const int32_t* prefix, int nrep, int item)
 {
     int lo = 0, hi = nrep - 1;

@@ -1684,7 +1684,7 @@ __global__ __launch_bounds__(NT, RULE ? 3 : 4) void k_collide_dense(Work w, int 
     }
 }
 
-// The cells that k_collide found beyond a group's capacity (a bit per
+// The cells that k_collide_dense found beyond a group's capacity (a bit per
 // tile-local cell in bigmask[tile]).  Workgroup w looks at tiles
 // [64 w, 64 w + 64) of the launch and collides each such cell with all its
 // threads (collide_big_cell); the cell's temperature, reaction energy and

@@ -36,36 +36,11 @@ __device__ __forceinline__ double wave_tree_sum(double v)
     return a + b;
 }
 
-// wave_tree_sum of N independent values, level by level so that the N
-// dependent chains overlap (each value's additions are the same as above)
-template <int N>
-__device__ __forceinline__ void wave_tree_sum_n(double (&v)[N])
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = v[i] + dpp_d<0xB1, 0xF>(v[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = v[i] + dpp_d<0x4E, 0xF>(v[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = v[i] + dpp_d<0x141, 0xF>(v[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = v[i] + dpp_d<0x140, 0xF>(v[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = v[i] + dpp_d<0x142, 0xA>(v[i]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const double a = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[i]), 31),
-                                          __builtin_amdgcn_readlane(__double2loint(v[i]), 31));
-        const double b = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[i]), 63),
-                                          __builtin_amdgcn_readlane(__double2loint(v[i]), 63));
-        v[i] = a + b;
-    }
-}
-
 // wave_tree_sum of N = 4 or 8 values, lane l returning that of value l % N: at
 // each of the first levels a lane keeps one of two values and gives the other
 // to its partner, so that a level handles half the values of the one before
-// (8 values: 64 instructions where wave_tree_sum_n takes 160).  The same two
-// operands are added at every level as above.
+// (8 values: 64 instructions, one after the other 160).  The same two operands
+// are added at every level as above.
 __device__ __forceinline__ double sel_d(bool c, double a, double b)
 {
     return __hiloint2double(c ? __double2hiint(a) : __double2hiint(b), c ? __double2loint(a) : __double2loint(b));
