@@ -55,11 +55,13 @@ REC_BYTES = {8: 64, 4: 32}          # a particle's record
 def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
                       flow: bool = False) -> float:
     """Bytes a kernel must move per launch given its inputs and outputs (not
-    counting re-reads), tb = bytes of the storage type, R = record:
-    stream      per free particle: read x, v (6 tb) + state (1), write x
-                (3 tb) + key/rank (8); cell counters 8 B per cell.  With a
-                flow every particle also writes v (12 tb + 9).  (In small
-                systems it is a part of the chain's launch.)
+    counting re-reads, nor the fields that share a record with those used), tb =
+    bytes of the storage type, R = record:
+    stream      per free particle: read x, v (6 tb) + list bit (counted as 1),
+                write x (3 tb) + key/rank (8); cell counters 8 B per cell.  With
+                a flow every particle also writes v (12 tb + 9).  (In small
+                systems it is a part of the chain's launch; "stream_bin" is its
+                name in older profiles.)
     perm        per particle: read key/rank (8), cell start (4); write the
                 array position (4).
     collide     per particle: read the record (R); write x, v (6 tb), id (4),
@@ -67,7 +69,8 @@ def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
                 the counter (4).
     scan_final  per cell: read count (4), write start (4).
     chain       per list entry: read and write x, v, state (12 tb + 2).
-    analysis    per particle: read x (3 tb) and state (1)."""
+    analysis    per particle: read x (3 tb) and state (1).
+    close       per particle: a list bit; per 1024 particles: a count (4)."""
     nf = max(n - n_cand, 0)
     R = REC_BYTES[tb]
     if kernel in ("stream", "stream_bin"):
@@ -83,14 +86,14 @@ def algorithmic_bytes(kernel: str, n: int, ncell: int, tb: int, n_cand: int,
     if kernel == "analysis":
         return n * (3 * tb + 1)
     if kernel == "close":
-        return n * 1 + 8 * math.ceil(n / 1024)
+        return n / 8 + 4 * math.ceil(n / 1024)
     return 0.0
 
 
 def method_bytes_per_particle(tb: int, ncell_per_particle: float) -> float:
     """Bytes per particle and interval that the method itself must move with
     fused-interval streaming (the algorithmic floor, independent of this
-    implementation's staging): streaming 9 tb + 9, cell key/rank 8, scatter
+    implementation's records): streaming 9 tb + 9, cell key/rank 8, scatter
     of a 12-byte index, cell scan 12 per cell, and the collision's gather
     and write of the payload (4 + 2 P, P = 6 tb + 5: x, v, id, state)."""
     P = 6 * tb + 5
