@@ -217,7 +217,6 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
     const gptr<uint64_t> bits = G(list_bits(D, coll)) + (int64_t)chunk * (CHUNK / 64);
     const gptr<uint64_t> spent = G(list_bits(D, coll + 1)) + (int64_t)chunk * (CHUNK / 64);
     const uint64_t word = chunk < nch ? bits[lane >> 2] : 0ull;
-    const bool clear = chunk < nch && lane < CHUNK / 64 && spent[lane] != 0ull;
     const uint32_t mine = chunk < nch ? cnt[chunk] : 0u;
     uint32_t pre = 0, total = 0;
     if (!counted) {
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(1024) void k_close(Work w, int after_collision)
         s_cnt[wave] = mine;
         if (chunk < nch) nxt[chunk] = 0u;
     }
-    if (clear) spent[lane] = 0ull;
+    if (chunk < nch && lane < CHUNK / 64) spent[lane] = 0ull;
     if (__syncthreads_or(mine != 0u || !counted)) {
         if (counted) {
             for (int k = t; k < c0; k += 4 * 1024) {
