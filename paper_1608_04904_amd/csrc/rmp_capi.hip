@@ -351,6 +351,10 @@ constexpr int64_t CHAIN_PRIO_MAX_PARTICLES = (int64_t)1 << 22;
 // particles from which the streaming is a launch of its own next to the MD
 // chain: its kernel then has more than four waves per SIMD to hold, while in
 // the chain's launch it gets the chain's registers, two waves per SIMD
+// (an interval with one sphere FP64 in us, on the side stream and in the chain's
+// launch: 327,680 particles 221 and 214, 1,038,230 253 and 243, 2,621,440 346 and
+// 331, 5,120,000 482 and 572; FP32 216 and 213, 248 and 235, 309 and 287, 409 and
+// 455: the two are equal near four million)
 constexpr int64_t CHAIN_SIDE_N = (int64_t)1 << 20;
 
 // Shape of the MD-chain workgroups: NT threads with K list entries each.

@@ -941,7 +941,8 @@ __device__ __forceinline__ int cell_of_slot(const uint32_t* s_start, const uint8
 // (collide_big_cell; a launch of its own for these cost 4.4 us an interval
 // even where there are none).
 // Bound by memory: the records once in and once out, 2.8 GB in FP64 for 20.97 M
-// particles, 530 us at the rate of a copy, measured 664 (FP32 426).  Scattering
+// particles, 530 us at the rate of a copy, measured 630 to 665 (FP32 405 to 440,
+// where the gather fetches three times the records).  Scattering
 // the records into cell order first and reading them back cost 557 + 714.
 constexpr int RUN_CELLS = 24;        // cells per run at most
 

@@ -155,7 +155,7 @@ struct Share {
 // a word per wave.
 // A wave reads and writes its 64 records through LDS so that each instruction
 // covers a contiguous kilobyte (one lane a record: 80 us more).
-// 20.97 M particles, 50 drifts: FP64 633 us, FP32 410.  The records, read whole
+// 20.97 M particles, 50 drifts: FP64 630 to 650 us, FP32 410 to 425.  The records, read whole
 // and half written, are 2.0 and 1.0 GB, 380 and 190 us at the rate of a copy;
 // with one drift instead of 50 it takes 540, and the draws for the cells cost
 // about 30.
