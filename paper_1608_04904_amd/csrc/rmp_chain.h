@@ -1417,7 +1417,7 @@ __device__ __forceinline__ void chain_body(Work w, int g, const RepDesc& D, cons
             rb[i].x[d] = x[j][d];
             rb[i].v[d] = v[j][d];
         }
-        rb[i].st = (uint32_t)st[j];
+        rb[i].st = (uint32_t)st[j] & 3u;
         uint32_t key = cell_key(D, (double)x[j][0], (double)x[j][1], (double)x[j][2], s3);
         const uint32_t rank = __hip_atomic_fetch_add(G(D.count) + key, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         G(D.keyrank)[i] = ((uint64_t)key << 32) | rank;

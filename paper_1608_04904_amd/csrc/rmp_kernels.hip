@@ -710,11 +710,26 @@ __device__ __forceinline__ double ordered_sums(double* buf, int cap, int nn, F f
 // wave's 128, in the workgroup form 512).  Its particles go to their output
 // slots in the stable order, found by counting ranks of the old indices; then
 // the sequential sums over them in that order, their terms staged in LDS; then
-// every particle in place.  buf: LDS of 3 cap doubles, cap a multiple of 4.
+// every particle in place.  buf: LDS of 3 cap doubles, cap a multiple of 4; s_n
+// holds the axis, s_u between plates the virtual momentum's normals (big_draws).
 // Bound by the comparisons of the ranks and the chains of additions.  (One
 // thread reading the records for the sums, the indices read from memory: 512
 // cells of 200 in 32^3 cells, 711 us an interval, under the thermostat 5920; now
 // 163 and 208.)
+template <int RULE, bool FLOW>
+__device__ __forceinline__ void big_draws(const RepDesc& D, int64_t coll, int64_t cell, double* s_u, double* s_n)
+{
+    if (threadIdx.x != 0) return;
+    if (RULE == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_n);
+    if (FLOW && D.walls) {
+        uint64_t wv[4];
+        philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
+        double z[3];
+        normals3(wv, z);
+        for (int d = 0; d < 3; ++d) s_u[d] = z[d];
+    }
+}
+
 template <class T, int RULE, int NT, bool FLOW>
 __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int nc, const double (*s_Xw)[3],
                                  int64_t coll, int64_t cell, uint32_t q0, int nn, double* buf, int cap,
@@ -774,11 +789,8 @@ __device__ void collide_big_cell(const RepDesc& D, const ColloidParams* cp, int 
     if (t < 3) {
         double um = S / (double)nn;
         if (FLOW && virt) {
-            uint64_t wv[4]; double z[3];
-            philox<true>((uint64_t)coll, (uint64_t)cell, 0, D.seed, TAG_VIRT, wv);
-            normals3(wv, z);
             const double sd = sqrt((double)(D.wall_n0 - nn)) * D.vscale;
-            um = (S + (sd * (t == 0 ? z[0] : t == 1 ? z[1] : z[2]))) / (double)D.wall_n0;
+            um = (S + (sd * s_u[t])) / (double)D.wall_n0;
         }
         if (!isfinite(um)) atomicOr(&rs->flags, RMP_FLAG_NONFINITE);
         s_u[t] = um;
@@ -1340,7 +1352,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 && RULE == 0 ? 5 : 4) void k_col
             const int64_t cell = D.hbits == KEY_ROW ? c0 + k : D.cell_of[c0 + k];
             const uint32_t q0b = D.start[c0 + k];
             const int nn = (int)(D.start[c0 + k + 1] - q0b);
-            if (RULE == 0 && t == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_bn);
+            big_draws<RULE, FLOW>(D, coll, cell, s_bu, s_bn);
             __syncthreads();
             collide_big_cell<T, RULE, NT, FLOW>(D, cp, nc, Xw, coll, cell, q0b, nn, buf, BIG_CAP, s_bu, s_bn, &s_bflip, b_sum,
                                           b_cells, b_du, b_flip);
@@ -1736,7 +1748,7 @@ __global__ __launch_bounds__(256) void k_collide_big(Work w, int n_items)
             const int64_t cell = D.hbits == KEY_ROW ? c0 + ga : D.cell_of[c0 + ga];
             const uint32_t q0 = D.start[c0 + ga];
             const int nn = (int)(D.start[c0 + ga + 1] - q0);
-            if (RULE == 0 && t == 0) marsaglia_axis<true>(D.seed, (uint64_t)coll, (uint64_t)cell, s_n);
+            big_draws<RULE, true>(D, coll, cell, s_u, s_n);
             __syncthreads();
             collide_big_cell<T, RULE, NT, true>(D, cp, nc, s_Xw, coll, cell, q0, nn, s_buf, BIG_CAP, s_u, s_n, &s_flip,
                                           t_sum, t_cells, du_sum, n_flip);
